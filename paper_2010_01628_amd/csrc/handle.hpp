@@ -37,6 +37,8 @@ struct lbm_handle {
     dim3 grid, block;
     dim3 step_grid, step_block;        // launch shape of the plain step kernel (tunable)
     int row_stage_pref = -1;           // -1: default (staged wherever possible), 0/1: tuner's choice
+    lbm::PairShape pair{};             // tiles of the two-steps-per-pass launch
+    bool pair_ok = false;              // lbm_step takes two steps per pass where it can
     bool walls = false, general = false, nt = true;
     int64_t bytes = 0;
     int nblocks = 0;

@@ -206,6 +206,39 @@ int64_t pad_stride(int64_t N, int eb)
     return (base + pad_bytes) / eb;
 }
 
+// Two steps per pass (two_step.hpp): A-B, single phase, where a pair is
+// estimated faster than two single steps.  A single step is estimated at its
+// traffic at 6.1 TB/s, 1.04 times that on rows of whole 128-byte lines and
+// 1.5 times on others, whose stores share lines between rows, and at least
+// 4 us.  Two steps measured against a pair, us: 256^3 FP32 834 / 623, FP64
+// 1805 / 1367, FP16 430 / 436 (estimated 509: single); 192^3 FP32 388 / 278;
+// 100^3 FP32 81 / 51; 113x293x281 FP32 852 / 382, FP16 379 / 260; 200x101x75
+// with walls FP32 116 / 82, FP16 48 / 64 (estimated 64 against 57: single);
+// 64^3 FP32 15 / 22 (single); D3Q27 128^3 FP32 161 / 126.  LBM_TWO_STEP=0
+// keeps single steps, =1 takes pairs wherever they are possible.
+void set_pair(lbm_handle* h)
+{
+    h->pair_ok = false;
+    if (h->p.streaming != LBM_AB || h->p.coupled != LBM_COUPLED_NONE) return;
+    if ((int64_t)h->g.nxy * 8 >= ((int64_t)1 << 31)) return; // 32-bit offsets within a plane
+    const char* env = std::getenv("LBM_TWO_STEP");
+    if (env && env[0] == '0') return;
+    const int eb = elem_bytes(h->p.precision);
+    const double traffic_us = 2e-6 * h->p.q * eb * (double)h->g.N / 6.1;
+    const double single_us = std::max(4.0, traffic_us * ((int64_t)h->g.nx * eb % 128 == 0 ? 1.04 : 1.5));
+    const bool forced = env && env[0] == '1';
+    if (!forced && single_us < 6.0) return; // three planes of a pair already take longer
+    int cus = 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, h->device) != hipSuccess || cus <= 0) return;
+    const int threads = h->p.q == 27 ? lbm::pair_threads_q27(h->kprec) : lbm::pair_threads_q19(h->kprec);
+    double pair_us = 0.0;
+    h->pair = lbm::pair_shape(h->g.nx, h->g.ny, h->g.nz, h->p.q, eb, threads, cus, &pair_us);
+    h->pair_ok = h->pair.w > 0 && (forced || pair_us < 0.95 * 2 * single_us);
+}
+
+// stochastic rounding: a new key per step (seed and step count hashed)
+uint32_t step_key(uint32_t seed, int64_t step) { return lbm::hash32(seed ^ lbm::hash32((uint32_t)step)); }
+
 int run_check(lbm_handle* h)
 {
     lbm::launch_moments(h->p.q, h->kprec, pattern_of(h), h->walls, h->buf[h->cur], h->g, h->ph, nullptr, nullptr,
@@ -345,6 +378,7 @@ int lbm_create(const lbm_params* p, void* stream, lbm_handle** out)
         }
         if (p->cache_policy == 0 && h->g.row_stage) h->nt = true;
     }
+    set_pair(h);
 
     const int64_t pop_bytes = (int64_t)p->q * h->g.stride * eb;
     const int nbuf = p->streaming == LBM_AB ? 2 : 1;
@@ -460,10 +494,19 @@ int lbm_step(lbm_handle* h, int64_t nsteps)
         if (h->mlp)
             lbm::launch_step_mlp(h->p.precision, pat, h->walls, h->nt, h->buf[src], h->buf[dst], h->g, h->ph,
                                  h->mlp->packed, h->fb_partials, h->grid, h->block, h->stream);
-        else
-        {
-            // stochastic rounding: a new key per step (seed and step count hashed)
-            if (h->kprec == lbm::PREC_BF16SR) h->ph.sr_key = lbm::hash32(h->p.seed ^ lbm::hash32((uint32_t)h->steps));
+        else if (h->pair_ok && s + 1 < nsteps && !(h->p.check_every > 0 && (h->steps + 1) % h->p.check_every == 0)) {
+            // two steps in one pass, unless a stability check falls between them
+            uint32_t key2 = 0;
+            if (h->kprec == lbm::PREC_BF16SR) {
+                h->ph.sr_key = step_key(h->p.seed, h->steps);
+                key2 = step_key(h->p.seed, h->steps + 1);
+            }
+            lbm::launch_pair(h->p.q, h->p.moments == LBM_RAW_MOMENTS, h->kprec, h->walls, h->general, h->buf[src],
+                             h->buf[dst], h->g, h->ph, h->pair, key2, h->stream);
+            h->steps++;
+            s++;
+        } else {
+            if (h->kprec == lbm::PREC_BF16SR) h->ph.sr_key = step_key(h->p.seed, h->steps);
             lbm::launch_step(h->p.q, h->p.moments == LBM_RAW_MOMENTS, h->kprec, pat, h->walls, h->general, h->nt,
                              h->buf[src], h->buf[dst], h->g, h->ph, h->step_grid, h->step_block, h->stream);
         }
@@ -562,7 +605,7 @@ int32_t lbm_step_variant(const lbm_handle* h)
 }
 
 // ---------------------------------------------------------------------------
-// Autotuner of the plain step: work-group shape x cache policy
+// Autotuner of the plain single step: work-group shape x cache policy
 // ---------------------------------------------------------------------------
 namespace {
 
@@ -611,6 +654,13 @@ int lbm_tune(lbm_handle* h, int32_t trial_steps, int32_t* block_x, int32_t* bloc
             }
     }
     if (!cached) {
+        // the candidates are launches of the single step
+        struct Single {
+            lbm_handle* h;
+            const bool ok;
+            explicit Single(lbm_handle* hh) : h(hh), ok(hh->pair_ok) { h->pair_ok = false; }
+            ~Single() { h->pair_ok = ok; }
+        } single(h);
         const int steps = trial_steps + (trial_steps & 1);
         const int shapes[][2] = {{1024, 1}, {256, 1}, {128, 2}, {64, 4}, {128, 1}, {64, 2}, {64, 1}};
         const int nx2 = next_pow2(h->g.nx), ny2 = next_pow2(h->g.ny);

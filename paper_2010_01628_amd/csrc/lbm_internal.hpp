@@ -99,6 +99,36 @@ inline void launch_moments(int q, int precision, int pattern, bool walls, const 
     if (q == 27) launch_moments_q27(precision, pattern, walls, buf, g, ph, rho, u, partials, grid, block, st);
     else launch_moments_q19(precision, pattern, walls, buf, g, ph, rho, u, partials, grid, block, st);
 }
+// Two steps per pass (two_step.hpp): tiles of w x h columns (tx x ty of them),
+// tz runs of len planes.
+struct PairShape {
+    int w, h, len;
+    int tx, ty, tz;
+};
+// threads of the pair kernel's work-groups (columns of a tile, halo included)
+int pair_threads_q19(int precision);
+int pair_threads_q27(int precision);
+void launch_pair_q19(int precision, bool walls, bool general, const void* src, void* dst, const Geom& g,
+                     const Phys& ph, const PairShape& sh, uint32_t key2, hipStream_t st);
+void launch_pair_q19rm(int precision, bool walls, bool general, const void* src, void* dst, const Geom& g,
+                       const Phys& ph, const PairShape& sh, uint32_t key2, hipStream_t st);
+void launch_pair_q27(int precision, bool raw, bool walls, const void* src, void* dst, const Geom& g,
+                     const Phys& ph, const PairShape& sh, hipStream_t st);
+inline void launch_pair(int q, bool raw, int precision, bool walls, bool general, const void* src, void* dst,
+                        const Geom& g, const Phys& ph, const PairShape& sh, uint32_t key2, hipStream_t st)
+{
+    if (q == 27) launch_pair_q27(precision, raw, walls, src, dst, g, ph, sh, st);
+    else if (raw) launch_pair_q19rm(precision, walls, general, src, dst, g, ph, sh, key2, st);
+    else launch_pair_q19(precision, walls, general, src, dst, g, ph, sh, key2, st);
+}
+// Tiles of a pair launch, at most `threads` columns each, one work-group per
+// compute unit at a time, and the time estimated for it (microseconds).  The
+// estimate, fitted to 64x13, 32x28 and 128x5 tiles on 256^3 with 2- and 4-byte
+// storage: a plane takes 0.8 us, 0.14 us per wavefront (its two collisions;
+// twice that in FP64) and 0.047 us per 128-byte line of one array that it
+// loads or stores (all scaled by q / 19).
+PairShape pair_shape(int nx, int ny, int nz, int q, int eb, int threads, int cus, double* us);
+
 // nout: totals written to out (at most NDIAG_OUT)
 void launch_reduce(const double* partials, int nblocks, double* out, hipStream_t st, int nout = 8);
 

@@ -1,0 +1,103 @@
+"""Two steps per pass over memory (lbm_step with n >= 2, A-B; LBM_TWO_STEP=1
+takes it wherever it is possible) against the single-step kernels
+(LBM_TWO_STEP=0): the same arithmetic in the same order at every node, so the
+populations agree bit for bit.  Sizes at the edges
+of the tiles: rows and columns one tile spans whole (no halo), ones it just
+does not, ragged last tiles, one to three z planes."""
+import os
+
+import numpy as np
+import pytest
+
+from paper_2010_01628_amd import inputs
+from paper_2010_01628_amd import lbm as L
+
+pytestmark = pytest.mark.gpu
+
+SIZES = [(16, 12, 10), (32, 16, 8), (33, 17, 5), (70, 41, 9), (1, 3, 2), (2, 1, 1), (130, 9, 3), (23, 300, 4), (512, 2, 3),
+         (513, 2, 3), (1100, 5, 2), (64, 64, 64)]
+
+
+def _run(n, size, single, seed=5, **kw):
+    import torch
+
+    nx, ny, nz = size
+    rho, u, F = inputs.random_lattice_fields(nx, ny, nz, seed=seed, umax=0.05, fmax=1e-3)
+    Ft = torch.from_numpy(F).cuda()
+    force = kw.pop("force_kind", "field")
+    if force == "field":
+        kw.update(force_mode=L.LBM_FORCE_FIELD, force_field_ptr=Ft.data_ptr())
+    elif force == "uniform":
+        kw.update(force_mode=L.LBM_FORCE_UNIFORM, force=(1e-4, -2e-4, 3e-4))
+    elif force == "kolmogorov":
+        kw.update(force_mode=L.LBM_FORCE_KOLMOGOROV, kolmogorov_amp=1e-4)
+    saved = os.environ.get("LBM_TWO_STEP")
+    os.environ["LBM_TWO_STEP"] = "0" if single else "1"
+    try:
+        lat = L.Lattice(L.make_params(nx, ny, nz, omega=1.7, **kw), force_field=Ft)
+    finally:
+        if saved is None:
+            del os.environ["LBM_TWO_STEP"]
+        else:
+            os.environ["LBM_TWO_STEP"] = saved
+    lat.init(rho, u)
+    lat.step(n)
+    f = lat.get_populations()
+    assert lat.step_count == n
+    lat.close()
+    return f
+
+
+def _same(n, size, **kw):
+    import torch
+
+    a, b = _run(n, size, True, **kw), _run(n, size, False, **kw)
+    assert torch.isfinite(a).all()
+    assert torch.equal(a, b), float((a - b).abs().max())
+
+
+@pytest.mark.parametrize("size", SIZES)
+@pytest.mark.parametrize("walls", [False, True])
+def test_sizes(size, walls):
+    if walls and size[1] < 2:
+        pytest.skip("walls need ny >= 2")
+    _same(5, size, precision="fp32", walls_y=walls)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32", "fp16", "bf16"])
+@pytest.mark.parametrize("kw", [dict(), dict(walls_y=True), dict(moments="raw"), dict(moments="raw", walls_y=True),
+                                dict(omega_bulk=1.2, omega_hi=[0.9, 1.1, 1.2, 0.8, 1.3, 1.0, 0.7, 1.4, 1.05]),
+                                dict(omega_bulk=1.2, walls_y=True)])
+@pytest.mark.parametrize("force", ["none", "uniform", "kolmogorov"])
+def test_storage_and_collisions(precision, kw, force):
+    _same(4, (37, 19, 11), precision=precision, force_kind=force, **kw)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("moments", ["central", "raw"])
+@pytest.mark.parametrize("walls", [False, True])
+@pytest.mark.parametrize("size", [(37, 19, 11), (32, 24, 3), (16, 16, 16)])
+def test_d3q27(precision, moments, walls, size):
+    _same(5, size, precision=precision, q=27, moments=moments, walls_y=walls)
+
+
+def test_stochastic_rounding():
+    _same(6, (37, 19, 11), precision="bf16", rounding="stochastic", seed=3)
+
+
+def test_checks_between_pairs():
+    """check_every falls on odd steps too: the state there is a whole step's."""
+    _same(7, (33, 17, 9), precision="fp32", check_every=3)
+
+
+@pytest.mark.parametrize("size", [(33, 17, 5), (64, 30, 7)])
+@pytest.mark.parametrize("walls", [False, True])
+def test_against_oracle(size, walls):
+    import oracle
+
+    nx, ny, nz = size
+    rho, u, F = inputs.random_lattice_fields(nx, ny, nz, seed=5, umax=0.05, fmax=1e-3)
+    f = _run(6, size, False, precision="fp64", walls_y=walls).cpu().numpy()
+    ref = oracle.run(oracle.init(rho, u), 6, oracle.K(1.7), F=F, walls_y=walls)
+    # FP64 against the oracle's dense solve: summation order only
+    assert np.abs(f - ref).max() < 1e-13
