@@ -915,10 +915,10 @@ int lbm_mlp_accumulate_grad(lbm_mlp* m, lbm_handle* h, const float* target, cons
     int rc = training_checks(m, h, sigma, 1, isig);
     if (rc) return rc;
     const lbm::Geom& g = h->g;
-    const int nwb = ((g.nx + 63) / 64) * g.ny * g.nz; // backward: one wavefront per block
+    const int nwb = lbm::train_waves(g), nlp = lbm::train_loss_parts(g);
     rc = grow((void**)&m->gbuf, m->gbuf_elems, (int64_t)2 * 19 * g.N, sizeof(float));
     if (!rc) rc = grow((void**)&m->grad_parts, m->grad_parts_n, (int64_t)nwb * LBM_MLP_NPARAM, sizeof(float));
-    if (!rc) rc = grow((void**)&m->loss_parts, m->loss_parts_n, h->nblocks, sizeof(double));
+    if (!rc) rc = grow((void**)&m->loss_parts, m->loss_parts_n, nlp, sizeof(double));
     if (rc) return rc;
     // the network and the lattice may use different streams: order m's work first
     HIP_TRY(hipStreamSynchronize(m->stream));
@@ -927,12 +927,12 @@ int lbm_mlp_accumulate_grad(lbm_mlp* m, lbm_handle* h, const float* target, cons
     void* post = h->buf[1 - h->cur];
     lbm::launch_step_mlp(LBM_FP32, 0, false, false, state, post, g, h->ph, m->packed, h->fb_partials, h->grid, h->block,
                          h->stream);
-    lbm::launch_train_loss((const float*)post, g, (float)h->p.rho0, target, m->inv_sigma, m->gbuf, m->loss_parts,
-                           false, nullptr, 0.0f, h->grid, h->block, h->stream);
-    lbm::launch_train_backward((const float*)state, m->gbuf, g, h->ph, m->packed, m->grad_parts, nullptr, false,
-                               h->stream);
+    lbm::launch_train_loss((const float*)post, g, (float)h->p.rho0, target, m->inv_sigma, m->gbuf, m->loss_parts, nullptr,
+                           0.0f, h->stream);
+    lbm::launch_train_backward((const float*)state, m->gbuf, g, h->ph, m->packed, m->grad_parts, nullptr, false, nullptr,
+                               nullptr, nullptr, nullptr, 0.0f, h->stream);
     lbm::launch_reduce_grad(m->grad_parts, nwb, m->grad, m->red_tmp, h->stream);
-    lbm::launch_sum_partials(m->loss_parts, h->nblocks, m->loss_dev, h->stream);
+    lbm::launch_sum_partials(m->loss_parts, 1, nlp, nlp, nlp, m->loss_dev, h->stream);
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipMemcpyAsync(m->loss_host, m->loss_dev, sizeof(double), hipMemcpyDeviceToHost, h->stream));
     HIP_TRY(hipStreamSynchronize(h->stream));
@@ -964,15 +964,15 @@ int lbm_mlp_accumulate_rollout_grad(lbm_mlp* m, lbm_handle* h, const float* targ
     }
     const lbm::Geom& g = h->g;
     const int64_t state_elems = (int64_t)19 * g.stride;
-    const int nwb = ((g.nx + 63) / 64) * g.ny * g.nz;
+    const int nwb = lbm::train_waves(g), nlp = lbm::train_loss_parts(g); // nwb >= nlp
     rc = grow((void**)&m->gbuf, m->gbuf_elems, (int64_t)2 * 19 * g.N, sizeof(float));
     if (!rc) rc = grow((void**)&m->traj, m->traj_elems, (int64_t)steps * state_elems, sizeof(float));
     if (!rc) rc = grow((void**)&m->grad_parts, m->grad_parts_n, (int64_t)nwb * LBM_MLP_NPARAM, sizeof(float));
-    if (!rc) rc = grow((void**)&m->loss_parts, m->loss_parts_n, (int64_t)steps * h->nblocks, sizeof(double));
+    if (!rc) rc = grow((void**)&m->loss_parts, m->loss_parts_n, (int64_t)steps * nwb, sizeof(double));
     if (!rc) rc = grow((void**)&m->isig_steps, m->isig_steps_n, (int64_t)steps * 10, sizeof(float));
     const bool energy = m->energy_weight > 0.0;
     if (!rc && energy) rc = grow((void**)&m->energies, m->energies_n, (int64_t)2 * steps, sizeof(double));
-    if (!rc && energy) rc = grow((void**)&m->energy_parts, m->energy_parts_n, (int64_t)2 * h->nblocks, sizeof(double));
+    if (!rc && energy) rc = grow((void**)&m->energy_parts, m->energy_parts_n, (int64_t)2 * steps * nlp, sizeof(double));
     if (!rc && m->loss_steps_n < LBM_MLP_MAX_ROLLOUT) {
         // both buffers or neither: a partial allocation is released, so a
         // later call starts from nothing again
@@ -997,38 +997,31 @@ int lbm_mlp_accumulate_rollout_grad(lbm_mlp* m, lbm_handle* h, const float* targ
         lbm::launch_step_mlp(LBM_FP32, 0, false, false, P(k), P(k + 1), g, h->ph, m->packed, h->fb_partials, h->grid,
                              h->block, h->stream);
     // kinetic energies of every state and target (energy term)
-    if (energy)
-        for (int k = 1; k <= steps; ++k) {
-            lbm::launch_train_energy(P(k), g, (float)h->p.rho0, targets + (int64_t)(k - 1) * 10 * g.N, m->energy_parts,
-                                     h->grid, h->block, h->stream);
-            lbm::launch_sum_partials(m->energy_parts, h->nblocks, m->energies + 2 * (k - 1), h->stream);
-            lbm::launch_sum_partials(m->energy_parts + h->nblocks, h->nblocks, m->energies + 2 * (k - 1) + 1, h->stream);
-        }
+    if (energy) {
+        lbm::launch_train_energy(P(1), state_elems, steps, g, (float)h->p.rho0, targets, m->energy_parts, h->stream);
+        lbm::launch_sum_partials(m->energy_parts, 2 * steps, nlp, nlp, nlp, m->energies, h->stream);
+    }
     const float ew = (float)(m->energy_weight / steps);
     // backward: A holds dL/df(t0 + k + 1); the step from P_k turns it into
-    // dL/df(t0 + k) (in B, or in dstate for k = 0), to which the loss after k
-    // steps adds its own gradient
+    // dL/df(t0 + k) (in B, or in dstate for k = 0), and adds the gradient of
+    // the loss after k steps
     float* A = m->gbuf;
     float* B = m->gbuf + (int64_t)19 * g.N;
-    auto loss_at = [&](int k, float* adj, bool acc) { // loss after k steps (k = 1..steps)
-        lbm::launch_train_loss(P(k), g, (float)h->p.rho0, targets + (int64_t)(k - 1) * 10 * g.N,
-                               m->isig_steps + (int64_t)(k - 1) * 10, adj,
-                               m->loss_parts + (int64_t)(k - 1) * h->nblocks, acc,
-                               energy ? m->energies + 2 * (k - 1) : nullptr, ew, h->grid, h->block, h->stream);
-    };
-    loss_at(steps, A, false);
+    auto target_of = [&](int k) { return targets + (int64_t)(k - 1) * 10 * g.N; }; // k = 1..steps
+    auto isig_of = [&](int k) { return m->isig_steps + (int64_t)(k - 1) * 10; };
+    auto parts_of = [&](int k) { return m->loss_parts + (int64_t)(k - 1) * nwb; };
+    auto energy_of = [&](int k) { return energy ? m->energies + 2 * (k - 1) : nullptr; };
+    lbm::launch_train_loss(P(steps), g, (float)h->p.rho0, target_of(steps), isig_of(steps), A, parts_of(steps),
+                           energy_of(steps), ew, h->stream);
     for (int k = steps - 1; k >= 0; --k) {
-        float* out = k > 0 ? B : dstate;
         // the partials of all steps add up in place; one reduction at the end
-        lbm::launch_train_backward(P(k), A, g, h->ph, m->packed, m->grad_parts, out, k < steps - 1, h->stream);
-        if (k > 0) {
-            loss_at(k, B, true);
-            std::swap(A, B);
-        }
+        lbm::launch_train_backward(P(k), A, g, h->ph, m->packed, m->grad_parts, k > 0 ? B : dstate, k < steps - 1,
+                                   k > 0 ? target_of(k) : nullptr, k > 0 ? isig_of(k) : nullptr,
+                                   k > 0 ? parts_of(k) : nullptr, k > 0 ? energy_of(k) : nullptr, ew, h->stream);
+        std::swap(A, B);
     }
     lbm::launch_reduce_grad(m->grad_parts, nwb, m->grad, m->red_tmp, h->stream);
-    for (int k = 0; k < steps; ++k)
-        lbm::launch_sum_partials(m->loss_parts + (int64_t)k * h->nblocks, h->nblocks, m->loss_steps + k, h->stream);
+    lbm::launch_sum_partials(m->loss_parts, steps, nwb, nwb, nlp, m->loss_steps, h->stream);
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipMemcpyAsync(m->loss_steps_host, m->loss_steps, sizeof(double) * steps, hipMemcpyDeviceToHost, h->stream));
     std::vector<double> en(energy ? 2 * (size_t)steps : 0);

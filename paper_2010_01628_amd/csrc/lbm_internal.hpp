@@ -136,21 +136,29 @@ void launch_reduce(const double* partials, int nblocks, double* out, hipStream_t
 constexpr int MLP_PARAMS = 1737;
 void launch_step_mlp(int precision, int pattern, bool walls, bool nt, const void* src, void* dst, const Geom& g,
                      const Phys& ph, const void* net, uint32_t* fb_partials, dim3 grid, dim3 block, hipStream_t st);
+// FP64 loss partials of launch_train_loss; wavefronts (gradient and loss
+// partials) of launch_train_backward
+int train_loss_parts(const Geom& g);
+int train_waves(const Geom& g);
 // energy (device, [E, E_target]) or nullptr: adds the energy term ew ((E - E_t) / E_t)^2
 void launch_train_loss(const float* post, const Geom& g, float rho0, const float* target, const float* inv_sigma,
-                       float* gbuf, double* loss_partials, bool accumulate, const double* energy, float ew, dim3 grid,
-                       dim3 block, hipStream_t st);
-// per-block partial kinetic energies of post (pulled) and of the target moments: partials[b], partials[nblocks + b]
-void launch_train_energy(const float* post, const Geom& g, float rho0, const float* target, double* partials,
-                         dim3 grid, dim3 block, hipStream_t st);
-// gout != nullptr: also write dL/df(t) (rollout back-propagation);
-// accumulate: add to grad_partials instead of overwriting them
+                       float* gbuf, double* loss_partials, const double* energy, float ew, hipStream_t st);
+// per-block partial kinetic energies after each of `steps` steps (posts,
+// step_stride floats apart; pulled) and of its target moments:
+// partials[2 k train_loss_parts + b] and partials[(2 k + 1) train_loss_parts + b]
+void launch_train_energy(const float* posts, int64_t step_stride, int steps, const Geom& g, float rho0, const float* targets,
+                         double* partials, hipStream_t st);
+// gout != nullptr: also write dL/df(t) (rollout back-propagation), with the
+// loss on f(t) against `target` (or nullptr) added to it; accumulate: add to
+// grad_partials instead of overwriting them
 void launch_train_backward(const float* state, const float* gbuf, const Geom& g, const Phys& ph, const void* net,
-                           float* grad_partials, float* gout, bool accumulate, hipStream_t st);
+                           float* grad_partials, float* gout, bool accumulate, const float* target, const float* inv_sigma,
+                           double* loss_partials, const double* energy, float ew, hipStream_t st);
 // tmp: reduce_grad_tmp_bytes() of device scratch
 size_t reduce_grad_tmp_bytes();
 void launch_reduce_grad(const float* partials, int nparts, double* grad, double* tmp, hipStream_t st);
-void launch_sum_partials(const double* partials, int n, double* out, hipStream_t st);
+// out[b] = sum of n partials at partials + b * row, b < rows (the last row: n_last)
+void launch_sum_partials(const double* partials, int rows, int64_t row, int n, int n_last, double* out, hipStream_t st);
 void launch_adam(float* theta, float* m1, float* m2, const double* grad, float lr, float b1, float b2, float eps,
                  float c1, float c2, hipStream_t st);
 void launch_mlp_pack(const float* theta, const float* inv_scale, void* packed, hipStream_t st);
@@ -197,7 +205,7 @@ struct lbm_mlp {
     double energy_weight = 0.0; // rollouts: weight of the kinetic-energy term
     double* energies = nullptr; // rollouts: [E, E_target] per step (device)
     int64_t energies_n = 0;
-    double* energy_parts = nullptr; // per-block partial energies of one step
+    double* energy_parts = nullptr; // per-block partial energies of every step
     int64_t energy_parts_n = 0;
 };
 

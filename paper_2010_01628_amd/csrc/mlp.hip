@@ -1,6 +1,6 @@
 // Learned-rate D3Q19 step, its training kernels, and the D3Q27 -> D3Q19
 // projection that produces training data.
-#include "dual.hpp"
+#include "cm_adjoint.hpp"
 #include "lattice_kernels.hpp"
 #include "mlp_device.hpp"
 
@@ -143,103 +143,114 @@ __global__ __launch_bounds__(256) void k_step_mlp(const S* src, S* dst, Geom g, 
 
 // ---------------------------------------------------------------------------
 // Training, reading L5: loss on the 10 raw moments of f(t+1) after one A-B
-// step from f(t) (periodic, no force).  post: post-collision buffer written by
-// k_step_mlp (A-B).  Writes dL/df_i(y, t+1) to gbuf (SoA floats, stride N) and
-// one FP64 loss partial per block; with `accumulate` the gradient is added to
-// what gbuf holds (the adjoint carried back from later steps of a rollout).
-// ---------------------------------------------------------------------------
+// step from f(t) (periodic, no force).
+//
 // Energy term (rollouts, `energy` != nullptr): the gradient of
 // ew ((E - E_t) / E_t)^2, with the kinetic energies E = 1/2 sum |j|^2 / rho of
 // the populations and E_t of the target moments (energy[0] = E, energy[1] =
 // E_t, from k_train_energy), is added per node: 2 ew (E - E_t) / E_t^2
 // (c_i . u - |u|^2 / 2).  The term's value is formed by the host.
+// ---------------------------------------------------------------------------
+// Loss of one node with populations s (deviations): its sum of squares, and
+// dL/df_i in add_to[i] += ... (or = ..., not `accumulate`).
+__device__ inline double train_loss_node(const float s[19], int n, int N, float rho0, const float* __restrict__ target,
+                                         const float* __restrict__ inv_sigma, const double* __restrict__ energy, float ew,
+                                         bool accumulate, float gi_out[19])
+{
+    // moments of f = w rho0 + s: rest part (1, 0,0,0, 1/3 x3, 0 x3) rho0
+    float m[10] = {rho0, 0, 0, 0, rho0 / 3.0f, rho0 / 3.0f, rho0 / 3.0f, 0, 0, 0};
+#pragma unroll
+    for (int i = 0; i < 19; ++i) {
+        const float cx = LatD3Q19::cx(i), cy = LatD3Q19::cy(i), cz = LatD3Q19::cz(i);
+        m[0] += s[i];
+        m[1] += cx * s[i];
+        m[2] += cy * s[i];
+        m[3] += cz * s[i];
+        m[4] += cx * cx * s[i];
+        m[5] += cy * cy * s[i];
+        m[6] += cz * cz * s[i];
+        m[7] += cx * cy * s[i];
+        m[8] += cx * cz * s[i];
+        m[9] += cy * cz * s[i];
+    }
+    double l2 = 0.0;
+    float dm[10];
+    const float two_over_n = 2.0f / (float)N;
+#pragma unroll
+    for (int k = 0; k < 10; ++k) {
+        const float r = (m[k] - target[(int64_t)k * N + n]) * inv_sigma[k];
+        l2 += (double)r * (double)r;
+        dm[k] = two_over_n * r * inv_sigma[k];
+    }
+    float ce = 0.0f, ux = 0.0f, uy = 0.0f, uz = 0.0f, u2 = 0.0f;
+    if (energy) {
+        ce = (float)(2.0 * ew * (energy[0] - energy[1]) / (energy[1] * energy[1]));
+        const float ir = 1.0f / m[0];
+        ux = m[1] * ir;
+        uy = m[2] * ir;
+        uz = m[3] * ir;
+        u2 = 0.5f * (ux * ux + uy * uy + uz * uz);
+    }
+#pragma unroll
+    for (int i = 0; i < 19; ++i) {
+        const float cx = LatD3Q19::cx(i), cy = LatD3Q19::cy(i), cz = LatD3Q19::cz(i);
+        float gi = dm[0] + cx * dm[1] + cy * dm[2] + cz * dm[3] + cx * cx * dm[4] + cy * cy * dm[5] + cz * cz * dm[6] +
+                   cx * cy * dm[7] + cx * cz * dm[8] + cy * cz * dm[9];
+        if (energy) gi += ce * (cx * ux + cy * uy + cz * uz - u2);
+        gi_out[i] = accumulate ? gi_out[i] + gi : gi;
+    }
+    return l2;
+}
+
+// node n of the lattice
+__device__ inline void node_of(const Geom& g, int n, NodeIdx& d)
+{
+    const int r = n / g.nx;
+    node_idx(g, n - r * g.nx, r % g.ny, r / g.ny, d);
+}
+
+// Loss after the last step of a rollout (or the only one) and dL/df_i(y, t+1),
+// written to gbuf (SoA floats, stride N); post: post-collision buffer written
+// by the learned step (A-B).  256 consecutive nodes per block, one FP64 loss
+// partial each.
 __global__ __launch_bounds__(256) void k_train_loss(const float* __restrict__ post, Geom g, float rho0,
                                                     const float* __restrict__ target, const float* __restrict__ inv_sigma,
                                                     float* __restrict__ gbuf, double* __restrict__ loss_partials,
-                                                    int accumulate, const double* __restrict__ energy, float ew)
+                                                    const double* __restrict__ energy, float ew)
 {
     __shared__ double red[4];
-    const int x = blockIdx.x * blockDim.x + threadIdx.x;
-    const int y = blockIdx.y * blockDim.y + threadIdx.y;
-    const int z = blockIdx.z;
-    double l2 = 0.0;
-    if (x < g.nx && y < g.ny) {
+    const int n = blockIdx.x * 256 + threadIdx.x;
+    double v = 0.0;
+    if (n < g.N) {
         NodeIdx d;
-        node_idx(g, x, y, z, d);
-        const int n = nb(d, 0, 0, 0);
-        float s[19];
+        node_of(g, n, d);
+        float s[19], gi[19];
         gather<LatD3Q19, float, AB, false>(post, g.stride, d, s);
-        // moments of f = w rho0 + s: rest part (1, 0,0,0, 1/3 x3, 0 x3) rho0
-        float m[10] = {rho0, 0, 0, 0, rho0 / 3.0f, rho0 / 3.0f, rho0 / 3.0f, 0, 0, 0};
+        v = train_loss_node(s, n, g.N, rho0, target, inv_sigma, energy, ew, false, gi);
 #pragma unroll
-        for (int i = 0; i < 19; ++i) {
-            const float cx = LatD3Q19::cx(i), cy = LatD3Q19::cy(i), cz = LatD3Q19::cz(i);
-            m[0] += s[i];
-            m[1] += cx * s[i];
-            m[2] += cy * s[i];
-            m[3] += cz * s[i];
-            m[4] += cx * cx * s[i];
-            m[5] += cy * cy * s[i];
-            m[6] += cz * cz * s[i];
-            m[7] += cx * cy * s[i];
-            m[8] += cx * cz * s[i];
-            m[9] += cy * cz * s[i];
-        }
-        float dm[10];
-        const float two_over_n = 2.0f / (float)g.N;
-#pragma unroll
-        for (int k = 0; k < 10; ++k) {
-            const float r = (m[k] - target[(int64_t)k * g.N + n]) * inv_sigma[k];
-            l2 += (double)r * (double)r;
-            dm[k] = two_over_n * r * inv_sigma[k];
-        }
-        float ce = 0.0f, ux = 0.0f, uy = 0.0f, uz = 0.0f, u2 = 0.0f;
-        if (energy) {
-            ce = (float)(2.0 * ew * (energy[0] - energy[1]) / (energy[1] * energy[1]));
-            const float ir = 1.0f / m[0];
-            ux = m[1] * ir;
-            uy = m[2] * ir;
-            uz = m[3] * ir;
-            u2 = 0.5f * (ux * ux + uy * uy + uz * uz);
-        }
-#pragma unroll
-        for (int i = 0; i < 19; ++i) {
-            const float cx = LatD3Q19::cx(i), cy = LatD3Q19::cy(i), cz = LatD3Q19::cz(i);
-            float gi = dm[0] + cx * dm[1] + cy * dm[2] + cz * dm[3] + cx * cx * dm[4] + cy * cy * dm[5] +
-                       cz * cz * dm[6] + cx * cy * dm[7] + cx * cz * dm[8] + cy * cz * dm[9];
-            if (energy) gi += ce * (cx * ux + cy * uy + cz * uz - u2);
-            float* gp = gbuf + (int64_t)i * g.N + n;
-            *gp = accumulate ? *gp + gi : gi;
-        }
+        for (int i = 0; i < 19; ++i) gbuf[(int64_t)i * g.N + n] = gi[i];
     }
-    const int tid = threadIdx.x + blockDim.x * threadIdx.y;
-    double v = l2;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    if ((tid & 63) == 0) red[tid >> 6] = v;
+    v = wave_sum(v);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
     __syncthreads();
-    if (tid == 0) {
-        double t = 0.0;
-        for (int i = 0; i < (int)((blockDim.x * blockDim.y + 63) / 64); ++i) t += red[i];
-        loss_partials[blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z)] = t / (double)g.N;
-    }
+    if (threadIdx.x == 0) loss_partials[blockIdx.x] = ((red[0] + red[1]) + (red[2] + red[3])) / (double)g.N;
 }
 
 // Per-block FP64 partial kinetic energies 1/2 |j|^2 / rho of the populations
-// pulled from post (no force) and of the target moments (rho, j): out[b] and
-// out[nblocks + b].
-__global__ __launch_bounds__(256) void k_train_energy(const float* __restrict__ post, Geom g, float rho0,
-                                                      const float* __restrict__ target, double* __restrict__ out)
+// pulled after each step (no force; blockIdx.y = step, states `stride` floats
+// apart) and of its target moments (rho, j), 256 consecutive nodes per block:
+// out[(2 step) gridDim.x + b] and out[(2 step + 1) gridDim.x + b].
+__global__ __launch_bounds__(256) void k_train_energy(const float* __restrict__ posts, int64_t step_stride, Geom g, float rho0,
+                                                      const float* __restrict__ targets, double* __restrict__ out)
 {
     __shared__ double red[2][4];
-    const int x = blockIdx.x * blockDim.x + threadIdx.x;
-    const int y = blockIdx.y * blockDim.y + threadIdx.y;
-    const int z = blockIdx.z;
+    const float* post = posts + (int64_t)blockIdx.y * step_stride;
+    const float* target = targets + (int64_t)blockIdx.y * 10 * g.N;
+    const int n = blockIdx.x * 256 + threadIdx.x;
     double e = 0.0, et = 0.0;
-    if (x < g.nx && y < g.ny) {
+    if (n < g.N) {
         NodeIdx d;
-        node_idx(g, x, y, z, d);
-        const int n = nb(d, 0, 0, 0);
+        node_of(g, n, d);
         float s[19];
         gather<LatD3Q19, float, AB, false>(post, g.stride, d, s);
         double r = rho0, jx = 0.0, jy = 0.0, jz = 0.0;
@@ -255,79 +266,105 @@ __global__ __launch_bounds__(256) void k_train_energy(const float* __restrict__ 
                      tz = target[3 * (int64_t)g.N + n];
         et = 0.5 * (tx * tx + ty * ty + tz * tz) / rt;
     }
-    const int tid = threadIdx.x + blockDim.x * threadIdx.y;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        e += __shfl_xor(e, o, 64);
-        et += __shfl_xor(et, o, 64);
-    }
-    if ((tid & 63) == 0) {
-        red[0][tid >> 6] = e;
-        red[1][tid >> 6] = et;
+    e = wave_sum(e);
+    et = wave_sum(et);
+    if ((threadIdx.x & 63) == 0) {
+        red[0][threadIdx.x >> 6] = e;
+        red[1][threadIdx.x >> 6] = et;
     }
     __syncthreads();
-    if (tid == 0) {
-        double a = 0.0, b = 0.0;
-        for (int i = 0; i < (int)((blockDim.x * blockDim.y + 63) / 64); ++i) {
-            a += red[0][i];
-            b += red[1][i];
-        }
-        const int bid = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
-        const int nb_ = gridDim.x * gridDim.y * gridDim.z;
-        out[bid] = a;
-        out[nb_ + bid] = b;
+    if (threadIdx.x < 2) {
+        const double* r = red[threadIdx.x];
+        out[(int64_t)(2 * blockIdx.y + threadIdx.x) * gridDim.x + blockIdx.x] = (r[0] + r[1]) + (r[2] + r[3]);
     }
 }
 
-// Backward pass, one wavefront per block (64 nodes): recompute the forward
-// state from f(t), pull dL/df*_i(x) = dL/df_i(x + c_i, t+1), form
+// Backward pass, one wavefront per block (64 consecutive nodes): recompute the
+// forward state from f(t), pull dL/df*_i(x) = dL/df_i(x + c_i, t+1), form
 // dL/domega_j = kbar_{10+j} (-(k_{10+j} - k_eq) - R_{10+j}/2) with
 // kbar = S(+u)^T M^-T gbar, then back-propagate through the network.  Writes
 // this wavefront's 1737 gradient entries to grad_partials[wave].
 //
-// PROP (rollouts): also dL/df_j(x, t), written to gout[j N + x].  It has two
-// parts: the collision's own dependence on the populations at fixed rates,
-// and the dependence through the rates (features -> network -> rates).  The
-// first is the directional derivative of the collision along each of the 19
-// unit vectors, by evaluating it on dual numbers, contracted with gbar; the
-// second contracts the same directional derivatives of the 11 raw features
-// with xbar = dL/dx, which the network's backward pass gives (ReLU masks,
-// W1^T, the input scales).  Nodes that fall back use rates 1 that do not
-// depend on the state, and take only the first part.
+// PROP (rollouts): also dL/df_j(x, t), written to gout[j N + x]: the
+// collision's adjoint (cm_adjoint.hpp), at fixed rates and through the
+// features, whose dL/dx the network's backward pass gives (ReLU masks, W1^T,
+// the input scales).  Nodes that fall back use rates 1 that do not depend on
+// the state.  With `target` (every step but the first) the loss on f(t)
+// itself, whose populations the wavefront has gathered, is added to gout, and
+// its sum of squares goes to loss_partials[wave].
+//
+// What bounds it: latency; a 32^3 step is 512 wavefronts, two per compute
+// unit, each a chain of loads, products through LDS and two collisions'
+// arithmetic.  32^3, us per step: 47 with one directional derivative of the
+// collision per population and a wavefront per row of 32 nodes; 18 with the
+// collision's adjoint and 64 consecutive nodes; 14.6 with all loads (the
+// network, the old gradient partials) issued first; 12.8 with dL/dx as a
+// product.  The loss on f(t) and the energies were three more launches per
+// step (15 us).
+struct TrainLoss {
+    const float* target;    // NULL: no loss on f(t)
+    const float* inv_sigma;
+    const double* energy;   // or NULL
+    float ew;
+    double* partials;
+};
 template <bool PROP>
 __global__ __launch_bounds__(64) void k_train_backward(const float* __restrict__ state, const float* __restrict__ gbuf,
                                                        Geom g, Phys ph, const MlpPacked* __restrict__ net,
                                                        float* __restrict__ grad_partials, float* __restrict__ gout,
-                                                       int accumulate)
+                                                       int accumulate, TrainLoss tl)
 {
     const float rho0 = (float)ph.rho0;
     __shared__ MlpPacked snet;
     __shared__ uint16_t tx[MLP_TILE], th1[MLP_TILE], th2[MLP_TILE], tdz[MLP_TILE], tdh[MLP_TILE];
-    __shared__ float tz[64 * MLP_NOUT];
-    load_net(reinterpret_cast<uint32_t*>(&snet), net, (int)(sizeof(MlpPacked) / 4));
+    __shared__ float tz[64 * MLP_NIN];
     const int l = threadIdx.x;
-    const int xr = blockIdx.x * 64 + l;
-    const int yr = blockIdx.y;
-    const bool valid = xr < g.nx;
-    const int x = valid ? xr : g.nx - 1;
-    const int y = yr, z = blockIdx.z;
+    const int nr = blockIdx.x * 64 + l;
+    const bool valid = nr < g.N;
+    const int n0 = valid ? nr : g.N - 1;
     NodeIdx d;
-    node_idx(g, x, y, z, d);
-    float s[19];
+    node_of(g, n0, d);
+    float s[19], gbar[19];
     gather<LatD3Q19, float, AB, false>(state, g.stride, d, s);
+    // adjoint of the streaming
+#pragma unroll
+    for (int i = 0; i < 19; ++i)
+        gbar[i] = gbuf[(int64_t)i * g.N + nb(d, LatD3Q19::cx(i), LatD3Q19::cy(i), LatD3Q19::cz(i))];
+    // the network, and with `accumulate` the partials of the later steps, which
+    // this step's are added to: everything the wavefront reads is in flight at once
+    constexpr int NCHUNK = (int)sizeof(MlpPacked) / 16;
+    uint4 nc[(NCHUNK + 63) / 64];
+#pragma unroll
+    for (int c = 0; c < (NCHUNK + 63) / 64; ++c) nc[c] = reinterpret_cast<const uint4*>(net)[min(c * 64 + l, NCHUNK - 1)];
+    float* gp = grad_partials + (int64_t)blockIdx.x * MLP_NPARAM;
+    const int col = l & 31, row4 = 4 * (l >> 5); // accumulator register r: row 8 (r / 4) + row4 + r % 4, column col
+    float g1[16], g2[16], g3[5], gb[3];
+    {
+        const float* q = gp;
+        auto old = [&](bool on, int at) { return accumulate && on ? q[at] : 0.0f; };
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int row = 8 * (r >> 2) + row4 + (r & 3);
+            g1[r] = old(col < MLP_NIN, MLP_OFF_W1 + row * MLP_NIN + col);
+            g2[r] = old(true, MLP_OFF_W2 + row * 32 + col);
+            if (r < 5) g3[r] = old(row < MLP_NOUT, MLP_OFF_W3 + row * 32 + col);
+        }
+        gb[0] = old(l < 32, MLP_OFF_B1 + l);
+        gb[1] = old(l < 32, MLP_OFF_B2 + l);
+        gb[2] = old(l < MLP_NOUT, MLP_OFF_B3 + l);
+    }
+#pragma unroll
+    for (int c = 0; c < (NCHUNK + 63) / 64; ++c) reinterpret_cast<uint4*>(&snet)[min(c * 64 + l, NCHUNK - 1)] = nc[c];
+    __syncthreads();
     CMState<float> st;
     pre_collide<float, true>(s, rho0, 0.0f, 0.0f, 0.0f, st);
     float xin[MLP_NIN], zout[MLP_NOUT], rates[MLP_NOUT];
     mlp_features(st, xin);
     mlp_forward_wave(snet, tx, th1, th2, tz, xin, zout);
     const bool fb = mlp_rates(zout, rates);
-    // adjoint of the streaming
-    float gbar[19];
-#pragma unroll
-    for (int i = 0; i < 19; ++i)
-        gbar[i] = gbuf[(int64_t)i * g.N + nb(d, LatD3Q19::cx(i), LatD3Q19::cy(i), LatD3Q19::cz(i))];
-    RawMoments<float> kb;
-    pops_from_raw_T(gbar, kb);
+    RawMoments<float> qb, kb;
+    pops_from_raw_T(gbar, qb);
+    kb = qb;
     shift_all_T(kb, st.ux, st.uy, st.uz);
     const RawMoments<float>& n = st.n;
     // no force in training: R = 0 on rows 10..18
@@ -337,23 +374,26 @@ __global__ __launch_bounds__(64) void k_train_backward(const float* __restrict__
 #pragma unroll
     for (int k = 0; k < 32; ++k) tdz[l * MLP_LDS_STRIDE + k] = (k < MLP_NOUT && active) ? f32_to_bf16(dz[k]) : 0;
     __syncthreads();
-    float* gp = grad_partials + (int64_t)(blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z)) * MLP_NPARAM;
-    // accumulate: add to the partials of earlier steps of a rollout
-    auto put = [accumulate](float* q, float v) { *q = accumulate ? *q + v : v; };
+    // column sums of a tile: each half-wave its 32 rows, then together
+    auto column_sum = [&](const uint16_t* t) {
+        float sb = 0.0f;
+#pragma unroll
+        for (int q = 0; q < 32; ++q) sb += bf16_to_f32(t[((l & 32) + q) * MLP_LDS_STRIDE + (l & 31)]);
+        return sb + __shfl_xor(sb, 32, 64);
+    };
     // dW3[o][h] = sum_n dz[n][o] h2[n][h]
     {
         const f32x16_t acc = mfma_AtB(tdz, th2);
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-            const int o = 8 * (r >> 2) + 4 * (l >> 5) + (r & 3);
-            if (o < MLP_NOUT) put(gp + MLP_OFF_W3 + o * 32 + (l & 31), acc[r]);
+            const int o = 8 * (r >> 2) + row4 + (r & 3);
+            if (r < 5 && o < MLP_NOUT) gp[MLP_OFF_W3 + o * 32 + col] = g3[r < 5 ? r : 0] + acc[r];
         }
     }
     // db3, and dh2 = (dz W3) * relu'(h2)
-    if (l < MLP_NOUT) {
-        float sb = 0.0f;
-        for (int q = 0; q < 64; ++q) sb += bf16_to_f32(tdz[q * MLP_LDS_STRIDE + l]);
-        put(gp + MLP_OFF_B3 + l, sb);
+    {
+        const float sb = column_sum(tdz);
+        if (l < MLP_NOUT) gp[MLP_OFF_B3 + l] = gb[2] + sb;
     }
 #pragma unroll
     for (int rb = 0; rb < 2; ++rb) {
@@ -370,12 +410,11 @@ __global__ __launch_bounds__(64) void k_train_backward(const float* __restrict__
     {
         const f32x16_t acc = mfma_AtB(tdh, th1);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) put(gp + MLP_OFF_W2 + (8 * (r >> 2) + 4 * (l >> 5) + (r & 3)) * 32 + (l & 31), acc[r]);
+        for (int r = 0; r < 16; ++r) gp[MLP_OFF_W2 + (8 * (r >> 2) + row4 + (r & 3)) * 32 + col] = g2[r] + acc[r];
     }
-    if (l < 32) {
-        float sb = 0.0f;
-        for (int q = 0; q < 64; ++q) sb += bf16_to_f32(tdh[q * MLP_LDS_STRIDE + l]);
-        put(gp + MLP_OFF_B2 + l, sb);
+    {
+        const float sb = column_sum(tdh);
+        if (l < 32) gp[MLP_OFF_B2 + l] = gb[1] + sb;
     }
 #pragma unroll
     for (int rb = 0; rb < 2; ++rb) {
@@ -392,50 +431,38 @@ __global__ __launch_bounds__(64) void k_train_backward(const float* __restrict__
     {
         const f32x16_t acc = mfma_AtB(tdz, tx);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int i = l & 31;
-            if (i < MLP_NIN) put(gp + MLP_OFF_W1 + (8 * (r >> 2) + 4 * (l >> 5) + (r & 3)) * MLP_NIN + i, acc[r]);
-        }
+        for (int r = 0; r < 16; ++r)
+            if (col < MLP_NIN) gp[MLP_OFF_W1 + (8 * (r >> 2) + row4 + (r & 3)) * MLP_NIN + col] = g1[r] + acc[r];
     }
-    if (l < 32) {
-        float sb = 0.0f;
-        for (int q = 0; q < 64; ++q) sb += bf16_to_f32(tdz[q * MLP_LDS_STRIDE + l]);
-        put(gp + MLP_OFF_B1 + l, sb);
+    {
+        const float sb = column_sum(tdz);
+        if (l < 32) gp[MLP_OFF_B1 + l] = gb[0] + sb;
     }
     if constexpr (PROP) {
-        // xbar = (W1^T dh1) * inv_scale: dh1 of this lane's node is row l of tdz
+        // xbar = (dh1 W1) * inv_scale, back to the node's lane through LDS
         float xbar[MLP_NIN];
 #pragma unroll
-        for (int i = 0; i < MLP_NIN; ++i) xbar[i] = 0.0f;
-        for (int o = 0; o < 32; ++o) {
-            const float dh = bf16_to_f32(tdz[l * MLP_LDS_STRIDE + o]);
+        for (int rb = 0; rb < 2; ++rb) {
+            const f32x16_t acc = mfma_xwT<32>(tdz, rb, snet.w1t, 32);
+            if (col < MLP_NIN)
 #pragma unroll
-            for (int i = 0; i < MLP_NIN; ++i) xbar[i] += dh * bf16_to_f32(snet.w1[o * 16 + i]);
+                for (int r = 0; r < 16; ++r) tz[acc_row(rb, r) * MLP_NIN + col] = acc[r];
         }
+        __syncthreads();
 #pragma unroll
-        for (int i = 0; i < MLP_NIN; ++i) xbar[i] *= snet.inv_scale[i];
-        Rates<Dual> rt = rates_of<Dual>(ph);
+        for (int i = 0; i < MLP_NIN; ++i) xbar[i] = tz[l * MLP_NIN + i] * snet.inv_scale[i];
+        Rates<float> rt = rates_of<float>(ph);
 #pragma unroll
-        for (int j = 0; j < MLP_NOUT; ++j) rt.omega_hi[j] = Dual(rates[j], 0.0f);
-#pragma unroll 1
-        for (int j = 0; j < 19; ++j) {
-            Dual sd[19];
-#pragma unroll
-            for (int i = 0; i < 19; ++i) sd[i] = Dual(s[i], i == j ? 1.0f : 0.0f);
-            CMState<Dual> sdt;
-            pre_collide<Dual, true>(sd, Dual(rho0, 0.0f), Dual(0.0), Dual(0.0), Dual(0.0), sdt);
-            Dual xd[MLP_NIN];
-            mlp_features(sdt, xd);
-            RawMoments<Dual> pd;
-            relax<Dual, true>(sdt, rt, pd);
-            post_collide_increment(sdt, pd, sd);
-            float acc = 0.0f;
-#pragma unroll
-            for (int i = 0; i < 19; ++i) acc += gbar[i] * sd[i].d;
-#pragma unroll
-            for (int k = 0; k < MLP_NIN; ++k) acc += xbar[k] * xd[k].d;
-            if (valid) gout[(int64_t)j * g.N + nb(d, 0, 0, 0)] = acc;
+        for (int j = 0; j < MLP_NOUT; ++j) rt.omega_hi[j] = rates[j];
+        collide_adjoint(st, rho0, rt, qb, kb, xbar, gbar);
+        if (tl.target) {
+            double l2 = train_loss_node(s, n0, g.N, rho0, tl.target, tl.inv_sigma, tl.energy, tl.ew, true, gbar);
+            l2 = wave_sum(valid ? l2 : 0.0);
+            if (l == 0) tl.partials[blockIdx.x] = l2 / (double)g.N;
         }
+        if (valid)
+#pragma unroll
+            for (int j = 0; j < 19; ++j) gout[(int64_t)j * g.N + n0] = gbar[j];
     }
 }
 
@@ -469,18 +496,22 @@ __global__ __launch_bounds__(256) void k_reduce_grad(const double* __restrict__ 
     grad[p] += s;
 }
 
-__global__ __launch_bounds__(256) void k_sum_partials(const double* __restrict__ partials, int n, double* __restrict__ out)
+// out[b] = sum of the n partials at partials + b * row (the last row: n_last of them), fixed order
+__global__ __launch_bounds__(256) void k_sum_partials(const double* __restrict__ partials, int64_t row, int n, int n_last,
+                                                      double* __restrict__ out)
 {
     __shared__ double red[256];
+    const double* p = partials + (int64_t)blockIdx.x * row;
+    const int count = blockIdx.x == gridDim.x - 1 ? n_last : n;
     double s = 0.0;
-    for (int i = threadIdx.x; i < n; i += 256) s += partials[i];
+    for (int i = threadIdx.x; i < count; i += 256) s += p[i];
     red[threadIdx.x] = s;
     __syncthreads();
     for (int w = 128; w > 0; w >>= 1) {
         if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
         __syncthreads();
     }
-    if (threadIdx.x == 0) *out = red[0];
+    if (threadIdx.x == 0) out[blockIdx.x] = red[0];
 }
 
 // Adam on the FP32 master parameters (FP64 gradient).
@@ -515,6 +546,7 @@ __global__ __launch_bounds__(256) void k_mlp_pack(const float* __restrict__ thet
         const uint16_t v3 = o < MLP_NOUT ? f32_to_bf16(theta[MLP_OFF_W3 + o * 32 + k]) : 0;
         out->w3[i] = v3;
         out->w3t[k * 32 + o] = v3;
+        out->w1t[k * 32 + o] = k < MLP_NIN ? f32_to_bf16(theta[MLP_OFF_W1 + o * MLP_NIN + k]) : 0;
     }
     if (t < 32) {
         out->b1[t] = theta[MLP_OFF_B1 + t];
@@ -698,30 +730,35 @@ void launch_step_mlp(int precision, int pattern, bool walls, bool nt, const void
     }
 }
 
+int train_loss_parts(const Geom& g) { return (g.N + 255) / 256; }
+int train_waves(const Geom& g) { return (g.N + 63) / 64; }
+
 void launch_train_loss(const float* post, const Geom& g, float rho0, const float* target, const float* inv_sigma,
-                       float* gbuf, double* loss_partials, bool accumulate, const double* energy, float ew, dim3 grid,
-                       dim3 block, hipStream_t st)
+                       float* gbuf, double* loss_partials, const double* energy, float ew, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_train_loss, grid, block, 0, st, post, g, rho0, target, inv_sigma, gbuf, loss_partials,
-                       (int)accumulate, energy, ew);
+    hipLaunchKernelGGL(k_train_loss, dim3(train_loss_parts(g)), dim3(256), 0, st, post, g, rho0, target, inv_sigma, gbuf,
+                       loss_partials, energy, ew);
 }
 
-void launch_train_energy(const float* post, const Geom& g, float rho0, const float* target, double* partials,
-                         dim3 grid, dim3 block, hipStream_t st)
+void launch_train_energy(const float* posts, int64_t step_stride, int steps, const Geom& g, float rho0, const float* targets,
+                         double* partials, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_train_energy, grid, block, 0, st, post, g, rho0, target, partials);
+    hipLaunchKernelGGL(k_train_energy, dim3(train_loss_parts(g), steps), dim3(256), 0, st, posts, step_stride, g, rho0,
+                       targets, partials);
 }
 
 void launch_train_backward(const float* state, const float* gbuf, const Geom& g, const Phys& ph, const void* net,
-                           float* grad_partials, float* gout, bool accumulate, hipStream_t st)
+                           float* grad_partials, float* gout, bool accumulate, const float* target, const float* inv_sigma,
+                           double* loss_partials, const double* energy, float ew, hipStream_t st)
 {
-    const dim3 grid((g.nx + 63) / 64, g.ny, g.nz);
+    const TrainLoss tl{target, inv_sigma, energy, ew, loss_partials};
+    const dim3 grid(train_waves(g));
     if (gout)
         hipLaunchKernelGGL(k_train_backward<true>, grid, dim3(64), 0, st, state, gbuf, g, ph, (const MlpPacked*)net,
-                           grad_partials, gout, (int)accumulate);
+                           grad_partials, gout, (int)accumulate, tl);
     else
         hipLaunchKernelGGL(k_train_backward<false>, grid, dim3(64), 0, st, state, gbuf, g, ph, (const MlpPacked*)net,
-                           grad_partials, gout, (int)accumulate);
+                           grad_partials, gout, (int)accumulate, tl);
 }
 
 size_t reduce_grad_tmp_bytes() { return sizeof(double) * MLP_RED_SLICES * MLP_NPARAM; }
@@ -733,9 +770,9 @@ void launch_reduce_grad(const float* partials, int nparts, double* grad, double*
     hipLaunchKernelGGL(k_reduce_grad, dim3((MLP_NPARAM + 255) / 256), dim3(256), 0, st, tmp, grad);
 }
 
-void launch_sum_partials(const double* partials, int n, double* out, hipStream_t st)
+void launch_sum_partials(const double* partials, int rows, int64_t row, int n, int n_last, double* out, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(256), 0, st, partials, n, out);
+    hipLaunchKernelGGL(k_sum_partials, dim3(rows), dim3(256), 0, st, partials, row, n, n_last, out);
 }
 
 void launch_adam(float* theta, float* m1, float* m2, const double* grad, float lr, float b1, float b2, float eps,

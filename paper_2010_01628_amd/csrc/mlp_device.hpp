@@ -47,6 +47,7 @@ struct alignas(16) MlpPacked {
     // transposed copies for the backward pass
     uint16_t w2t[32 * 32]; // [in][out]
     uint16_t w3t[32 * 32]; // [in][out (9 used)]
+    uint16_t w1t[32 * 32]; // [in (11 used)][out]
 };
 constexpr int MLP_INFER_WORDS = (int)(__builtin_offsetof(MlpPacked, w2t) / 4);
 static_assert(MLP_INFER_WORDS % 4 == 0 && sizeof(MlpPacked) % 16 == 0, "16-byte network copies");
@@ -101,11 +102,15 @@ typedef float f32x16_t __attribute__((ext_vector_type(16)));
 
 __host__ __device__ inline uint16_t f32_to_bf16(float f)
 {
+#ifdef __HIP_DEVICE_COMPILE__
+    return __builtin_bit_cast(uint16_t, (__bf16)f); // the conversion instruction: nearest even
+#else
     uint32_t u;
     __builtin_memcpy(&u, &f, 4);
     if ((u & 0x7fffffffu) > 0x7f800000u) return (uint16_t)((u >> 16) | 0x40u);
     u += 0x7fffu + ((u >> 16) & 1u);
     return (uint16_t)(u >> 16);
+#endif
 }
 __host__ __device__ inline float bf16_to_f32(uint16_t b)
 {
