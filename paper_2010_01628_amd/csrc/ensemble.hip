@@ -9,6 +9,7 @@
 // launches and the whole step is one kernel node in a captured graph.
 #include "lattice_kernels.hpp"
 #include "mlp_device.hpp"
+#include "two_step.hpp"
 
 namespace lbm {
 
@@ -67,6 +68,37 @@ __global__ __launch_bounds__(256) void k_ens_step(const S* __restrict__ src_all,
         L::template collide<R, false, Codec<S>::increment>(s, (R)rho0, R(0), R(0), R(0), ph, mac);
         scatter<L, S, AB, false, true, O32>(dst_all + bd.off, g.stride, d, s);
     }
+}
+
+// Two plain steps in one pass (two_step.hpp): one work-group per item.
+template <class L, class S>
+__global__ __launch_bounds__((pair_threads<L, S>())) __attribute__((amdgpu_waves_per_eu((pair_waves<L, S>())))) void k_ens_pair(
+    const S* __restrict__ src_all, S* __restrict__ dst_all, const BoxDesc* __restrict__ boxes,
+    const EnsPairItem* __restrict__ items, float rho0)
+{
+    constexpr int T = pair_threads<L, S>();
+    __shared__ S lds[Pair<L>::SLOTS * T];
+    const EnsPairItem it = items[blockIdx.x];
+    if (it.len == 0) return;
+    const BoxDesc bd = boxes[it.box];
+    PairTile t;
+    t.nx = t.ny = t.nz = bd.L;
+    t.stride = bd.stride;
+    t.x0 = it.x0;
+    t.y0 = it.y0;
+    t.z0 = it.z0;
+    t.w = it.w;
+    t.h = it.h;
+    t.len = it.len;
+    t.hx = it.w < bd.L;
+    t.hy = it.h < bd.L;
+    t.W = it.W;
+    Phys ph{};
+    ph.omega = bd.omega;
+    ph.omega_bulk = 1.0;
+    for (int j = 0; j < 9; ++j) ph.omega_hi[j] = 1.0;
+    ph.rho0 = (double)rho0;
+    pair_sweep<L, S, false, false, false, T>(src_all + bd.off, dst_all + bd.off, t, ph, 0, bd.N, lds);
 }
 
 // Learned rates (D3Q19, FP32 collision): every thread of a block takes part in
@@ -283,6 +315,23 @@ void launch_ens_step(int q, int precision, bool mlp, bool off32, const void* src
         ens_step_o<true>(q, precision, mlp, src, dst, bd, tile_box, ntiles, rho0, net, fb, grid, block, pad, st);
     else
         ens_step_o<false>(q, precision, mlp, src, dst, bd, tile_box, ntiles, rho0, net, fb, grid, block, pad, st);
+}
+
+void launch_ens_pair(int q, int precision, const void* src, void* dst, const void* boxes, const EnsPairItem* items,
+                     int nitems, float rho0, hipStream_t st)
+{
+    const BoxDesc* bd = (const BoxDesc*)boxes;
+#define LBM_ENS_PAIR(LAT, S_)                                                                                        \
+    hipLaunchKernelGGL((k_ens_pair<LAT, S_>), dim3(nitems), dim3(pair_threads<LAT, S_>()), 0, st, (const S_*)src, (S_*)dst, \
+                       bd, items, rho0)
+    if (q == 27) {
+        if (precision == PREC_FP64) LBM_ENS_PAIR(LatD3Q27, double);
+        else LBM_ENS_PAIR(LatD3Q27, float);
+    } else {
+        if (precision == PREC_FP64) LBM_ENS_PAIR(LatD3Q19, double);
+        else LBM_ENS_PAIR(LatD3Q19, float);
+    }
+#undef LBM_ENS_PAIR
 }
 
 void launch_ens_energy(int q, int precision, const void* buf, const void* boxes, const int* tile_box, int ntiles,

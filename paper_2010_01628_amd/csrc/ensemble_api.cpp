@@ -72,6 +72,9 @@ struct lbm_ensemble {
     // plain step: at most occ_waves resident wavefronts per SIMD (by LDS
     // allocation; 0: no cap), as for the single lattice
     int occ_waves = 5, lds_per_cu = 163840;
+    // two plain steps per pass (empty list: single steps)
+    lbm::EnsPairItem* pair_dev = nullptr;
+    int pair_items = 0;
 };
 
 namespace {
@@ -83,6 +86,91 @@ void launch_one(lbm_ensemble* e)
                          e->boxes_dev, e->tile_box_dev, e->ntiles, 1.0f, e->mlp ? e->mlp->packed : nullptr, e->fb,
                          e->grid, TILE, e->occ_waves, e->lds_per_cu, e->stream);
     e->cur = dst;
+}
+
+// Two plain steps in one launch.
+bool pairs(const lbm_ensemble* e) { return e->pair_items > 0 && !e->mlp; }
+void launch_pair(lbm_ensemble* e)
+{
+    lbm::launch_ens_pair(e->q, e->precision == LBM_FP64 ? 0 : 1, e->buf[e->cur], e->buf[1 - e->cur], e->boxes_dev, e->pair_dev,
+                         e->pair_items, 1.0f, e->stream);
+    e->cur = 1 - e->cur;
+}
+
+// The pair launch's work list: every box in its best tile, in runs of planes
+// of one length chosen for all boxes (short runs repeat more planes, long ones
+// leave compute units without work at the end).  The tiles of a run share
+// their halos, so a run stays on one XCD; runs go to the least loaded XCD,
+// the largest first.  Empty where two single steps, at their traffic at
+// 5.55 TB/s, are estimated faster.  Measured, us per step, single / pair: 64
+// boxes of 48, 64 and 96 (31 M nodes) D3Q19 FP32 864 / 608, FP64 1824 / 1203,
+// D3Q27 FP32 1279 / 828; four boxes of 32 to 96 D3Q19 FP32 38.9 / 43.3
+// (single), FP64 78.7 / 65.2.  LBM_TWO_STEP=0 and =1 as for the lattice.
+std::vector<lbm::EnsPairItem> pair_list(const lbm_ensemble* e, int cus)
+{
+    const char* env = std::getenv("LBM_TWO_STEP");
+    if (env && env[0] == '0') return {};
+    const int prec = e->precision == LBM_FP64 ? lbm::PREC_FP64 : lbm::PREC_FP32;
+    const int threads = e->q == 27 ? lbm::pair_threads_q27(prec) : lbm::pair_threads_q19(prec);
+    std::vector<lbm::PairShape> tile(e->nboxes);
+    std::vector<double> us(e->nboxes);
+    for (int b = 0; b < e->nboxes; ++b) {
+        int a = 0;
+        while (e->L[a] != e->L[b]) ++a;
+        tile[b] = a < b ? tile[a] : lbm::pair_tile(e->L[b], e->L[b], e->q, e->eb, threads, &us[b]);
+        if (a < b) us[b] = us[a];
+        if (tile[b].w == 0) return {};
+    }
+    int best_len = 0;
+    double best_us = 1e300;
+    for (int len : {6, 8, 12, 16, 24, 32, 48, 64, 96, 128}) {
+        double total = 0.0, longest = 0.0;
+        for (int b = 0; b < e->nboxes; ++b) {
+            const int runs = (e->L[b] + len - 1) / len, planes = (e->L[b] + runs - 1) / runs;
+            total += (double)tile[b].tx * tile[b].ty * runs * (planes + 2) * us[b];
+            longest = std::max(longest, (planes + 2) * us[b]);
+        }
+        const double t = 2.0 + std::max(total / cus + 0.5 * longest, longest);
+        if (t < best_us) {
+            best_us = t;
+            best_len = len;
+        }
+    }
+    const double single_us = std::max(4.0, 2e-6 * e->q * e->eb * (double)e->nodes / 5.55);
+    if (!(env && env[0] == '1') && best_us > 0.95 * 2 * single_us) return {};
+    struct Run {
+        int box, z0, len;
+        double cost;
+    };
+    std::vector<Run> runs;
+    for (int b = 0; b < e->nboxes; ++b) {
+        const int n = (e->L[b] + best_len - 1) / best_len, len = (e->L[b] + n - 1) / n;
+        for (int z = 0; z < e->L[b]; z += len) {
+            const int l = std::min(len, e->L[b] - z);
+            runs.push_back({b, z, l, (double)tile[b].tx * tile[b].ty * (l + 2) * us[b]});
+        }
+    }
+    std::stable_sort(runs.begin(), runs.end(), [](const Run& a, const Run& b) { return a.cost > b.cost; });
+    std::vector<lbm::EnsPairItem> of_xcd[8];
+    double load[8] = {};
+    for (const Run& r : runs) {
+        int x = 0;
+        for (int k = 1; k < 8; ++k)
+            if (load[k] < load[x]) x = k;
+        load[x] += r.cost;
+        const lbm::PairShape& t = tile[r.box];
+        const int L = e->L[r.box], W = t.w + (t.w < L ? 2 : 0);
+        for (int iy = 0; iy < t.ty; ++iy)
+            for (int ix = 0; ix < t.tx; ++ix)
+                of_xcd[x].push_back({r.box, ix * t.w, iy * t.h, r.z0, std::min(t.w, L - ix * t.w),
+                                     std::min(t.h, L - iy * t.h), r.len, W});
+    }
+    size_t most = 0;
+    for (const auto& v : of_xcd) most = std::max(most, v.size());
+    std::vector<lbm::EnsPairItem> list(most * 8, lbm::EnsPairItem{});
+    for (int x = 0; x < 8; ++x)
+        for (size_t k = 0; k < of_xcd[x].size(); ++k) list[k * 8 + x] = of_xcd[x][k];
+    return list;
 }
 
 void drop_graph(lbm_ensemble* e)
@@ -98,7 +186,10 @@ int build_graph(lbm_ensemble* e, int nsteps)
     drop_graph(e);
     const int saved = e->cur;
     EHIP(hipStreamBeginCapture(e->stream, hipStreamCaptureModeThreadLocal));
-    for (int s = 0; s < nsteps; ++s) launch_one(e);
+    if (pairs(e))
+        for (int s = 0; s < nsteps; s += 2) launch_pair(e);
+    else
+        for (int s = 0; s < nsteps; ++s) launch_one(e);
     hipError_t err = hipStreamEndCapture(e->stream, &e->graph);
     e->cur = saved;
     if (err != hipSuccess) return efail(LBM_EDEVICE, "graph capture: %s", hipGetErrorString(err));
@@ -200,9 +291,15 @@ int lbm_ensemble_create(const lbm_box* boxes, int32_t nboxes, int32_t q, int32_t
         hipMalloc((void**)&e->fb, sizeof(uint32_t) * (size_t)(e->fb_len = std::max<int64_t>((int64_t)ncu * 64, tiles))) !=
             hipSuccess)
         return cleanup(efail(LBM_ENOMEM, "ensemble tables"));
+    const std::vector<lbm::EnsPairItem> list = pair_list(e, ncu);
+    if (!list.empty() && hipMalloc((void**)&e->pair_dev, sizeof(list[0]) * list.size()) != hipSuccess)
+        return cleanup(efail(LBM_ENOMEM, "ensemble tables"));
+    e->pair_items = (int)list.size();
     hipError_t err = hipMemcpy(e->boxes_dev, desc.data(), desc.size(), hipMemcpyHostToDevice);
     if (err == hipSuccess) err = hipMemcpy(e->tile_box_dev, tile_box.data(), sizeof(int) * tiles, hipMemcpyHostToDevice);
     if (err == hipSuccess) err = hipMemcpy(e->tile_count_dev, e->tiles.data(), sizeof(int) * nboxes, hipMemcpyHostToDevice);
+    if (err == hipSuccess && !list.empty())
+        err = hipMemcpy(e->pair_dev, list.data(), sizeof(list[0]) * list.size(), hipMemcpyHostToDevice);
     if (err == hipSuccess) err = hipMemset(e->buf[0], 0, elems * e->eb);
     if (err == hipSuccess) err = hipMemset(e->buf[1], 0, elems * e->eb);
     if (err == hipSuccess) err = hipMemset(e->fb, 0, sizeof(uint32_t) * (size_t)e->fb_len);
@@ -219,7 +316,8 @@ int lbm_ensemble_destroy(lbm_ensemble* e)
     if (!e) return LBM_OK;
     hipStreamSynchronize(e->stream);
     drop_graph(e);
-    void* bufs[] = {e->buf[0], e->buf[1], e->boxes_dev, e->tile_box_dev, e->tile_count_dev, e->tile_out, e->box_out, e->fb};
+    void* bufs[] = {e->buf[0], e->buf[1], e->boxes_dev, e->tile_box_dev, e->tile_count_dev, e->tile_out, e->box_out, e->fb,
+                    e->pair_dev};
     for (void* b : bufs)
         if (b) hipFree(b);
     if (e->own_stream) hipStreamDestroy(e->stream);
@@ -312,17 +410,26 @@ int lbm_ensemble_step(lbm_ensemble* e, int64_t nsteps)
 {
     if (!e || nsteps < 0) return efail(LBM_EINVAL, "bad arguments");
     const char* env = std::getenv("LBM_ENSEMBLE_GRAPH_STEPS");
-    // even (rounded down): a replay then leaves the buffer parity unchanged,
-    // which the replay loop below relies on (e->cur is not advanced by it)
+    // a multiple of two launches (rounded down): a replay then leaves the
+    // buffer parity unchanged, which the replay loop below relies on (e->cur
+    // is not advanced by it)
     int chunk = env ? std::atoi(env) : 16;
-    chunk &= ~1;
+    const int per = pairs(e) ? 2 : 1; // steps per launch
+    chunk = chunk / (2 * per) * (2 * per);
     int64_t left = nsteps;
-    // single steps until the parity is even, so the graph always starts from buffer 0
-    while (left > 0 && (e->cur != 0 || chunk < 2 || left < chunk)) {
-        launch_one(e);
-        e->steps++;
-        left--;
-    }
+    auto advance = [&]() {
+        if (per == 2 && left >= 2) {
+            launch_pair(e);
+            e->steps += 2;
+            left -= 2;
+        } else {
+            launch_one(e);
+            e->steps++;
+            left--;
+        }
+    };
+    // single launches until the parity is even, so the graph always starts from buffer 0
+    while (left > 0 && (e->cur != 0 || chunk < 2 || left < chunk)) advance();
     if (left >= chunk && chunk >= 2) {
         if (!e->exec || e->graph_steps != chunk || e->graph_net != (e->mlp ? e->mlp->packed : nullptr)) {
             int rc = build_graph(e, chunk);
@@ -334,11 +441,7 @@ int lbm_ensemble_step(lbm_ensemble* e, int64_t nsteps)
             left -= chunk;
         }
     }
-    while (left > 0) {
-        launch_one(e);
-        e->steps++;
-        left--;
-    }
+    while (left > 0) advance();
     EHIP(hipGetLastError());
     return LBM_OK;
 }

@@ -128,6 +128,9 @@ inline void launch_pair(int q, bool raw, int precision, bool walls, bool general
 // twice that in FP64) and 0.047 us per 128-byte line of one array that it
 // loads or stores (all scaled by q / 19).
 PairShape pair_shape(int nx, int ny, int nz, int q, int eb, int threads, int cus, double* us);
+// The tile with the lowest estimated time for a whole plane of a lattice that
+// shares the GPU with others (no run length), and one of its planes' time.
+PairShape pair_tile(int nx, int ny, int q, int eb, int threads, double* us);
 
 // nout: totals written to out (at most NDIAG_OUT)
 void launch_reduce(const double* partials, int nblocks, double* out, hipStream_t st, int nout = 8);
@@ -220,5 +223,13 @@ void launch_ens_energy(int q, int precision, const void* buf, const void* boxes,
                        int nboxes, const int* tile_count, double rho0, double* tile_out, double* box_out, int grid,
                        hipStream_t st);
 size_t ens_box_desc_bytes();
+// two plain steps in one pass: one work-group per item of the list, which
+// holds the XCDs' items in turn (item k belongs to XCD k % 8); len = 0: none
+struct EnsPairItem {
+    int box, x0, y0, z0;
+    int w, h, len, W;
+};
+void launch_ens_pair(int q, int precision, const void* src, void* dst, const void* boxes, const EnsPairItem* items,
+                     int nitems, float rho0, hipStream_t st);
 void ens_fill_box_desc(void* out, int L, int tile0, int64_t off, int64_t stride, double omega);
 } // namespace lbm

@@ -20,53 +20,83 @@ int pair_threads_q19(int precision)
     return precision == PREC_FP64 ? pair_threads<LatD3Q19, double>() : pair_threads<LatD3Q19, float>();
 }
 
-PairShape pair_shape(int nx, int ny, int nz, int q, int eb, int threads, int cus, double* us)
+namespace {
+
+// Estimated time of one plane of a w x h tile (PairShape's comment).
+double plane_us(int nx, int ny, int q, int eb, int w, int h)
 {
-    PairShape best{};
-    double best_us = 1e300;
-    const bool aligned_rows = (int64_t)nx * eb % 128 == 0;
-    auto try_shape = [&](int w, int h) {
-        const int hx = w < nx, hy = h < ny, W = w + 2 * hx, H = h + 2 * hy;
-        const int waves = (W * H + 63) / 64;
-        const int tx = (nx + w - 1) / w, ty = (ny + h - 1) / h;
-        // 128-byte lines of one array that a plane's loads and stores touch;
-        // a tile row that starts or ends inside a line shares that line's
-        // store with its neighbour
-        const bool aligned = aligned_rows && (int64_t)w * eb % 128 == 0;
-        const double row = (double)w * eb / 128;
-        const double lines = H * (row + (aligned ? 2 * hx : 1 + hx)) + h * (row + (aligned ? 0 : 2));
-        const double plane_us = 0.8 + (eb == 8 ? 2 : 1) * 0.14 * waves * q / 19 + 0.047 * lines * q / 19;
-        for (int len = nz, tz = 1;; len = (nz + tz - 1) / tz) { // each length once
-            const int64_t groups = (int64_t)tx * ty * tz;
-            if (groups > (1 << 20)) break;
-            const double t = 2.0 + (double)((groups + cus - 1) / cus) * (len + 2) * plane_us;
-            if (t < best_us) {
-                best_us = t;
-                best = PairShape{w, h, len, tx, ty, tz};
-            }
-            if (len == 1) break;
-            tz = (nz + len - 2) / (len - 1);
-        }
-    };
+    const int hx = w < nx, hy = h < ny, W = w + 2 * hx, H = h + 2 * hy;
+    const int waves = (W * H + 63) / 64;
+    // 128-byte lines of one array that a plane's loads and stores touch; a
+    // tile row that starts or ends inside a line shares that line's store
+    // with its neighbour
+    const bool aligned = (int64_t)nx * eb % 128 == 0 && (int64_t)w * eb % 128 == 0;
+    const double row = (double)w * eb / 128;
+    const double lines = H * (row + (aligned ? 2 * hx : 1 + hx)) + h * (row + (aligned ? 0 : 2));
+    return 0.8 + (eb == 8 ? 2 : 1) * 0.14 * waves * q / 19 + 0.047 * lines * q / 19;
+}
+
+// The tile sizes worth trying: widths of whole lines and equal shares of the
+// row, each as high as the threads allow, or in equal shares of the columns.
+template <class F> void for_tiles(int nx, int ny, int eb, int threads, F&& f)
+{
     auto rows_for = [&](int w) {
         const int W = w + (w < nx ? 2 : 0);
         if (W > threads) return;
         const int rows = threads / W;
-        if (rows >= ny) try_shape(w, ny);
+        if (rows >= ny) f(w, ny);
         else if (rows >= 3) {
             const int ty = (ny + rows - 3) / (rows - 2);
-            try_shape(w, (ny + ty - 1) / ty);
-            if ((ny + rows - 3) / (rows - 2) * (rows - 2) != ny) try_shape(w, rows - 2);
+            f(w, (ny + ty - 1) / ty);
+            if (ty * (rows - 2) != ny) f(w, rows - 2);
         }
     };
-    for (int w = 128 / eb; w < nx; w += 128 / eb) rows_for(w); // whole lines
-    for (int w = nx, k = 1;; w = (nx + k - 1) / k) {           // equal tiles
+    for (int w = 128 / eb; w < nx; w += 128 / eb) rows_for(w);
+    for (int w = nx, k = 1;; w = (nx + k - 1) / k) {
         if (w < 8 && k > 1) break;
         rows_for(w);
         if (w == 1) break;
         k = (nx + w - 2) / (w - 1);
     }
-    *us = best_us;
+}
+
+} // namespace
+
+PairShape pair_shape(int nx, int ny, int nz, int q, int eb, int threads, int cus, double* us)
+{
+    PairShape best{};
+    *us = 1e300;
+    for_tiles(nx, ny, eb, threads, [&](int w, int h) {
+        const int tx = (nx + w - 1) / w, ty = (ny + h - 1) / h;
+        const double plane = plane_us(nx, ny, q, eb, w, h);
+        for (int len = nz, tz = 1;; len = (nz + tz - 1) / tz) { // each length once
+            const int64_t groups = (int64_t)tx * ty * tz;
+            if (groups > (1 << 20)) break;
+            const double t = 2.0 + (double)((groups + cus - 1) / cus) * (len + 2) * plane;
+            if (t < *us) {
+                *us = t;
+                best = PairShape{w, h, len, tx, ty, tz};
+            }
+            if (len == 1) break;
+            tz = (nz + len - 2) / (len - 1);
+        }
+    });
+    return best;
+}
+
+PairShape pair_tile(int nx, int ny, int q, int eb, int threads, double* us)
+{
+    PairShape best{};
+    double best_us = 1e300;
+    for_tiles(nx, ny, eb, threads, [&](int w, int h) {
+        const int tx = (nx + w - 1) / w, ty = (ny + h - 1) / h;
+        const double plane = plane_us(nx, ny, q, eb, w, h);
+        if (tx * ty * plane < best_us) {
+            best_us = tx * ty * plane;
+            *us = plane;
+            best = PairShape{w, h, 0, tx, ty, 0};
+        }
+    });
     return best;
 }
 

@@ -101,3 +101,32 @@ def test_against_oracle(size, walls):
     ref = oracle.run(oracle.init(rho, u), 6, oracle.K(1.7), F=F, walls_y=walls)
     # FP64 against the oracle's dense solve: summation order only
     assert np.abs(f - ref).max() < 1e-13
+
+
+@pytest.mark.parametrize("q", [19, 27])
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("steps,chunk", [(5, "0"), (21, "6"), (35, "16")])
+def test_ensemble(q, precision, steps, chunk, monkeypatch):
+    """Uneven boxes, with and without captured launches, odd step counts: bit
+    for bit the single-step ensemble's."""
+    boxes = [(2, 1.2), (7, 1.9), (33, 1.7), (16, 1.5), (70, 1.95), (7, 1.1)]
+    monkeypatch.setenv("LBM_ENSEMBLE_GRAPH_STEPS", chunk)
+
+    def run(two):
+        monkeypatch.setenv("LBM_TWO_STEP", two)
+        ens = L.Ensemble(boxes, q=q, precision=precision)
+        for b, (n, _) in enumerate(boxes):
+            rho, u, _ = inputs.random_lattice_fields(n, n, n, seed=b + 1, umax=0.03)
+            ens.init(b, rho, u)
+        ens.step(steps)
+        ens.step(3)
+        f = [ens.get_populations(b) for b in range(len(boxes))]
+        ke = ens.energy()[0]
+        assert ens.step_count == steps + 3
+        ens.close()
+        return f, ke
+
+    (fa, ka), (fb, kb) = run("0"), run("1")
+    assert np.array_equal(ka, kb)
+    for a, b in zip(fa, fb):
+        assert np.isfinite(a).all() and np.array_equal(a, b)
