@@ -193,9 +193,11 @@ __global__ __launch_bounds__(256) void k_cg_fields(const S* __restrict__ red, co
                                                   double* __restrict__ partials)
 {
     using R = typename Codec<S>::R;
-    int x, y, z;
+    const int x = blockIdx.x * blockDim.x + threadIdx.x;
+    const int y = blockIdx.y * blockDim.y + threadIdx.y;
     double v[NDIAG] = {0, 0, 0, 0, 0, 0, 0, 1e300};
-    if (thread_node(g, x, y, z)) {
+    bool first = true;
+    for (int z = blockIdx.z; z < g.nz && x < g.nx && y < g.ny; z += gridDim.z) {
         NodeIdx d;
         node_idx(g, x, y, z, d);
         const int n = nb(d, 0, 0, 0);
@@ -226,15 +228,18 @@ __global__ __launch_bounds__(256) void k_cg_fields(const S* __restrict__ red, co
             u_out[2 * (int64_t)g.N + n] = uz;
         }
         const double u2 = ux * ux + uy * uy + uz * uz;
-        v[0] = rho;
-        v[1] = rho * ux;
-        v[2] = rho * uy;
-        v[3] = rho * uz;
-        v[4] = 0.5 * rho * u2;
-        v[5] = sqrt(u2);
-        v[6] = (isfinite(rho) && isfinite(u2) && rho > 0.0) ? 0.0 : 1.0;
-        v[7] = rho;
+        double w[NDIAG];
+        w[0] = rho;
+        w[1] = rho * ux;
+        w[2] = rho * uy;
+        w[3] = rho * uz;
+        w[4] = 0.5 * rho * u2;
+        w[5] = sqrt(u2);
+        w[6] = (isfinite(rho) && isfinite(u2) && rho > 0.0) ? 0.0 : 1.0;
+        w[7] = rho;
+        diag_add(v, w, first);
     }
+    if (!partials) return;
     const int bid = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
     block_reduce_store(v, partials + (int64_t)bid * NDIAG);
 }

@@ -257,6 +257,7 @@ int coupled_moments(lbm_handle* h, double* rho, double* u, double* diag, int on_
     double* drho = rho;
     double* du = u;
     double* staging = nullptr;
+    const dim3 fgrid = diag_grid(h);
     if (!on_device && (rho || u)) {
         CHIP(hipMalloc((void**)&staging, sizeof(double) * 4 * N));
         drho = rho ? staging : nullptr;
@@ -264,17 +265,17 @@ int coupled_moments(lbm_handle* h, double* rho, double* u, double* diag, int on_
     }
     if (h->p.coupled == LBM_COUPLED_COLOUR)
         lbm::launch_cg_fields(h->p.precision, h->walls, h->buf[h->cur], c->buf[h->cur], h->g, c->cc, drho, du, nullptr,
-                              nullptr, h->partials, h->grid, h->block, h->stream);
+                              nullptr, h->partials, fgrid, h->block, h->stream);
     else if (h->p.coupled == LBM_COUPLED_SHAN_CHEN)
         lbm::launch_sc_fields(h->p.precision, h->buf[h->cur], c->scratch, h->g, h->ph, c->sc_G, drho, du, h->partials,
-                              h->grid, h->block, h->stream);
+                              fgrid, h->block, h->stream);
     else if (h->p.coupled == LBM_COUPLED_MAGNETIC)
         lbm::launch_mhd_fields(h->p.precision, h->walls, h->buf[h->cur], c->buf[h->cur], h->g, h->ph, c->mc, drho, du,
-                               nullptr, nullptr, h->partials, h->grid, h->block, h->stream);
+                               nullptr, nullptr, h->partials, fgrid, h->block, h->stream);
     else
         lbm::launch_phase_fields(h->p.precision, h->buf[h->cur], c->buf[h->cur], c->scratch, h->g, c->pc, nullptr,
-                                 nullptr, drho, du, h->partials, h->grid, h->block, h->stream);
-    if (diag) lbm::launch_reduce(h->partials, h->nblocks, h->diag_dev, h->stream);
+                                 nullptr, drho, du, h->partials, fgrid, h->block, h->stream);
+    if (diag) lbm::launch_reduce(h->partials, blocks_of(fgrid), h->diag_dev, h->stream);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess && staging) {
         if (rho) e = hipMemcpyAsync(rho, staging, sizeof(double) * N, hipMemcpyDeviceToHost, h->stream);
@@ -325,7 +326,7 @@ int lbm_phase_fields(lbm_handle* h, double* phi, double* p, int on_device)
         dp = p ? staging + N : nullptr;
     }
     lbm::launch_phase_fields(h->p.precision, h->buf[h->cur], h->cp->buf[h->cur], h->cp->scratch, h->g, h->cp->pc, dphi,
-                             dp, nullptr, nullptr, h->partials, h->grid, h->block, h->stream);
+                             dp, nullptr, nullptr, nullptr, h->grid, h->block, h->stream);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess && staging) {
         if (phi) e = hipMemcpyAsync(phi, staging, sizeof(double) * N, hipMemcpyDeviceToHost, h->stream);
@@ -415,7 +416,7 @@ int lbm_colour_fields(lbm_handle* h, double* rho_red, double* rho_blue, int on_d
         db = rho_blue ? staging + N : nullptr;
     }
     lbm::launch_cg_fields(h->p.precision, h->walls, h->buf[h->cur], h->cp->buf[h->cur], h->g, h->cp->cc, nullptr,
-                          nullptr, dr, db, h->partials, h->grid, h->block, h->stream);
+                          nullptr, dr, db, nullptr, h->grid, h->block, h->stream);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess && staging) {
         if (rho_red) e = hipMemcpyAsync(rho_red, staging, sizeof(double) * N, hipMemcpyDeviceToHost, h->stream);
@@ -461,7 +462,7 @@ int lbm_magnetic_fields(lbm_handle* h, double* b, double* j, int on_device)
         dj = j ? staging + 3 * N : nullptr;
     }
     lbm::launch_mhd_fields(h->p.precision, h->walls, h->buf[h->cur], h->cp->buf[h->cur], h->g, h->ph, h->cp->mc, nullptr,
-                           nullptr, db, dj, h->partials, h->grid, h->block, h->stream);
+                           nullptr, db, dj, nullptr, h->grid, h->block, h->stream);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess && staging) {
         if (b) e = hipMemcpyAsync(b, staging, sizeof(double) * 3 * N, hipMemcpyDeviceToHost, h->stream);

@@ -47,6 +47,17 @@ struct lbm_handle {
     lbm_coupled* cp = nullptr;         // coupled lattice, if any
 };
 
+// Grid of the field and diagnostics kernels, which loop over z planes: about
+// 4096 work-groups (at least one per x-y block), and their number.
+inline dim3 diag_grid(const lbm_handle* h)
+{
+    const int64_t per_plane = (int64_t)h->grid.x * h->grid.y;
+    int64_t gz = 4096 / per_plane;
+    gz = gz < 1 ? 1 : (gz > (int64_t)h->grid.z ? (int64_t)h->grid.z : gz);
+    return dim3(h->grid.x, h->grid.y, (unsigned)gz);
+}
+inline int blocks_of(dim3 g) { return (int)(g.x * g.y * g.z); }
+
 // Coupled-lattice parts of the entry points (coupled_api.cpp).
 int coupled_validate(const lbm_params* p);
 int coupled_create(lbm_handle* h);

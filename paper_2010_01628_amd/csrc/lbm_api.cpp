@@ -242,8 +242,8 @@ uint32_t step_key(uint32_t seed, int64_t step) { return lbm::hash32(seed ^ lbm::
 int run_check(lbm_handle* h)
 {
     lbm::launch_moments(h->p.q, h->kprec, pattern_of(h), h->walls, h->buf[h->cur], h->g, h->ph, nullptr, nullptr,
-                        h->partials, h->grid, h->block, h->stream);
-    lbm::launch_reduce(h->partials, h->nblocks, h->diag_dev, h->stream);
+                        h->partials, diag_grid(h), h->block, h->stream);
+    lbm::launch_reduce(h->partials, blocks_of(diag_grid(h)), h->diag_dev, h->stream);
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipMemcpyAsync(h->diag_host, h->diag_dev, lbm::NDIAG_OUT * sizeof(double), hipMemcpyDeviceToHost, h->stream));
     HIP_TRY(hipStreamSynchronize(h->stream));
@@ -539,8 +539,8 @@ int lbm_moments(lbm_handle* h, double* rho, double* u, double* diag, int on_devi
         du = u ? staging + N : nullptr;
     }
     lbm::launch_moments(h->p.q, h->kprec, pattern_of(h), h->walls, h->buf[h->cur], h->g, h->ph, drho, du, h->partials,
-                        h->grid, h->block, h->stream);
-    if (diag) lbm::launch_reduce(h->partials, h->nblocks, h->diag_dev, h->stream);
+                        diag_grid(h), h->block, h->stream);
+    if (diag) lbm::launch_reduce(h->partials, blocks_of(diag_grid(h)), h->diag_dev, h->stream);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess && staging) {
         if (rho) e = hipMemcpyAsync(rho, staging, sizeof(double) * N, hipMemcpyDeviceToHost, h->stream);

@@ -184,9 +184,9 @@ __global__ __launch_bounds__(256) void k_mhd_fields(const S* __restrict__ fsrc, 
     using R = typename Codec<S>::R;
     const int x = blockIdx.x * blockDim.x + threadIdx.x;
     const int y = blockIdx.y * blockDim.y + threadIdx.y;
-    const int z = blockIdx.z;
     double v[NDIAG] = {0, 0, 0, 0, 0, 0, 0, 1e300};
-    if (x < gm.nx && y < gm.ny) {
+    bool first = true;
+    for (int z = blockIdx.z; z < gm.nz && x < gm.nx && y < gm.ny; z += gridDim.z) {
         NodeIdx d;
         node_idx(gm, x, y, z, d);
         const int n = nb(d, 0, 0, 0);
@@ -204,15 +204,18 @@ __global__ __launch_bounds__(256) void k_mhd_fields(const S* __restrict__ fsrc, 
             if (j_out) j_out[(int64_t)c * gm.N + n] = (double)j[c];
         }
         const double r = (double)rho, u2 = u[0] * u[0] + u[1] * u[1] + u[2] * u[2];
-        v[0] = r;
-        v[1] = r * u[0];
-        v[2] = r * u[1];
-        v[3] = r * u[2];
-        v[4] = 0.5 * r * u2;
-        v[5] = sqrt(u2);
-        v[6] = (isfinite(r) && isfinite(u2) && r > 0.0) ? 0.0 : 1.0;
-        v[7] = r;
+        double w[NDIAG];
+        w[0] = r;
+        w[1] = r * u[0];
+        w[2] = r * u[1];
+        w[3] = r * u[2];
+        w[4] = 0.5 * r * u2;
+        w[5] = sqrt(u2);
+        w[6] = (isfinite(r) && isfinite(u2) && r > 0.0) ? 0.0 : 1.0;
+        w[7] = r;
+        diag_add(v, w, first);
     }
+    if (!partials) return;
     const int bid = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
     block_reduce_store(v, partials + (int64_t)bid * NDIAG);
 }

@@ -195,9 +195,9 @@ __global__ __launch_bounds__(256) void k_phase_fields(const S* __restrict__ gsrc
     using R = typename Codec<S>::R;
     const int x = blockIdx.x * blockDim.x + threadIdx.x;
     const int y = blockIdx.y * blockDim.y + threadIdx.y;
-    const int z = blockIdx.z;
     double v[NDIAG] = {0, 0, 0, 0, 0, 0, 0, 1e300};
-    if (x < g.nx && y < g.ny) {
+    bool first = true;
+    for (int z = blockIdx.z; z < g.nz && x < g.nx && y < g.ny; z += gridDim.z) {
         NodeIdx d;
         node_idx(g, x, y, z, d);
         const int n = nb(d, 0, 0, 0);
@@ -220,15 +220,18 @@ __global__ __launch_bounds__(256) void k_phase_fields(const S* __restrict__ gsrc
             u_out[2 * (int64_t)g.N + n] = uz;
         }
         const double u2 = ux * ux + uy * uy + uz * uz;
-        v[0] = rho;
-        v[1] = rho * ux;
-        v[2] = rho * uy;
-        v[3] = rho * uz;
-        v[4] = 0.5 * rho * u2;
-        v[5] = sqrt(u2);
-        v[6] = (isfinite(rho) && isfinite(u2) && isfinite((double)o.dPi)) ? 0.0 : 1.0;
-        v[7] = rho;
+        double w[NDIAG];
+        w[0] = rho;
+        w[1] = rho * ux;
+        w[2] = rho * uy;
+        w[3] = rho * uz;
+        w[4] = 0.5 * rho * u2;
+        w[5] = sqrt(u2);
+        w[6] = (isfinite(rho) && isfinite(u2) && isfinite((double)o.dPi)) ? 0.0 : 1.0;
+        w[7] = rho;
+        diag_add(v, w, first);
     }
+    if (!partials) return;
     const int bid = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
     block_reduce_store(v, partials + (int64_t)bid * NDIAG);
 }
@@ -322,12 +325,13 @@ void launch_phase_fields(int precision, const void* gsrc, const void* hsrc, void
                          const PhaseConst& pc, double* phi_out, double* p_out, double* rho_out, double* u_out,
                          double* partials, dim3 grid, dim3 block, hipStream_t st)
 {
+    const dim3 planes(grid.x, grid.y, g.nz); // the fields kernel may take several planes per work-group
     if (precision == PREC_FP64) {
-        hipLaunchKernelGGL((k_phase_sum<double, false>), grid, block, 0, st, (const double*)hsrc, (double*)phi, g);
+        hipLaunchKernelGGL((k_phase_sum<double, false>), planes, block, 0, st, (const double*)hsrc, (double*)phi, g);
         hipLaunchKernelGGL(k_phase_fields<double>, grid, block, 0, st, (const double*)gsrc, (const double*)phi, g, pc,
                            phi_out, p_out, rho_out, u_out, partials);
     } else {
-        hipLaunchKernelGGL((k_phase_sum<float, false>), grid, block, 0, st, (const float*)hsrc, (float*)phi, g);
+        hipLaunchKernelGGL((k_phase_sum<float, false>), planes, block, 0, st, (const float*)hsrc, (float*)phi, g);
         hipLaunchKernelGGL(k_phase_fields<float>, grid, block, 0, st, (const float*)gsrc, (const float*)phi, g, pc,
                            phi_out, p_out, rho_out, u_out, partials);
     }

@@ -83,9 +83,9 @@ __global__ __launch_bounds__(256) void k_sc_fields(const S* __restrict__ src, co
     using R = typename Codec<S>::R;
     const int x = blockIdx.x * blockDim.x + threadIdx.x;
     const int y = blockIdx.y * blockDim.y + threadIdx.y;
-    const int z = blockIdx.z;
     double v[NDIAG] = {0, 0, 0, 0, 0, 0, 0, 1e300};
-    if (x < g.nx && y < g.ny) {
+    bool first = true;
+    for (int z = blockIdx.z; z < g.nz && x < g.nx && y < g.ny; z += gridDim.z) {
         NodeIdx d;
         node_idx(g, x, y, z, d);
         const int n = nb(d, 0, 0, 0);
@@ -113,15 +113,18 @@ __global__ __launch_bounds__(256) void k_sc_fields(const S* __restrict__ src, co
             u_out[2 * (int64_t)g.N + n] = uz;
         }
         const double u2 = ux * ux + uy * uy + uz * uz;
-        v[0] = rho;
-        v[1] = rho * ux;
-        v[2] = rho * uy;
-        v[3] = rho * uz;
-        v[4] = 0.5 * rho * u2;
-        v[5] = sqrt(u2);
-        v[6] = (isfinite(rho) && isfinite(u2) && rho > 0.0) ? 0.0 : 1.0;
-        v[7] = rho;
+        double w[NDIAG];
+        w[0] = rho;
+        w[1] = rho * ux;
+        w[2] = rho * uy;
+        w[3] = rho * uz;
+        w[4] = 0.5 * rho * u2;
+        w[5] = sqrt(u2);
+        w[6] = (isfinite(rho) && isfinite(u2) && rho > 0.0) ? 0.0 : 1.0;
+        w[7] = rho;
+        diag_add(v, w, first);
     }
+    if (!partials) return;
     const int bid = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
     block_reduce_store(v, partials + (int64_t)bid * NDIAG);
 }
@@ -167,12 +170,13 @@ void launch_sc_step(int precision, bool general, bool nt, const void* src, void*
 void launch_sc_fields(int precision, const void* src, void* psi, const Geom& g, const Phys& ph, double G, double* rho,
                       double* u, double* partials, dim3 grid, dim3 block, hipStream_t st)
 {
+    const dim3 planes(grid.x, grid.y, g.nz); // the fields kernel may take several planes per work-group
     if (precision == PREC_FP64) {
-        hipLaunchKernelGGL((k_sc_psi<double, false>), grid, block, 0, st, (const double*)src, (double*)psi, g, ph.rho0);
+        hipLaunchKernelGGL((k_sc_psi<double, false>), planes, block, 0, st, (const double*)src, (double*)psi, g, ph.rho0);
         hipLaunchKernelGGL((k_sc_fields<double>), grid, block, 0, st, (const double*)src, (const double*)psi, g, ph, G,
                            rho, u, partials);
     } else {
-        hipLaunchKernelGGL((k_sc_psi<float, false>), grid, block, 0, st, (const float*)src, (float*)psi, g, ph.rho0);
+        hipLaunchKernelGGL((k_sc_psi<float, false>), planes, block, 0, st, (const float*)src, (float*)psi, g, ph.rho0);
         hipLaunchKernelGGL((k_sc_fields<float>), grid, block, 0, st, (const float*)src, (const float*)psi, g, ph, G,
                            rho, u, partials);
     }
