@@ -215,7 +215,8 @@ int64_t pad_stride(int64_t N, int eb)
 // 100^3 FP32 81 / 51; 113x293x281 FP32 852 / 382, FP16 379 / 260; 200x101x75
 // with walls FP32 116 / 82, FP16 48 / 64 (estimated 64 against 57: single);
 // 64^3 FP32 15 / 22 (single); D3Q27 128^3 FP32 161 / 126.  LBM_TWO_STEP=0
-// keeps single steps, =1 takes pairs wherever they are possible.
+// keeps single steps, =1 takes sweeps wherever they are possible.  Lattices
+// small enough for one work-group per compute unit take blocks instead.
 void set_pair(lbm_handle* h)
 {
     h->pair_ok = false;
@@ -227,9 +228,13 @@ void set_pair(lbm_handle* h)
     const double traffic_us = 2e-6 * h->p.q * eb * (double)h->g.N / 6.1;
     const double single_us = std::max(4.0, traffic_us * ((int64_t)h->g.nx * eb % 128 == 0 ? 1.04 : 1.5));
     const bool forced = env && env[0] == '1';
-    if (!forced && single_us < 6.0) return; // three planes of a pair already take longer
     int cus = 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, h->device) != hipSuccess || cus <= 0) return;
+    if (!forced) {
+        h->pair = lbm::pair_block_shape(h->g.nx, h->g.ny, h->g.nz, lbm::pair_block_threads_of(eb), cus);
+        h->pair_ok = h->pair.w > 0;
+        if (h->pair_ok || single_us < 6.0) return; // three planes of a sweep already take longer than two single steps
+    }
     const int threads = h->p.q == 27 ? lbm::pair_threads_q27(h->kprec) : lbm::pair_threads_q19(h->kprec);
     double pair_us = 0.0;
     h->pair = lbm::pair_shape(h->g.nx, h->g.ny, h->g.nz, h->p.q, eb, threads, cus, &pair_us);

@@ -100,10 +100,11 @@ inline void launch_moments(int q, int precision, int pattern, bool walls, const 
     else launch_moments_q19(precision, pattern, walls, buf, g, ph, rho, u, partials, grid, block, st);
 }
 // Two steps per pass (two_step.hpp): tiles of w x h columns (tx x ty of them),
-// tz runs of len planes.
+// tz runs of len planes; `block`: a thread per node of a w x h x len block.
 struct PairShape {
     int w, h, len;
     int tx, ty, tz;
+    int block;
 };
 // threads of the pair kernel's work-groups (columns of a tile, halo included)
 int pair_threads_q19(int precision);
@@ -128,6 +129,14 @@ inline void launch_pair(int q, bool raw, int precision, bool walls, bool general
 // twice that in FP64) and 0.047 us per 128-byte line of one array that it
 // loads or stores (all scaled by q / 19).
 PairShape pair_shape(int nx, int ny, int nz, int q, int eb, int threads, int cus, double* us);
+// The smallest block of whole x rows, at most `threads` nodes with its halo,
+// that leaves at most one work-group per compute unit (w = 0: none).  Two
+// single steps against blocks, us: 32^3 FP64 10.5 / 7.7, FP32 9.9 / 6.2, FP16
+// 9.2 / 5.5, D3Q27 FP32 11.3 / 7.8; 16^3 FP64 10.0 / 5.3; 24^3 FP32 8.5 / 6.1.
+// With more than one round of work-groups the halo's steps cost more than the
+// launch saved: 48^3 FP32 12.5 / 14.6.
+PairShape pair_block_shape(int nx, int ny, int nz, int threads, int cus);
+int pair_block_threads_of(int eb);
 // The tile with the lowest estimated time for a whole plane of a lattice that
 // shares the GPU with others (no run length), and one of its planes' time.
 PairShape pair_tile(int nx, int ny, int q, int eb, int threads, double* us);

@@ -75,13 +75,37 @@ PairShape pair_shape(int nx, int ny, int nz, int q, int eb, int threads, int cus
             const double t = 2.0 + (double)((groups + cus - 1) / cus) * (len + 2) * plane;
             if (t < *us) {
                 *us = t;
-                best = PairShape{w, h, len, tx, ty, tz};
+                best = PairShape{w, h, len, tx, ty, tz, 0};
             }
             if (len == 1) break;
             tz = (nz + len - 2) / (len - 1);
         }
     });
     return best;
+}
+
+PairShape pair_block_shape(int nx, int ny, int nz, int threads, int cus)
+{
+    PairShape best{};
+    int least = threads + 1;
+    for (int h = 1; h <= ny; ++h) {
+        const int H = h + 2 * (h < ny);
+        if ((int64_t)nx * H > threads) break;
+        for (int d = 1; d <= nz; ++d) {
+            const int nodes = nx * H * (d + 2 * (d < nz));
+            if (nodes > threads) break;
+            const int ty = (ny + h - 1) / h, tz = (nz + d - 1) / d;
+            if ((int64_t)ty * tz <= cus && nodes < least) {
+                least = nodes;
+                best = PairShape{nx, h, d, 1, ty, tz, 1};
+            }
+        }
+    }
+    return best;
+}
+int pair_block_threads_of(int eb)
+{
+    return eb == 8 ? pair_block_threads<LatD3Q19, double>() : pair_block_threads<LatD3Q19, float>();
 }
 
 PairShape pair_tile(int nx, int ny, int q, int eb, int threads, double* us)
@@ -94,7 +118,7 @@ PairShape pair_tile(int nx, int ny, int q, int eb, int threads, double* us)
         if (tx * ty * plane < best_us) {
             best_us = tx * ty * plane;
             *us = plane;
-            best = PairShape{w, h, 0, tx, ty, 0};
+            best = PairShape{w, h, 0, tx, ty, 0, 0};
         }
     });
     return best;

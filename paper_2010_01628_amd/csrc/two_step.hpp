@@ -378,6 +378,99 @@ __global__ __launch_bounds__((pair_threads<L, S>())) __attribute__((amdgpu_waves
     pair_sweep<L, S, WALLS, GENERAL, FIELD, T>(src, dst, t, ph, key2, g.N, lds);
 }
 
+// ---------------------------------------------------------------------------
+// The same for lattices too small to fill the GPU with sweeps: a work-group
+// takes a w x h x d block of nodes with one halo node on each side (none along
+// an axis that the block spans), one thread per node, both steps at once, the
+// whole state between them in LDS.  The halo repeats most of the first step
+// (32x2x2 blocks: 512 first steps for 128 stored nodes), but a launch takes
+// one trip to memory and two collisions where two single steps take two
+// launches and two trips.
+// ---------------------------------------------------------------------------
+template <class L, class S> constexpr int pair_block_threads() { return sizeof(S) == 8 ? 512 : 1024; }
+
+template <class L, class S, bool WALLS, bool GENERAL>
+__global__ __launch_bounds__((pair_block_threads<L, S>())) void k_step_pair_block(const S* __restrict__ src,
+                                                                                 S* __restrict__ dst, Geom g, Phys ph,
+                                                                                 PairShape sh, uint32_t key2)
+{
+    using R = typename Codec<S>::R;
+    constexpr int Q = L::Q, T = pair_block_threads<L, S>();
+    __shared__ S lds[(Q - 1) * T]; // population i > 0 of the node in place p: lds[(i - 1) T + p]
+    int k = blockIdx.x;
+    const int bx = k % sh.tx;
+    k /= sh.tx;
+    const int x0 = bx * sh.w, y0 = k % sh.ty * sh.h, z0 = k / sh.ty * sh.len;
+    const int w = min(sh.w, g.nx - x0), h = min(sh.h, g.ny - y0), d = min(sh.len, g.nz - z0);
+    const int hx = sh.w < g.nx, hy = sh.h < g.ny, hz = sh.len < g.nz;
+    const int W = w + 2 * hx, H = h + 2 * hy, D = d + 2 * hz;
+    // stored nodes first, then the halo: z faces, y faces, x faces
+    int r = threadIdx.x, cx, cy, cz;
+    const bool stored = r < w * h * d;
+    bool node = true;
+    if (stored) {
+        cz = r / (w * h);
+        r -= cz * w * h;
+        cy = r / w;
+        cx = r - cy * w + hx;
+        cy += hy;
+        cz += hz;
+    } else if ((r -= w * h * d) < 2 * hz * W * H) {
+        const int up = r >= W * H;
+        r -= up * W * H;
+        cz = up * (D - 1);
+        cy = r / W;
+        cx = r - cy * W;
+    } else if ((r -= 2 * hz * W * H) < 2 * hy * W * d) {
+        const int up = r >= W * d;
+        r -= up * W * d;
+        cy = up * (H - 1);
+        cz = r / W;
+        cx = r - cz * W;
+        cz += hz;
+    } else {
+        r -= 2 * hy * W * d;
+        node = r < 2 * hx * h * d;
+        const int up = node && r >= h * d;
+        r = node ? r - up * h * d : 0;
+        cx = up * (W - 1);
+        cz = r / h;
+        cy = r - cz * h + hy;
+        cz += hz;
+    }
+    const int place = node ? (cz * H + cy) * W + cx : T - 1;
+    // its lattice node (wrapped; beyond a wall a halo node is never read)
+    auto wrap = [](int v, int n) { return v < 0 ? v + n : (v >= n ? v - n : v); };
+    const int x = wrap(x0 - hx + cx, g.nx), y = wrap(y0 - hy + cy, g.ny), z = wrap(z0 - hz + cz, g.nz);
+    NodeIdx n;
+    node_idx(g, x, y, z, n);
+    R s[Q], F[3];
+    gather<L, S, AB, WALLS>(src, g.stride, n, s);
+    node_force(ph, g, nb(n, 0, 0, 0), y, F[0], F[1], F[2]);
+    NodeMacro<R> mac;
+    L::template collide<R, GENERAL, Codec<S>::increment>(s, (R)ph.rho0, F[0], F[1], F[2], ph, mac);
+    if constexpr (Codec<S>::stochastic) dither_bf16(s, ph.sr_key, (uint32_t)nb(n, 0, 0, 0));
+    const S rest = Codec<S>::enc(s[0]);
+#pragma unroll
+    for (int i = 1; i < Q; ++i) lds[(i - 1) * T + place] = Codec<S>::enc(s[i]);
+    __syncthreads();
+    if (!stored) return;
+    // places of the neighbours, wrapping where the block spans the axis
+    const int px[3] = {hx == 0 && cx == 0 ? w - 1 : -1, 0, hx == 0 && cx == w - 1 ? 1 - w : 1};
+    const int py[3] = {(hy == 0 && cy == 0 ? h - 1 : -1) * W, 0, (hy == 0 && cy == h - 1 ? 1 - h : 1) * W};
+    const int pz[3] = {(hz == 0 && cz == 0 ? d - 1 : -1) * H * W, 0, (hz == 0 && cz == d - 1 ? 1 - d : 1) * H * W};
+    s[0] = Codec<S>::dec(rest);
+#pragma unroll
+    for (int i = 1; i < Q; ++i) {
+        int at = (i - 1) * T + place + px[1 - L::cx(i)] + py[1 - L::cy(i)] + pz[1 - L::cz(i)];
+        if (beyond<WALLS>(n, -L::cy(i))) at = (L::opp(i) - 1) * T + place;
+        s[i] = Codec<S>::dec(lds[at]);
+    }
+    L::template collide<R, GENERAL, Codec<S>::increment>(s, (R)ph.rho0, F[0], F[1], F[2], ph, mac);
+    if constexpr (Codec<S>::stochastic) dither_bf16(s, key2, (uint32_t)nb(n, 0, 0, 0));
+    scatter<L, S, AB, WALLS, false>(dst, g.stride, n, s);
+}
+
 // Shape of a pair launch on this lattice.
 template <class L, class S> struct LaunchPair {
     static void step(bool walls, bool general, const void* src, void* dst, const Geom& g, const Phys& ph,
@@ -399,6 +492,13 @@ template <class L, class S> struct LaunchPair {
     static void by_force(const void* src, void* dst, const Geom& g, const Phys& ph, const PairShape& sh, uint32_t key2,
                          hipStream_t st)
     {
+        if (sh.block) {
+            const int hx = sh.w < g.nx, hy = sh.h < g.ny, hz = sh.len < g.nz;
+            const int nodes = (sh.w + 2 * hx) * (sh.h + 2 * hy) * (sh.len + 2 * hz);
+            hipLaunchKernelGGL((k_step_pair_block<L, S, WALLS, GENERAL>), dim3(sh.tx * sh.ty * sh.tz),
+                               dim3((nodes + 63) / 64 * 64), 0, st, (const S*)src, (S*)dst, g, ph, sh, key2);
+            return;
+        }
         const dim3 grid((unsigned)((sh.tx * sh.ty * sh.tz + 7) / 8 * 8)), block(pair_threads<L, S>());
         const S* a = (const S*)src;
         S* b = (S*)dst;

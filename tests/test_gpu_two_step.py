@@ -1,7 +1,8 @@
 """Two steps per pass over memory (lbm_step with n >= 2, A-B; LBM_TWO_STEP=1
 takes it wherever it is possible) against the single-step kernels
 (LBM_TWO_STEP=0): the same arithmetic in the same order at every node, so the
-populations agree bit for bit.  Sizes at the edges
+populations agree bit for bit.  The default takes blocks of whole rows on
+lattices small enough for one work-group per compute unit.  Sizes at the edges
 of the tiles: rows and columns one tile spans whole (no halo), ones it just
 does not, ragged last tiles, one to three z planes."""
 import os
@@ -15,10 +16,10 @@ from paper_2010_01628_amd import lbm as L
 pytestmark = pytest.mark.gpu
 
 SIZES = [(16, 12, 10), (32, 16, 8), (33, 17, 5), (70, 41, 9), (1, 3, 2), (2, 1, 1), (130, 9, 3), (23, 300, 4), (512, 2, 3),
-         (513, 2, 3), (1100, 5, 2), (64, 64, 64)]
+         (513, 2, 3), (1100, 5, 2), (64, 64, 64), (16, 16, 16), (32, 32, 32), (100, 20, 10), (1, 1, 1), (5, 2, 1)]
 
 
-def _run(n, size, single, seed=5, **kw):
+def _run(n, size, two_step, seed=5, **kw):
     import torch
 
     nx, ny, nz = size
@@ -32,12 +33,15 @@ def _run(n, size, single, seed=5, **kw):
     elif force == "kolmogorov":
         kw.update(force_mode=L.LBM_FORCE_KOLMOGOROV, kolmogorov_amp=1e-4)
     saved = os.environ.get("LBM_TWO_STEP")
-    os.environ["LBM_TWO_STEP"] = "0" if single else "1"
+    if two_step is None:
+        os.environ.pop("LBM_TWO_STEP", None)
+    else:
+        os.environ["LBM_TWO_STEP"] = two_step
     try:
         lat = L.Lattice(L.make_params(nx, ny, nz, omega=1.7, **kw), force_field=Ft)
     finally:
         if saved is None:
-            del os.environ["LBM_TWO_STEP"]
+            os.environ.pop("LBM_TWO_STEP", None)
         else:
             os.environ["LBM_TWO_STEP"] = saved
     lat.init(rho, u)
@@ -51,9 +55,11 @@ def _run(n, size, single, seed=5, **kw):
 def _same(n, size, **kw):
     import torch
 
-    a, b = _run(n, size, True, **kw), _run(n, size, False, **kw)
+    a = _run(n, size, "0", **kw)
     assert torch.isfinite(a).all()
-    assert torch.equal(a, b), float((a - b).abs().max())
+    for mode in ("1", None):  # sweeps; the default (blocks on small lattices)
+        b = _run(n, size, mode, **kw)
+        assert torch.equal(a, b), (mode, float((a - b).abs().max()))
 
 
 @pytest.mark.parametrize("size", SIZES)
@@ -92,12 +98,13 @@ def test_checks_between_pairs():
 
 @pytest.mark.parametrize("size", [(33, 17, 5), (64, 30, 7)])
 @pytest.mark.parametrize("walls", [False, True])
-def test_against_oracle(size, walls):
+@pytest.mark.parametrize("mode", ["1", None])
+def test_against_oracle(size, walls, mode):
     import oracle
 
     nx, ny, nz = size
     rho, u, F = inputs.random_lattice_fields(nx, ny, nz, seed=5, umax=0.05, fmax=1e-3)
-    f = _run(6, size, False, precision="fp64", walls_y=walls).cpu().numpy()
+    f = _run(6, size, mode, precision="fp64", walls_y=walls).cpu().numpy()
     ref = oracle.run(oracle.init(rho, u), 6, oracle.K(1.7), F=F, walls_y=walls)
     # FP64 against the oracle's dense solve: summation order only
     assert np.abs(f - ref).max() < 1e-13
