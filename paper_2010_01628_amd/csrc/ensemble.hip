@@ -43,7 +43,7 @@ __device__ inline Geom box_geom(const BoxDesc& bd)
     return g;
 }
 
-template <class L, class S, bool O32>
+template <class L, class S, bool O32, bool NT>
 __global__ __launch_bounds__(256) void k_ens_step(const S* __restrict__ src_all, S* __restrict__ dst_all,
                                                   const BoxDesc* __restrict__ boxes, const int* __restrict__ tile_box,
                                                   int ntiles, float rho0)
@@ -59,14 +59,14 @@ __global__ __launch_bounds__(256) void k_ens_step(const S* __restrict__ src_all,
         NodeIdx d;
         node_idx(g, x, y, z, d);
         R s[L::Q];
-        gather<L, S, AB, false, true, O32>(src_all + bd.off, g.stride, d, s);
+        gather<L, S, AB, false, NT, O32>(src_all + bd.off, g.stride, d, s);
         Phys ph{};
         ph.omega = bd.omega;
         ph.omega_bulk = 1.0;
         for (int j = 0; j < 9; ++j) ph.omega_hi[j] = 1.0;
         NodeMacro<R> mac;
         L::template collide<R, false, Codec<S>::increment>(s, (R)rho0, R(0), R(0), R(0), ph, mac);
-        scatter<L, S, AB, false, true, O32>(dst_all + bd.off, g.stride, d, s);
+        scatter<L, S, AB, false, NT, O32>(dst_all + bd.off, g.stride, d, s);
     }
 }
 
@@ -74,7 +74,7 @@ __global__ __launch_bounds__(256) void k_ens_step(const S* __restrict__ src_all,
 template <class L, class S>
 __global__ __launch_bounds__((pair_threads<L, S>())) __attribute__((amdgpu_waves_per_eu((pair_waves<L, S>())))) void k_ens_pair(
     const S* __restrict__ src_all, S* __restrict__ dst_all, const BoxDesc* __restrict__ boxes,
-    const EnsPairItem* __restrict__ items, float rho0)
+    const EnsPairItem* __restrict__ items, float rho0, int nt)
 {
     constexpr int T = pair_threads<L, S>();
     __shared__ S lds[Pair<L>::SLOTS * T];
@@ -93,6 +93,7 @@ __global__ __launch_bounds__((pair_threads<L, S>())) __attribute__((amdgpu_waves
     t.hx = it.w < bd.L;
     t.hy = it.h < bd.L;
     t.W = it.W;
+    t.nt = nt;
     Phys ph{};
     ph.omega = bd.omega;
     ph.omega_bulk = 1.0;
@@ -278,7 +279,7 @@ __global__ __launch_bounds__(256) void k_ens_box_sums(const double* __restrict__
 // lds_pad: dynamic LDS of the plain step's work-groups (a cap on resident
 // wavefronts per SIMD, as for the single lattice); the learned step runs at
 // four wavefronts per SIMD by its registers and takes none
-template <bool O32>
+template <bool O32, bool NT>
 static void ens_step_o(int q, int precision, bool mlp, const void* src, void* dst, const BoxDesc* bd, const int* tile_box,
                        int ntiles, float rho0, const void* net, uint32_t* fb, int grid, int block, unsigned lds_pad,
                        hipStream_t st)
@@ -288,42 +289,43 @@ static void ens_step_o(int q, int precision, bool mlp, const void* src, void* ds
                            bd, tile_box, ntiles, rho0, (const MlpPacked*)net, fb);
         return;
     }
+#define LBM_ENS_STEP(LAT, S_)                                                                                             \
+    hipLaunchKernelGGL((k_ens_step<LAT, S_, O32, NT>), dim3(grid), dim3(block), lds_pad, st, (const S_*)src, (S_*)dst, bd, \
+                       tile_box, ntiles, rho0)
     if (q == 27) {
-        if (precision == PREC_FP64)
-            hipLaunchKernelGGL((k_ens_step<LatD3Q27, double, O32>), dim3(grid), dim3(block), lds_pad, st, (const double*)src,
-                               (double*)dst, bd, tile_box, ntiles, rho0);
-        else
-            hipLaunchKernelGGL((k_ens_step<LatD3Q27, float, O32>), dim3(grid), dim3(block), lds_pad, st, (const float*)src,
-                               (float*)dst, bd, tile_box, ntiles, rho0);
+        if (precision == PREC_FP64) LBM_ENS_STEP(LatD3Q27, double);
+        else LBM_ENS_STEP(LatD3Q27, float);
     } else {
-        if (precision == PREC_FP64)
-            hipLaunchKernelGGL((k_ens_step<LatD3Q19, double, O32>), dim3(grid), dim3(block), lds_pad, st, (const double*)src,
-                               (double*)dst, bd, tile_box, ntiles, rho0);
-        else
-            hipLaunchKernelGGL((k_ens_step<LatD3Q19, float, O32>), dim3(grid), dim3(block), lds_pad, st, (const float*)src,
-                               (float*)dst, bd, tile_box, ntiles, rho0);
+        if (precision == PREC_FP64) LBM_ENS_STEP(LatD3Q19, double);
+        else LBM_ENS_STEP(LatD3Q19, float);
     }
+#undef LBM_ENS_STEP
 }
 
-void launch_ens_step(int q, int precision, bool mlp, bool off32, const void* src, void* dst, const void* boxes,
+void launch_ens_step(int q, int precision, bool mlp, bool off32, bool nt, const void* src, void* dst, const void* boxes,
                      const int* tile_box, int ntiles, float rho0, const void* net, uint32_t* fb, int grid, int block,
                      int occ_waves, int lds_per_cu, hipStream_t st)
 {
     const BoxDesc* bd = (const BoxDesc*)boxes;
     const unsigned pad = occ_pad(occ_waves, lds_per_cu, 0, dim3(block));
-    if (off32)
-        ens_step_o<true>(q, precision, mlp, src, dst, bd, tile_box, ntiles, rho0, net, fb, grid, block, pad, st);
-    else
-        ens_step_o<false>(q, precision, mlp, src, dst, bd, tile_box, ntiles, rho0, net, fb, grid, block, pad, st);
+#define LBM_ENS_O(O, N) ens_step_o<O, N>(q, precision, mlp, src, dst, bd, tile_box, ntiles, rho0, net, fb, grid, block, pad, st)
+    if (off32) {
+        if (nt) LBM_ENS_O(true, true);
+        else LBM_ENS_O(true, false);
+    } else {
+        if (nt) LBM_ENS_O(false, true);
+        else LBM_ENS_O(false, false);
+    }
+#undef LBM_ENS_O
 }
 
 void launch_ens_pair(int q, int precision, const void* src, void* dst, const void* boxes, const EnsPairItem* items,
-                     int nitems, float rho0, hipStream_t st)
+                     int nitems, float rho0, bool nt, hipStream_t st)
 {
     const BoxDesc* bd = (const BoxDesc*)boxes;
 #define LBM_ENS_PAIR(LAT, S_)                                                                                        \
     hipLaunchKernelGGL((k_ens_pair<LAT, S_>), dim3(nitems), dim3(pair_threads<LAT, S_>()), 0, st, (const S_*)src, (S_*)dst, \
-                       bd, items, rho0)
+                       bd, items, rho0, (int)nt)
     if (q == 27) {
         if (precision == PREC_FP64) LBM_ENS_PAIR(LatD3Q27, double);
         else LBM_ENS_PAIR(LatD3Q27, float);

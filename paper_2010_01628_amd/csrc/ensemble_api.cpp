@@ -75,6 +75,7 @@ struct lbm_ensemble {
     // two plain steps per pass (empty list: single steps)
     lbm::EnsPairItem* pair_dev = nullptr;
     int pair_items = 0;
+    bool nt = true; // streaming loads and stores (the state is larger than the last-level cache)
 };
 
 namespace {
@@ -82,7 +83,7 @@ namespace {
 void launch_one(lbm_ensemble* e)
 {
     const int src = e->cur, dst = 1 - e->cur;
-    lbm::launch_ens_step(e->q, e->precision == LBM_FP64 ? 0 : 1, e->mlp != nullptr, e->off32, e->buf[src], e->buf[dst],
+    lbm::launch_ens_step(e->q, e->precision == LBM_FP64 ? 0 : 1, e->mlp != nullptr, e->off32, e->nt, e->buf[src], e->buf[dst],
                          e->boxes_dev, e->tile_box_dev, e->ntiles, 1.0f, e->mlp ? e->mlp->packed : nullptr, e->fb,
                          e->grid, TILE, e->occ_waves, e->lds_per_cu, e->stream);
     e->cur = dst;
@@ -93,7 +94,7 @@ bool pairs(const lbm_ensemble* e) { return e->pair_items > 0 && !e->mlp; }
 void launch_pair(lbm_ensemble* e)
 {
     lbm::launch_ens_pair(e->q, e->precision == LBM_FP64 ? 0 : 1, e->buf[e->cur], e->buf[1 - e->cur], e->boxes_dev, e->pair_dev,
-                         e->pair_items, 1.0f, e->stream);
+                         e->pair_items, 1.0f, e->nt, e->stream);
     e->cur = 1 - e->cur;
 }
 
@@ -117,7 +118,7 @@ std::vector<lbm::EnsPairItem> pair_list(const lbm_ensemble* e, int cus)
     for (int b = 0; b < e->nboxes; ++b) {
         int a = 0;
         while (e->L[a] != e->L[b]) ++a;
-        tile[b] = a < b ? tile[a] : lbm::pair_tile(e->L[b], e->L[b], e->q, e->eb, threads, &us[b]);
+        tile[b] = a < b ? tile[a] : lbm::pair_tile(e->L[b], e->L[b], e->q, e->eb, !e->nt, threads, &us[b]);
         if (a < b) us[b] = us[a];
         if (tile[b].w == 0) return {};
     }
@@ -291,6 +292,7 @@ int lbm_ensemble_create(const lbm_box* boxes, int32_t nboxes, int32_t q, int32_t
         hipMalloc((void**)&e->fb, sizeof(uint32_t) * (size_t)(e->fb_len = std::max<int64_t>((int64_t)ncu * 64, tiles))) !=
             hipSuccess)
         return cleanup(efail(LBM_ENOMEM, "ensemble tables"));
+    e->nt = !lbm::fits_last_level_cache((int64_t)2 * e->q * e->nodes * e->eb);
     const std::vector<lbm::EnsPairItem> list = pair_list(e, ncu);
     if (!list.empty() && hipMalloc((void**)&e->pair_dev, sizeof(list[0]) * list.size()) != hipSuccess)
         return cleanup(efail(LBM_ENOMEM, "ensemble tables"));

@@ -209,15 +209,19 @@ int64_t pad_stride(int64_t N, int eb)
 // Two steps per pass (two_step.hpp): A-B, single phase, where a pair is
 // estimated faster than two single steps.  A single step is estimated at its
 // traffic at 6.1 TB/s, 1.04 times that on rows of whole 128-byte lines and
-// 1.5 times on others, whose stores share lines between rows, and at least
-// 4 us.  Two steps measured against a pair, us: 256^3 FP32 834 / 623, FP64
-// 1805 / 1367, FP16 430 / 436 (estimated 509: single); 192^3 FP32 388 / 278;
-// 100^3 FP32 81 / 51; 113x293x281 FP32 852 / 382, FP16 379 / 260; 200x101x75
-// with walls FP32 116 / 82, FP16 48 / 64 (estimated 64 against 57: single);
-// 64^3 FP32 15 / 22 (single); D3Q27 128^3 FP32 161 / 126.  LBM_TWO_STEP=0
-// keeps single steps, =1 takes sweeps wherever they are possible.  Lattices
-// small enough for one work-group per compute unit take blocks instead.
-void set_pair(lbm_handle* h)
+// 1.5 times on others, whose stores share lines between rows (1.1 times, 1.25
+// with 2-byte storage, where the last-level cache holds the lattice, `cached`:
+// it merges them), and at least 4 us.  Two steps measured against a pair, us:
+// 256^3 FP32 834 / 612, with walls 856 / 620, FP64 1805 / 1367, FP16 430 / 436
+// (single); 192^3 FP32 388 / 278; 113x293x281 FP32 852 / 382, FP16 379 / 260;
+// 64^3 FP32 15 / 22 (single); D3Q27 128^3 FP32 160 / 127.  In the cache:
+// 200x101x75 FP32 79 / 63, with walls 78 / 70, FP16 49 / 61 (single); FP32
+// 100^3 56 / 44, 128x128x96 73 / 58, 72^3 26 / 24 (single); FP64 80^3 51 / 42,
+// 91^3 78 / 59; D3Q27 96^3 FP32 62 / 61, 64^3 22 / 30 (single).
+// LBM_TWO_STEP=0 keeps single steps, =1 takes sweeps wherever they are
+// possible.  Lattices small enough for one work-group per compute unit take
+// blocks instead.
+void set_pair(lbm_handle* h, bool cached)
 {
     h->pair_ok = false;
     if (h->p.streaming != LBM_AB || h->p.coupled != LBM_COUPLED_NONE) return;
@@ -226,7 +230,8 @@ void set_pair(lbm_handle* h)
     if (env && env[0] == '0') return;
     const int eb = elem_bytes(h->p.precision);
     const double traffic_us = 2e-6 * h->p.q * eb * (double)h->g.N / 6.1;
-    const double single_us = std::max(4.0, traffic_us * ((int64_t)h->g.nx * eb % 128 == 0 ? 1.04 : 1.5));
+    const bool aligned = (int64_t)h->g.nx * eb % 128 == 0;
+    const double single_us = std::max(4.0, traffic_us * (aligned ? 1.04 : (cached ? (eb == 2 ? 1.25 : 1.1) : 1.5)));
     const bool forced = env && env[0] == '1';
     int cus = 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, h->device) != hipSuccess || cus <= 0) return;
@@ -237,7 +242,7 @@ void set_pair(lbm_handle* h)
     }
     const int threads = h->p.q == 27 ? lbm::pair_threads_q27(h->kprec) : lbm::pair_threads_q19(h->kprec);
     double pair_us = 0.0;
-    h->pair = lbm::pair_shape(h->g.nx, h->g.ny, h->g.nz, h->p.q, eb, threads, cus, &pair_us);
+    h->pair = lbm::pair_shape(h->g.nx, h->g.ny, h->g.nz, h->p.q, eb, cached, threads, cus, &pair_us);
     h->pair_ok = h->pair.w > 0 && (forced || pair_us < 0.95 * 2 * single_us);
 }
 
@@ -383,7 +388,15 @@ int lbm_create(const lbm_params* p, void* stream, lbm_handle** out)
         }
         if (p->cache_policy == 0 && h->g.row_stage) h->nt = true;
     }
-    set_pair(h);
+    {
+        // values per node of every buffer (two of each lattice with A-B)
+        const int coupled = p->coupled == LBM_COUPLED_PHASE ? 7 : p->coupled == LBM_COUPLED_MAGNETIC ? 21
+                            : p->coupled == LBM_COUPLED_COLOUR ? 19 : 0;
+        const int64_t bytes = (int64_t)(p->streaming == LBM_AB ? 2 : 1) * (p->q + coupled) * h->g.N * eb;
+        h->cached = p->cache_policy == 2 || (p->cache_policy == 0 && lbm::fits_last_level_cache(bytes));
+        if (h->cached) h->nt = false;
+        set_pair(h, h->cached && lbm::fits_last_level_cache(bytes));
+    }
 
     const int64_t pop_bytes = (int64_t)p->q * h->g.stride * eb;
     const int nbuf = p->streaming == LBM_AB ? 2 : 1;
@@ -506,8 +519,10 @@ int lbm_step(lbm_handle* h, int64_t nsteps)
                 h->ph.sr_key = step_key(h->p.seed, h->steps);
                 key2 = step_key(h->p.seed, h->steps + 1);
             }
+            lbm::PairShape sh = h->pair;
+            sh.nt = !h->cached;
             lbm::launch_pair(h->p.q, h->p.moments == LBM_RAW_MOMENTS, h->kprec, h->walls, h->general, h->buf[src],
-                             h->buf[dst], h->g, h->ph, h->pair, key2, h->stream);
+                             h->buf[dst], h->g, h->ph, sh, key2, h->stream);
             h->steps++;
             s++;
         } else {

@@ -105,7 +105,17 @@ struct PairShape {
     int w, h, len;
     int tx, ty, tz;
     int block;
+    int nt = 1; // streaming hint on the sweeps' stores
 };
+// Whether a state of this many bytes (all buffers of all lattices) is kept in
+// the caches from one step to the next, so that the steps take ordinary loads
+// and stores instead of streaming ones: more than the L2s hold and no more
+// than the 256 MiB last-level cache.  Streaming / ordinary, us per step: FP32
+// 96^3 26.6 / 19.4, 100^3 41 / 23.6, FP16 128^3 29.4 / 21.9, FP32 AA 128^3
+// 54.8 / 40.5, Shan-Chen 100^3 50.4 / 42.6, two-phase 96^3 43.9 / 32.7,
+// magnetic 64^3 17.6 / 12.9; below the range (40 MB) FP32 64^3 7.5 / 8.1,
+// above it (320 MB) Shan-Chen 128^3 85 / 88, two-phase 128^3 (436 MB) 85 / 94.
+inline bool fits_last_level_cache(int64_t bytes) { return bytes >= 48000000 && bytes <= ((int64_t)256 << 20); }
 // threads of the pair kernel's work-groups (columns of a tile, halo included)
 int pair_threads_q19(int precision);
 int pair_threads_q27(int precision);
@@ -127,8 +137,9 @@ inline void launch_pair(int q, bool raw, int precision, bool walls, bool general
 // estimate, fitted to 64x13, 32x28 and 128x5 tiles on 256^3 with 2- and 4-byte
 // storage: a plane takes 0.8 us, 0.14 us per wavefront (its two collisions;
 // twice that in FP64) and 0.047 us per 128-byte line of one array that it
-// loads or stores (all scaled by q / 19).
-PairShape pair_shape(int nx, int ny, int nz, int q, int eb, int threads, int cus, double* us);
+// loads or stores (all scaled by q / 19).  `cached`: the last-level cache
+// holds the lattice.
+PairShape pair_shape(int nx, int ny, int nz, int q, int eb, bool cached, int threads, int cus, double* us);
 // The smallest block of whole x rows, at most `threads` nodes with its halo,
 // that leaves at most one work-group per compute unit (w = 0: none).  Two
 // single steps against blocks, us: 32^3 FP64 10.5 / 7.7, FP32 9.9 / 6.2, FP16
@@ -139,7 +150,7 @@ PairShape pair_block_shape(int nx, int ny, int nz, int threads, int cus);
 int pair_block_threads_of(int eb);
 // The tile with the lowest estimated time for a whole plane of a lattice that
 // shares the GPU with others (no run length), and one of its planes' time.
-PairShape pair_tile(int nx, int ny, int q, int eb, int threads, double* us);
+PairShape pair_tile(int nx, int ny, int q, int eb, bool cached, int threads, double* us);
 
 // nout: totals written to out (at most NDIAG_OUT)
 void launch_reduce(const double* partials, int nblocks, double* out, hipStream_t st, int nout = 8);
@@ -224,8 +235,9 @@ struct lbm_mlp {
 
 // ensemble (ensemble.hip)
 namespace lbm {
-// off32: every box's population arrays are below 4 GiB (32-bit element offsets)
-void launch_ens_step(int q, int precision, bool mlp, bool off32, const void* src, void* dst, const void* boxes,
+// off32: every box's population arrays are below 4 GiB (32-bit element
+// offsets); nt: streaming loads and stores in the plain step
+void launch_ens_step(int q, int precision, bool mlp, bool off32, bool nt, const void* src, void* dst, const void* boxes,
                      const int* tile_box, int ntiles, float rho0, const void* net, uint32_t* fb, int grid, int block,
                      int occ_waves, int lds_per_cu, hipStream_t st);
 void launch_ens_energy(int q, int precision, const void* buf, const void* boxes, const int* tile_box, int ntiles,
@@ -239,6 +251,6 @@ struct EnsPairItem {
     int w, h, len, W;
 };
 void launch_ens_pair(int q, int precision, const void* src, void* dst, const void* boxes, const EnsPairItem* items,
-                     int nitems, float rho0, hipStream_t st);
+                     int nitems, float rho0, bool nt, hipStream_t st);
 void ens_fill_box_desc(void* out, int L, int tile0, int64_t off, int64_t stride, double omega);
 } // namespace lbm

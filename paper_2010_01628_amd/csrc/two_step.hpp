@@ -82,6 +82,7 @@ struct PairTile {
     int w, h, len;      // nodes stored along x, y and z
     int hx, hy;         // halo columns on each side (1, or 0 where the tile spans the axis)
     int W;              // columns per tile row (the same for every tile of a launch: w + 2 hx of the widest)
+    int nt;             // streaming hint on the stores
 };
 
 // Element at a wavefront-uniform base and a 32-bit per-lane byte offset.
@@ -97,11 +98,11 @@ template <class S> __device__ inline S* lane_at(S* base, uint32_t off)
     return const_cast<S*>(lane_at(static_cast<const S*>(base), off));
 }
 
-// Streaming store of one element at byte offset `off` from a wavefront-uniform
-// base; nothing is written where off lies beyond `range` bytes.
-template <class S> __device__ inline void st_range(S* base, uint32_t range, uint32_t off, S v)
+// Store of one element at byte offset `off` from a wavefront-uniform base;
+// nothing is written where off lies beyond `range` bytes.
+template <class S, bool STREAM> __device__ inline void st_range(S* base, uint32_t range, uint32_t off, S v)
 {
-    constexpr int NT = 2; // the non-temporal bit of the instruction
+    constexpr int NT = STREAM ? 2 : 0; // the non-temporal bit of the instruction
     auto rsrc = __builtin_amdgcn_make_buffer_rsrc(base, 0, range, 0x00027000);
     if constexpr (sizeof(S) == 8) {
         typedef int v2i __attribute__((ext_vector_type(2)));
@@ -162,6 +163,10 @@ __device__ inline void pair_sweep(const S* __restrict__ src, S* __restrict__ dst
     gy = gy < 0 ? gy + t.ny : (gy >= t.ny ? gy - t.ny : gy);
     const bool ylo = WALLS && gy == 0, yhi = WALLS && gy == t.ny - 1;
     auto blocked = [&](int dy) { return WALLS && ((dy < 0 && ylo) || (dy > 0 && yhi)); };
+    // wavefronts with a row at a wall: only these take the bounce-back's
+    // second load over the first (200x101x75 FP32, a pair: with an address
+    // selected per lane in every wavefront 89 us, so 70, without walls 63)
+    const bool at_wall = WALLS && __builtin_amdgcn_ballot_w64(ylo || yhi) != 0;
     // byte offsets of the column and its neighbours within a plane
     uint32_t off[3][3]; // [1 + dx][1 + dy]
     {
@@ -218,15 +223,12 @@ __device__ inline void pair_sweep(const S* __restrict__ src, S* __restrict__ dst
 #pragma unroll
         for (int i = 0; i < Q; ++i) {
             const S* base = pl[1 - L::cz(i)] + i * stride;
-            const uint32_t o = off[1 - L::cx(i)][1 - L::cy(i)];
-            if constexpr (WALLS) {
-                const char* a = reinterpret_cast<const char*>(base) + o;
-                if (L::cy(i) != 0 && blocked(-L::cy(i)))
-                    a = reinterpret_cast<const char*>(pl[1] + L::opp(i) * stride) + self;
-                in[i] = *reinterpret_cast<const S*>(a);
-            } else {
-                in[i] = *lane_at(base, o);
-            }
+            in[i] = *lane_at(base, off[1 - L::cx(i)][1 - L::cy(i)]);
+        }
+        if (at_wall) {
+#pragma unroll
+            for (int i = 0; i < Q; ++i)
+                if (L::cy(i) != 0 && blocked(-L::cy(i))) in[i] = *lane_at(pl[1] + L::opp(i) * stride, off[1][1]);
         }
         if constexpr (FIELD) {
             const double* f = ph.force_field + (int64_t)p * nxy;
@@ -261,8 +263,14 @@ __device__ inline void pair_sweep(const S* __restrict__ src, S* __restrict__ dst
         uint32_t o = stored && on ? self : 0x80000000u;
         asm volatile("" : "+s"(stride), "+v"(o));
         S* const base = dst + (int64_t)z * nxy;
+        const uint32_t range = (uint32_t)nxy * (uint32_t)sizeof(S);
+        if (t.nt) {
 #pragma unroll
-        for (int i = 0; i < Q; ++i) st_range(base + i * stride, (uint32_t)nxy * (uint32_t)sizeof(S), o, Codec<S>::enc(v[i]));
+            for (int i = 0; i < Q; ++i) st_range<S, true>(base + i * stride, range, o, Codec<S>::enc(v[i]));
+        } else {
+#pragma unroll
+            for (int i = 0; i < Q; ++i) st_range<S, false>(base + i * stride, range, o, Codec<S>::enc(v[i]));
+        }
     };
     load(pz);
     arrived();
@@ -310,13 +318,19 @@ __device__ inline void pair_sweep(const S* __restrict__ src, S* __restrict__ dst
                 else if (L::cz(i) < 0) a = ldsM[E::rank(i) * T + c];
                 else if (L::cz(i) == 0) a = rz[E::rank(i) * T + c];
                 else a = rp[E::rank(i) * T + c];
-                if (WALLS && L::cy(i) != 0 && blocked(-L::cy(i))) {
-                    const int o = L::opp(i);
-                    if (L::cz(o) < 0) a = low[o];
-                    else if (L::cz(o) == 0) a = rz[E::rank(o) * T + col];
-                    else a = rpb[E::rank(o) * T + col];
-                }
                 v[i] = Codec<S>::dec(a);
+            }
+            if (at_wall) {
+#pragma unroll
+                for (int i = 0; i < Q; ++i)
+                    if (L::cy(i) != 0 && blocked(-L::cy(i))) {
+                        const int o = L::opp(i);
+                        S a;
+                        if (L::cz(o) < 0) a = low[o];
+                        else if (L::cz(o) == 0) a = rz[E::rank(o) * T + col];
+                        else a = rpb[E::rank(o) * T + col];
+                        v[i] = Codec<S>::dec(a);
+                    }
             }
         }
         __syncthreads(); // every value of this plane's exchange has been taken
@@ -375,6 +389,7 @@ __global__ __launch_bounds__((pair_threads<L, S>())) __attribute__((amdgpu_waves
     t.hx = sh.w < g.nx;
     t.hy = sh.h < g.ny;
     t.W = sh.w + 2 * t.hx;
+    t.nt = sh.nt;
     pair_sweep<L, S, WALLS, GENERAL, FIELD, T>(src, dst, t, ph, key2, g.N, lds);
 }
 
