@@ -112,7 +112,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
 {
     __shared__ uint32_t wave_fb[4];
     __shared__ __align__(16) uint32_t net_lds[MLP_INFER_WORDS];
-    load_net(net_lds, net, MLP_INFER_WORDS);
+    load_net(net_lds, &net->infer, MLP_INFER_WORDS);
     const int w = threadIdx.x >> 6;
     uint32_t my_fb = 0;
     for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
@@ -128,21 +128,21 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
         float s[19];
         gather<LatD3Q19, S, AB, false, true, O32>(src_all + bd.off, g.stride, d, s);
         float xin[MLP_NIN], zout[MLP_NOUT];
+        CMState<float> st;
+        pre_collide<float, true>(s, rho0, 0.0f, 0.0f, 0.0f, st);
         {
-            CMState<float> st0;
-            pre_collide<float, true>(s, rho0, 0.0f, 0.0f, 0.0f, st0);
-            const float ir = 1.0f / st0.rho;
-            xin[0] = st0.rho - 1.0f;
-            xin[1] = st0.k4 * ir;
-            xin[2] = st0.n.m210 * ir;
-            xin[3] = st0.n.m120 * ir;
-            xin[4] = st0.n.m201 * ir;
-            xin[5] = st0.n.m102 * ir;
-            xin[6] = st0.n.m021 * ir;
-            xin[7] = st0.n.m012 * ir;
-            xin[8] = st0.n.m220 * ir;
-            xin[9] = st0.n.m202 * ir;
-            xin[10] = st0.n.m022 * ir;
+            const float ir = 1.0f / st.rho;
+            xin[0] = st.rho - 1.0f;
+            xin[1] = st.k4 * ir;
+            xin[2] = st.n.m210 * ir;
+            xin[3] = st.n.m120 * ir;
+            xin[4] = st.n.m201 * ir;
+            xin[5] = st.n.m102 * ir;
+            xin[6] = st.n.m021 * ir;
+            xin[7] = st.n.m012 * ir;
+            xin[8] = st.n.m220 * ir;
+            xin[9] = st.n.m202 * ir;
+            xin[10] = st.n.m022 * ir;
         }
         // the network, staged in LDS once per work-group, is re-read every
         // tile rather than held in registers across the loop (hoisting its
@@ -150,16 +150,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
         // keeps the reads inside the loop, and LDS reads
         int zoff = 0;
         asm volatile("" : "+s"(zoff));
-        mlp_forward_regs(*reinterpret_cast<const MlpPacked*>(reinterpret_cast<const char*>(net_lds) + zoff), xin, zout);
+        mlp_forward_regs(*reinterpret_cast<const MlpInfer*>(reinterpret_cast<const char*>(net_lds) + zoff), xin, zout);
         const bool fb = mlp_fallback(zout);
-        // recomputed rather than kept live across the network: with the tile
-        // loop's own state, keeping it would spill at four waves per SIMD;
-        // kept at three waves per SIMD (15 % fewer VALU instructions) the
-        // step measured the same
-#pragma unroll
-        for (int i = 0; i < 19; ++i) asm volatile("" : "+v"(s[i]));
-        CMState<float> st;
-        pre_collide<float, true>(s, rho0, 0.0f, 0.0f, 0.0f, st);
         Rates<float> rt;
         rt.omega = (float)bd.omega;
         rt.omega_bulk = 1.0f;

@@ -7,7 +7,7 @@
 namespace lbm {
 
 // Raw features of reading L1 from the pre-collision state (the kernels scale
-// them by MlpPacked::inv_scale).
+// them by MlpInfer::inv_scale).
 template <class R> __device__ inline void mlp_features(const CMState<R>& st, R x[MLP_NIN])
 {
     const R ir = R(1) / st.rho;
@@ -23,6 +23,32 @@ template <class R> __device__ inline void mlp_features(const CMState<R>& st, R x
     x[8] = n.m220 * ir;
     x[9] = n.m202 * ir;
     x[10] = n.m022 * ir;
+}
+
+// Collision with learned rates of this lane's node, populations s in place;
+// returns whether the node fell back.  All 64 lanes take part.
+template <class S>
+__device__ __attribute__((always_inline)) inline bool learned_collide(const MlpInfer& net, const Phys& ph, const ForceRaw& fr, float s[19])
+{
+    float Fx, Fy, Fz;
+    force_value(ph, fr, Fx, Fy, Fz);
+    float xin[MLP_NIN], zout[MLP_NOUT];
+    CMState<float> st;
+    pre_collide<float, true>(s, (float)ph.rho0, Fx, Fy, Fz, st);
+    mlp_features(st, xin);
+    mlp_forward_regs(net, xin, zout);
+    const bool fb = mlp_fallback(zout);
+    const Rates<float> rt = rates_of<float>(ph);
+    RawMoments<float> p;
+    if (fb && ph.omega_bulk == 1.0)
+        relax<float, false>(st, rt, p); // the paper's rates: the plain step's arithmetic, bit for bit
+    else
+        relax_learned(st, rt, zout, p);
+    if constexpr (Codec<S>::increment)
+        post_collide_increment(st, p, s);
+    else
+        post_collide(st, p, s);
+    return fb;
 }
 
 // ---------------------------------------------------------------------------
@@ -45,8 +71,8 @@ __device__ inline void step_mlp_body(const S* src, S* dst, const Geom& g, const 
     // there instead of from memory (~17 KB per wavefront).  Its loads are
     // issued first, the populations' next, so both are in flight together.
     __shared__ __align__(16) uint32_t net_lds[MLP_INFER_WORDS];
-    const NetCopy netcopy = net_copy_begin(net, MLP_INFER_WORDS);
-    const MlpPacked* snet = reinterpret_cast<const MlpPacked*>(net_lds);
+    const NetCopy netcopy = net_copy_begin(&net->infer, MLP_INFER_WORDS);
+    const MlpInfer* snet = reinterpret_cast<const MlpInfer*>(net_lds);
     const int xr = blockIdx.x * blockDim.x + threadIdx.x;
     const int yr = blockIdx.y * blockDim.y + threadIdx.y;
     const bool valid = xr < g.nx && yr < g.ny;
@@ -77,7 +103,7 @@ __device__ inline void step_mlp_body(const S* src, S* dst, const Geom& g, const 
                 }
             }
         }
-        net_copy_finish(netcopy, net, MLP_INFER_WORDS, net_lds);
+        net_copy_finish(netcopy, &net->infer, MLP_INFER_WORDS, net_lds);
         int k = 0;
 #pragma unroll
         for (int i = 0; i < L::Q; ++i) {
@@ -92,41 +118,22 @@ __device__ inline void step_mlp_body(const S* src, S* dst, const Geom& g, const 
         }
     } else {
         gather<LatD3Q19, S, P, WALLS, NT, O32>(src, g.stride, d, s);
-        net_copy_finish(netcopy, net, MLP_INFER_WORDS, net_lds);
+        net_copy_finish(netcopy, &net->infer, MLP_INFER_WORDS, net_lds);
     }
-    float Fx, Fy, Fz;
-    force_value(ph, fr, Fx, Fy, Fz);
-    float xin[MLP_NIN], zout[MLP_NOUT];
-    CMState<float> st;
-    pre_collide<float, true>(s, (float)ph.rho0, Fx, Fy, Fz, st);
-    mlp_features(st, xin);
-    const int tid = threadIdx.x + blockDim.x * threadIdx.y;
-    mlp_forward_regs(*snet, xin, zout);
-    const bool fb = mlp_fallback(zout);
-    const Rates<float> rt = rates_of<float>(ph);
-    RawMoments<float> p;
-    if (fb && ph.omega_bulk == 1.0)
-        relax<float, false>(st, rt, p); // the paper's rates: the plain step's arithmetic, bit for bit
-    else
-        relax_learned(st, rt, zout, p);
-    if constexpr (Codec<S>::increment)
-        post_collide_increment(st, p, s);
-    else
-        post_collide(st, p, s);
+    const bool fb = learned_collide<S>(*snet, ph, fr, s);
     if (valid) scatter<LatD3Q19, S, P, WALLS, NT, O32>(dst, g.stride, d, s);
     // fallback count: one atomic add per wavefront that has fallen-back
     // nodes (none in normal operation), so a wavefront neither waits for the
     // others of its block nor for a read before it retires
     const uint64_t ballot = __ballot(valid && fb);
-    if (ballot != 0 && (tid & 63) == 0) {
+    if (ballot != 0 && ((threadIdx.x + blockDim.x * threadIdx.y) & 63) == 0) {
         const int bid = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
         atomicAdd(&fb_partials[bid], (uint32_t)__popcll(ballot));
     }
 }
 
-// A-B fits four waves per SIMD without spilling (~125 VGPRs, the collision
-// state kept live across the network); the AA variants would spill under
-// that limit and keep the compiler's choice.
+// Five waves per SIMD for A-B and the AA even step (88 VGPRs), four for the
+// AA odd step (125); no spills.
 template <class S, bool WALLS, bool NT, bool O32, bool ROWS = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_step_mlp_ab(
     const S* src, S* dst, Geom g, Phys ph, const MlpPacked* __restrict__ net, uint32_t* __restrict__ fb_partials)
@@ -135,7 +142,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
 }
 
 template <class S, Pattern P, bool WALLS, bool NT>
-__global__ __launch_bounds__(256) void k_step_mlp(const S* src, S* dst, Geom g, Phys ph,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_step_mlp(const S* src, S* dst, Geom g, Phys ph,
                                                   const MlpPacked* __restrict__ net, uint32_t* __restrict__ fb_partials)
 {
     step_mlp_body<S, P, WALLS, NT>(src, dst, g, ph, net, fb_partials);
@@ -315,7 +322,7 @@ __global__ __launch_bounds__(64) void k_train_backward(const float* __restrict__
                                                        int accumulate, TrainLoss tl)
 {
     const float rho0 = (float)ph.rho0;
-    __shared__ MlpPacked snet;
+    __shared__ MlpTrain snet;
     __shared__ uint16_t tx[MLP_TILE], th1[MLP_TILE], th2[MLP_TILE], tdz[MLP_TILE], tdh[MLP_TILE];
     __shared__ float tz[64 * MLP_NIN];
     const int l = threadIdx.x;
@@ -332,10 +339,10 @@ __global__ __launch_bounds__(64) void k_train_backward(const float* __restrict__
         gbar[i] = gbuf[(int64_t)i * g.N + nb(d, LatD3Q19::cx(i), LatD3Q19::cy(i), LatD3Q19::cz(i))];
     // the network, and with `accumulate` the partials of the later steps, which
     // this step's are added to: everything the wavefront reads is in flight at once
-    constexpr int NCHUNK = (int)sizeof(MlpPacked) / 16;
+    constexpr int NCHUNK = (int)sizeof(MlpTrain) / 16;
     uint4 nc[(NCHUNK + 63) / 64];
 #pragma unroll
-    for (int c = 0; c < (NCHUNK + 63) / 64; ++c) nc[c] = reinterpret_cast<const uint4*>(net)[min(c * 64 + l, NCHUNK - 1)];
+    for (int c = 0; c < (NCHUNK + 63) / 64; ++c) nc[c] = reinterpret_cast<const uint4*>(&net->train)[min(c * 64 + l, NCHUNK - 1)];
     float* gp = grad_partials + (int64_t)blockIdx.x * MLP_NPARAM;
     const int col = l & 31, row4 = 4 * (l >> 5); // accumulator register r: row 8 (r / 4) + row4 + r % 4, column col
     float g1[16], g2[16], g3[5], gb[3];
@@ -534,26 +541,36 @@ __global__ __launch_bounds__(256) void k_mlp_pack(const float* __restrict__ thet
                                                   MlpPacked* __restrict__ out)
 {
     const int t = threadIdx.x;
+    MlpInfer& in = out->infer;
+    MlpTrain& tr = out->train;
+    for (int i = t; i < 5 * 512; i += 256) {
+        const int p = i / 512, l = i % 512 / 8, k = mlp_op_unit(p, l, i % 8), o = l & 31;
+        float w = 0.0f;
+        if (p == 0) w = k < MLP_NIN ? theta[MLP_OFF_W1 + o * MLP_NIN + k] : 0.0f;
+        else if (p < 3) w = theta[MLP_OFF_W2 + o * 32 + k];
+        else w = o < MLP_NOUT ? theta[MLP_OFF_W3 + o * 32 + k] : 0.0f;
+        in.op[p][i % 512] = f32_to_bf16(w);
+    }
     for (int i = t; i < 32 * 16; i += 256) {
         const int o = i / 16, k = i % 16;
-        out->w1[i] = k < MLP_NIN ? f32_to_bf16(theta[MLP_OFF_W1 + o * MLP_NIN + k]) : 0;
+        tr.w1[i] = k < MLP_NIN ? f32_to_bf16(theta[MLP_OFF_W1 + o * MLP_NIN + k]) : 0;
     }
     for (int i = t; i < 32 * 32; i += 256) {
         const int o = i / 32, k = i % 32;
         const uint16_t v2 = f32_to_bf16(theta[MLP_OFF_W2 + o * 32 + k]);
-        out->w2[i] = v2;
-        out->w2t[k * 32 + o] = v2;
+        tr.w2[i] = v2;
+        tr.w2t[k * 32 + o] = v2;
         const uint16_t v3 = o < MLP_NOUT ? f32_to_bf16(theta[MLP_OFF_W3 + o * 32 + k]) : 0;
-        out->w3[i] = v3;
-        out->w3t[k * 32 + o] = v3;
-        out->w1t[k * 32 + o] = k < MLP_NIN ? f32_to_bf16(theta[MLP_OFF_W1 + o * MLP_NIN + k]) : 0;
+        tr.w3[i] = v3;
+        tr.w3t[k * 32 + o] = v3;
+        tr.w1t[k * 32 + o] = k < MLP_NIN ? f32_to_bf16(theta[MLP_OFF_W1 + o * MLP_NIN + k]) : 0;
     }
     if (t < 32) {
-        out->b1[t] = theta[MLP_OFF_B1 + t];
-        out->b2[t] = theta[MLP_OFF_B2 + t];
-        out->b3[t] = t < MLP_NOUT ? theta[MLP_OFF_B3 + t] : 0.0f;
+        in.b1[t] = tr.b1[t] = theta[MLP_OFF_B1 + t];
+        in.b2[t] = tr.b2[t] = theta[MLP_OFF_B2 + t];
+        in.b3[t] = tr.b3[t] = t < MLP_NOUT ? theta[MLP_OFF_B3 + t] : 0.0f;
     }
-    if (t < 16) out->inv_scale[t] = t < MLP_NIN ? inv_scale[t] : 0.0f;
+    if (t < 16) in.inv_scale[t] = tr.inv_scale[t] = t < MLP_NIN ? inv_scale[t] : 0.0f;
 }
 
 // D3Q27 populations (canonical, double) -> D3Q19 populations with the same 19

@@ -34,23 +34,41 @@ constexpr int MLP_OFF_W1 = 0, MLP_OFF_B1 = 352, MLP_OFF_W2 = 384, MLP_OFF_B2 = 1
               MLP_OFF_B3 = 1728;
 static_assert(MLP_OFF_B3 + MLP_NOUT == MLP_NPARAM, "parameter layout");
 
-// Packed network as the kernels read it (built by k_mlp_pack from the FP32
-// master parameters).  Matrices are bf16 [row][col], zero padded to 32 x 32
-// (W1 to 32 x 16); the transposed copies serve the backward products.
-struct alignas(16) MlpPacked {
-    // inference part (what the step kernels read)
+// Network as the step kernels read it: the weight operands of the five
+// products (layer 1, layers 2 and 3 in two k-steps each) in lane order, lane l
+// of a product holding the eight bf16 at op[product][8 l], so that a
+// wavefront's read of one is 1 KiB in a row.  (Rows of the 32 x 32 matrices
+// lie 64 bytes apart, and 32 lanes reading one row each met 8 to 16 in a bank:
+// 456 of the 656 LDS cycles per wavefront, the LDS 87 % busy through the
+// learned 192^3 FP16 step.)
+struct alignas(16) MlpInfer {
+    uint16_t op[5][64 * 8];
+    float b1[32], b2[32], b3[32];
+    float inv_scale[16];
+};
+constexpr int MLP_INFER_WORDS = (int)sizeof(MlpInfer) / 4;
+static_assert(MLP_INFER_WORDS % 4 == 0, "16-byte network copies");
+
+// Network as the training kernel reads it: matrices bf16 [row][col], zero
+// padded to 32 x 32 (W1 to 32 x 16); the transposed copies serve the backward
+// products.
+struct alignas(16) MlpTrain {
     uint16_t w1[32 * 16]; // [out][in]
     uint16_t w2[32 * 32]; // [out][in]
     uint16_t w3[32 * 32]; // [out (9 used)][in]
     float b1[32], b2[32], b3[32];
     float inv_scale[16];
-    // transposed copies for the backward pass
     uint16_t w2t[32 * 32]; // [in][out]
     uint16_t w3t[32 * 32]; // [in][out (9 used)]
     uint16_t w1t[32 * 32]; // [in (11 used)][out]
 };
-constexpr int MLP_INFER_WORDS = (int)(__builtin_offsetof(MlpPacked, w2t) / 4);
-static_assert(MLP_INFER_WORDS % 4 == 0 && sizeof(MlpPacked) % 16 == 0, "16-byte network copies");
+static_assert(sizeof(MlpTrain) % 16 == 0, "16-byte network copies");
+
+// Packed network (built by k_mlp_pack from the FP32 master parameters).
+struct MlpPacked {
+    MlpInfer infer;
+    MlpTrain train;
+};
 
 // Cooperative copy of the first `words` 32-bit words (a multiple of four) of
 // the packed network into 16-byte aligned LDS, in two parts so that a kernel
@@ -65,7 +83,7 @@ struct NetCopy {
     uint4 r0, r1;
     int i0, i1;
 };
-__device__ __attribute__((always_inline)) inline NetCopy net_copy_begin(const MlpPacked* __restrict__ src, int words)
+__device__ __attribute__((always_inline)) inline NetCopy net_copy_begin(const MlpInfer* __restrict__ src, int words)
 {
     const int tid = threadIdx.x + blockDim.x * threadIdx.y;
     const int nthr = blockDim.x * blockDim.y;
@@ -78,7 +96,7 @@ __device__ __attribute__((always_inline)) inline NetCopy net_copy_begin(const Ml
     c.r1 = s[c.i1];
     return c;
 }
-__device__ __attribute__((always_inline)) inline void net_copy_finish(const NetCopy& c, const MlpPacked* __restrict__ src,
+__device__ __attribute__((always_inline)) inline void net_copy_finish(const NetCopy& c, const MlpInfer* __restrict__ src,
                                                                       int words, uint32_t* d)
 {
     const int tid = threadIdx.x + blockDim.x * threadIdx.y;
@@ -92,7 +110,7 @@ __device__ __attribute__((always_inline)) inline void net_copy_finish(const NetC
     __syncthreads();
 }
 
-__device__ inline void load_net(uint32_t* d, const MlpPacked* __restrict__ src, int words)
+__device__ inline void load_net(uint32_t* d, const MlpInfer* __restrict__ src, int words)
 {
     net_copy_finish(net_copy_begin(src, words), src, words, d);
 }
@@ -156,7 +174,7 @@ __device__ inline int acc_row(int rb, int r) { return rb * 32 + 8 * (r >> 2) + 4
 // features.  Tiles: tx (inputs), th1, th2 (hidden activations, kept for the
 // backward pass), tz (outputs as floats, 64 x 9).  On return z holds this
 // lane's 9 outputs.  Must be called by all 64 lanes.
-__device__ inline void mlp_forward_wave(const MlpPacked& W, uint16_t* tx, uint16_t* th1, uint16_t* th2, float* tz,
+__device__ inline void mlp_forward_wave(const MlpTrain& W, uint16_t* tx, uint16_t* th1, uint16_t* th2, float* tz,
                                         const float x[MLP_NIN], float z[MLP_NOUT])
 {
     const int l = lane_id();
@@ -212,9 +230,9 @@ __device__ inline void mlp_forward_wave(const MlpPacked& W, uint16_t* tx, uint16
 // Y^T[8 (r / 4) + 4 (l / 32) + r % 4][l % 32]: for k-step m (16 hidden
 // units) slots 0..3 are units 16 m + 4 (l / 32) + 0..3 and slots 4..7 units
 // 16 m + 8 + 4 (l / 32) + 0..3, i.e. acc[8m .. 8m+7].  Hidden layers chain
-// without data movement; the weight operand reads the two matching 8-byte
-// runs of the row.  The input layer takes features 8 (l / 32) + v (one
-// 16-byte run of the zero-padded W1 row).  Only the input (lane = node,
+// without data movement; the weight operands are packed in this order
+// (mlp_op_unit).  The input layer takes features 8 (l / 32) + v.  Only the
+// input (lane = node,
 // features split over the two half-waves) and the output (rates back to the
 // node's lane) cross half-waves, by v_permlane32_swap.
 // ---------------------------------------------------------------------------
@@ -286,34 +304,47 @@ __device__ inline void act_to_operands(const f32x16_t& acc, bf16x8_t op[2])
     }
 }
 
-// weight operand of a hidden layer's k-step m: row l % 32 of the 32 x 32
-// matrix, units 16 m + 4 (l / 32) + 0..3 and 16 m + 8 + 4 (l / 32) + 0..3
-__device__ inline bf16x8_t w_hidden(const uint16_t* w, int row, int kh, int m)
+// hidden unit (or, product 0, feature) in slot v of lane l of product p
+__host__ __device__ inline int mlp_op_unit(int p, int l, int v)
 {
-    typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
-    const u32x2_t a = *reinterpret_cast<const u32x2_t*>(w + row * 32 + 16 * m + kh);
-    const u32x2_t b = *reinterpret_cast<const u32x2_t*>(w + row * 32 + 16 * m + 8 + kh);
-    return __builtin_bit_cast(bf16x8_t, (u32x4_t){a[0], a[1], b[0], b[1]});
+    if (p == 0) return 8 * (l >> 5) + v;
+    return 16 * ((p - 1) & 1) + 8 * (v >> 2) + 4 * (l >> 5) + (v & 3);
+}
+
+// weight operand of product p: outputs l % 32, units mlp_op_unit
+__device__ inline bf16x8_t w_op(const MlpInfer& W, int p)
+{
+    return __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4_t*>(&W.op[p][8 * lane_id()]));
 }
 
 // One 32-node column block through the three layers; o[q] = accumulator
 // rows q (q < 5) of the output layer.
-__device__ inline void mlp_block_regs(const MlpPacked& W, const bf16x8_t in, float o[5])
+//
+// What bounds the learned steps: the issue of about 690 VALU instructions and
+// ten products per wavefront beside the step's own traffic.  The scheduling
+// barriers (here between the layers, in mlp_forward_regs between the blocks)
+// keep the biases and operands of one product at a time in registers: 88
+// VGPRs and five waves per SIMD in place of 125 and four for A-B, 125 and four
+// in place of 200 and two for the AA odd step.  With them and the operands in
+// lane order, us per step: FP16 192^3 A-B 156 -> 148, AA 204 -> 161, 128^3 A-B
+// 47 -> 40, AA 60 -> 43; FP32 192^3 A-B 198 -> 195, AA 233 -> 216.  (Without
+// the barriers A-B takes 152; loading the next 64 nodes' populations ahead of
+// the network, four waves per SIMD, 148 at 192^3 and 45 at 128^3.)
+__device__ inline void mlp_block_regs(const MlpInfer& W, const bf16x8_t in, float o[5])
 {
-    const int l = lane_id();
-    const int row = l & 31, kh = 4 * (l >> 5);
     f32x16_t acc = bias_acc(W.b1);
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-        __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4_t*>(W.w1 + row * 16 + 2 * kh)), in, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w_op(W, 0), in, acc, 0, 0, 0);
     bf16x8_t h[2];
     act_to_operands(acc, h);
+    __builtin_amdgcn_sched_barrier(0);
     acc = bias_acc(W.b2);
 #pragma unroll
-    for (int m = 0; m < 2; ++m) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w_hidden(W.w2, row, kh, m), h[m], acc, 0, 0, 0);
+    for (int m = 0; m < 2; ++m) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w_op(W, 1 + m), h[m], acc, 0, 0, 0);
     act_to_operands(acc, h);
+    __builtin_amdgcn_sched_barrier(0);
     acc = bias_acc(W.b3);
 #pragma unroll
-    for (int m = 0; m < 2; ++m) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w_hidden(W.w3, row, kh, m), h[m], acc, 0, 0, 0);
+    for (int m = 0; m < 2; ++m) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w_op(W, 3 + m), h[m], acc, 0, 0, 0);
 #pragma unroll
     for (int q = 0; q < 5; ++q) o[q] = acc[q];
 }
@@ -321,7 +352,7 @@ __device__ inline void mlp_block_regs(const MlpPacked& W, const bf16x8_t in, flo
 // Forward pass for the 64 nodes of this wavefront (node = lane), network W in
 // global or LDS memory.  x: this lane's 11 raw features; z: its 9 outputs.
 // Must be called by all 64 lanes.
-__device__ inline void mlp_forward_regs(const MlpPacked& W, const float x[MLP_NIN], float z[MLP_NOUT])
+__device__ inline void mlp_forward_regs(const MlpInfer& W, const float x[MLP_NIN], float z[MLP_NOUT])
 {
     // input operands: features scaled and rounded, lo = features 0..7 and
     // hi = 8..15 of this lane's node; after the swap lo feeds block 0
@@ -347,6 +378,7 @@ __device__ inline void mlp_forward_regs(const MlpPacked& W, const float x[MLP_NI
     // o_b[4]: output 8 (lanes < 32)
     float o0[5], o1[5];
     mlp_block_regs(W, __builtin_bit_cast(bf16x8_t, lo), o0);
+    __builtin_amdgcn_sched_barrier(0);
     mlp_block_regs(W, __builtin_bit_cast(bf16x8_t, hi), o1);
 #pragma unroll
     for (int q = 0; q < 5; ++q) swap_halves(o0[q], o1[q]);
