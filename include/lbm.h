@@ -190,8 +190,10 @@ typedef struct {
                                  through LDS on periodic lattices */
     int32_t cache_policy;     /* population loads/stores: 0 = library default (non-temporal
                                  for staged steps and for A-B with 4- and 8-byte storage,
-                                 cached otherwise), 1 = non-temporal (streaming) hints,
-                                 2 = ordinary cached accesses */
+                                 cached otherwise; cached too where all buffers together
+                                 hold 48 MB to 256 MiB, or 48 MB and more in x rows that
+                                 are not whole 128-byte lines), 1 = non-temporal
+                                 (streaming) hints, 2 = ordinary cached accesses */
     int32_t coupled;          /* lbm_coupling */
     lbm_phase_params phase;   /* LBM_COUPLED_PHASE: q = 19, FP64 or FP32, A-B, periodic, no
                                  external force, the paper's bulk and higher-order rates,

@@ -93,7 +93,7 @@ __global__ __launch_bounds__((pair_threads<L, S>())) __attribute__((amdgpu_waves
     t.hx = it.w < bd.L;
     t.hy = it.h < bd.L;
     t.W = it.W;
-    t.nt = nt;
+    t.nt = nt && bd.L * sizeof(S) % 128 == 0; // rows sharing lines: ordinary stores (ordinary_accesses)
     Phys ph{};
     ph.omega = bd.omega;
     ph.omega_bulk = 1.0;

@@ -118,7 +118,7 @@ std::vector<lbm::EnsPairItem> pair_list(const lbm_ensemble* e, int cus)
     for (int b = 0; b < e->nboxes; ++b) {
         int a = 0;
         while (e->L[a] != e->L[b]) ++a;
-        tile[b] = a < b ? tile[a] : lbm::pair_tile(e->L[b], e->L[b], e->q, e->eb, !e->nt, threads, &us[b]);
+        tile[b] = a < b ? tile[a] : lbm::pair_tile(e->L[b], e->L[b], e->q, e->eb, !e->nt || e->L[b] * e->eb % 128 != 0, threads, &us[b]);
         if (a < b) us[b] = us[a];
         if (tile[b].w == 0) return {};
     }
@@ -137,7 +137,7 @@ std::vector<lbm::EnsPairItem> pair_list(const lbm_ensemble* e, int cus)
             best_len = len;
         }
     }
-    const double single_us = std::max(4.0, 2e-6 * e->q * e->eb * (double)e->nodes / 5.55);
+    const double single_us = std::max(4.0, 2e-6 * e->q * e->eb * (double)e->nodes / (e->nt ? 5.55 : 6.1));
     if (!(env && env[0] == '1') && best_us > 0.95 * 2 * single_us) return {};
     struct Run {
         int box, z0, len;
@@ -292,7 +292,7 @@ int lbm_ensemble_create(const lbm_box* boxes, int32_t nboxes, int32_t q, int32_t
         hipMalloc((void**)&e->fb, sizeof(uint32_t) * (size_t)(e->fb_len = std::max<int64_t>((int64_t)ncu * 64, tiles))) !=
             hipSuccess)
         return cleanup(efail(LBM_ENOMEM, "ensemble tables"));
-    e->nt = !lbm::fits_last_level_cache((int64_t)2 * e->q * e->nodes * e->eb);
+    e->nt = !lbm::ordinary_accesses((int64_t)2 * e->q * e->nodes * e->eb, 128);
     const std::vector<lbm::EnsPairItem> list = pair_list(e, ncu);
     if (!list.empty() && hipMalloc((void**)&e->pair_dev, sizeof(list[0]) * list.size()) != hipSuccess)
         return cleanup(efail(LBM_ENOMEM, "ensemble tables"));

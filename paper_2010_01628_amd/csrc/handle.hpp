@@ -39,7 +39,7 @@ struct lbm_handle {
     int row_stage_pref = -1;           // -1: default (staged wherever possible), 0/1: tuner's choice
     lbm::PairShape pair{};             // tiles of the two-steps-per-pass launch
     bool pair_ok = false;              // lbm_step takes two steps per pass where it can
-    bool cached = false;               // the state stays in the last-level cache: ordinary loads and stores
+    bool cached = false;               // population accesses without the streaming hint (ordinary_accesses)
     bool walls = false, general = false, nt = true;
     int64_t bytes = 0;
     int nblocks = 0;

@@ -208,20 +208,22 @@ int64_t pad_stride(int64_t N, int eb)
 
 // Two steps per pass (two_step.hpp): A-B, single phase, where a pair is
 // estimated faster than two single steps.  A single step is estimated at its
-// traffic at 6.1 TB/s, 1.04 times that on rows of whole 128-byte lines and
-// 1.5 times on others, whose stores share lines between rows (1.1 times, 1.25
-// with 2-byte storage, where the last-level cache holds the lattice, `cached`:
-// it merges them), and at least 4 us.  Two steps measured against a pair, us:
-// 256^3 FP32 834 / 612, with walls 856 / 620, FP64 1805 / 1367, FP16 430 / 436
-// (single); 192^3 FP32 388 / 278; 113x293x281 FP32 852 / 382, FP16 379 / 260;
-// 64^3 FP32 15 / 22 (single); D3Q27 128^3 FP32 160 / 127.  In the cache:
-// 200x101x75 FP32 79 / 63, with walls 78 / 70, FP16 49 / 61 (single); FP32
-// 100^3 56 / 44, 128x128x96 73 / 58, 72^3 26 / 24 (single); FP64 80^3 51 / 42,
-// 91^3 78 / 59; D3Q27 96^3 FP32 62 / 61, 64^3 22 / 30 (single).
+// traffic at 6.1 TB/s, 1.04 times that on rows of whole 128-byte lines; on
+// others, whose stores share lines between rows, 1.5 times with streaming
+// accesses, 1.2 to 1.55 times by the storage with ordinary ones (`cached`),
+// 1.1 to 1.25 times where the last-level cache holds both buffers (`fits`);
+// at least 4 us.  Two steps measured against a pair, us: 256^3 FP32 834 / 612,
+// with walls 856 / 620, FP64 1805 / 1367, FP16 430 / 436 (single); 64^3 FP32
+// 15 / 22 (single); D3Q27 128^3 FP32 160 / 127.  Rows sharing lines: 200^3
+// FP16 329 / 235, FP32 534 / 322, FP64 1002 / 625, D3Q27 FP32 800 / 637;
+// 500x110x120 FP16 242 / 229, FP32 413 / 329.  In the cache: 200x101x75 FP32
+// 79 / 63, with walls 78 / 70, FP16 49 / 61 (single); FP32 100^3 56 / 44,
+// 128x128x96 73 / 58, 72^3 26 / 24 (single); FP64 80^3 51 / 42, 91^3 78 / 59;
+// D3Q27 96^3 FP32 62 / 61, 64^3 22 / 30 (single).
 // LBM_TWO_STEP=0 keeps single steps, =1 takes sweeps wherever they are
 // possible.  Lattices small enough for one work-group per compute unit take
 // blocks instead.
-void set_pair(lbm_handle* h, bool cached)
+void set_pair(lbm_handle* h, bool cached, bool fits)
 {
     h->pair_ok = false;
     if (h->p.streaming != LBM_AB || h->p.coupled != LBM_COUPLED_NONE) return;
@@ -231,7 +233,7 @@ void set_pair(lbm_handle* h, bool cached)
     const int eb = elem_bytes(h->p.precision);
     const double traffic_us = 2e-6 * h->p.q * eb * (double)h->g.N / 6.1;
     const bool aligned = (int64_t)h->g.nx * eb % 128 == 0;
-    const double single_us = std::max(4.0, traffic_us * (aligned ? 1.04 : (cached ? (eb == 2 ? 1.25 : 1.1) : 1.5)));
+    const double single_us = std::max(4.0, traffic_us * (aligned ? 1.04 : !cached ? 1.5 : fits ? (eb == 2 ? 1.25 : 1.1) : (eb == 2 ? 1.55 : eb == 4 ? 1.3 : 1.2)));
     const bool forced = env && env[0] == '1';
     int cus = 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, h->device) != hipSuccess || cus <= 0) return;
@@ -393,9 +395,9 @@ int lbm_create(const lbm_params* p, void* stream, lbm_handle** out)
         const int coupled = p->coupled == LBM_COUPLED_PHASE ? 7 : p->coupled == LBM_COUPLED_MAGNETIC ? 21
                             : p->coupled == LBM_COUPLED_COLOUR ? 19 : 0;
         const int64_t bytes = (int64_t)(p->streaming == LBM_AB ? 2 : 1) * (p->q + coupled) * h->g.N * eb;
-        h->cached = p->cache_policy == 2 || (p->cache_policy == 0 && lbm::fits_last_level_cache(bytes));
+        h->cached = p->cache_policy == 2 || (p->cache_policy == 0 && lbm::ordinary_accesses(bytes, (int64_t)p->nx * eb));
         if (h->cached) h->nt = false;
-        set_pair(h, h->cached && lbm::fits_last_level_cache(bytes));
+        set_pair(h, h->cached, bytes <= ((int64_t)256 << 20));
     }
 
     const int64_t pop_bytes = (int64_t)p->q * h->g.stride * eb;

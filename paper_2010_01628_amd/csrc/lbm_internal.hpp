@@ -107,15 +107,23 @@ struct PairShape {
     int block;
     int nt = 1; // streaming hint on the sweeps' stores
 };
-// Whether a state of this many bytes (all buffers of all lattices) is kept in
-// the caches from one step to the next, so that the steps take ordinary loads
-// and stores instead of streaming ones: more than the L2s hold and no more
-// than the 256 MiB last-level cache.  Streaming / ordinary, us per step: FP32
+// Whether the steps take ordinary loads and stores instead of streaming ones,
+// for a state of this many bytes (all buffers of all lattices) in x rows of
+// row_bytes: states larger than the L2s hold that either stay in the 256 MiB
+// last-level cache from one step to the next or have rows that are not whole
+// 128-byte lines, whose shared lines it merges.  In the cache, streaming / ordinary, us per step: FP32
 // 96^3 26.6 / 19.4, 100^3 41 / 23.6, FP16 128^3 29.4 / 21.9, FP32 AA 128^3
 // 54.8 / 40.5, Shan-Chen 100^3 50.4 / 42.6, two-phase 96^3 43.9 / 32.7,
 // magnetic 64^3 17.6 / 12.9; below the range (40 MB) FP32 64^3 7.5 / 8.1,
 // above it (320 MB) Shan-Chen 128^3 85 / 88, two-phase 128^3 (436 MB) 85 / 94.
-inline bool fits_last_level_cache(int64_t bytes) { return bytes >= 48000000 && bytes <= ((int64_t)256 << 20); }
+// Larger ones with such rows: 200^3 FP32 320 / 265 (a pair of steps), FP16 255
+// / 164, FP32 AA 340 / 257; 330x150x200 FP32 282 / 219 (two steps per pass),
+// FP64 516 / 389; 208x200x200 FP16 248 / 183; with whole lines, 256x256x200
+// FP32 242 / 254, AA 333 / 361.
+inline bool ordinary_accesses(int64_t bytes, int64_t row_bytes)
+{
+    return bytes >= 48000000 && (bytes <= ((int64_t)256 << 20) || row_bytes % 128 != 0);
+}
 // threads of the pair kernel's work-groups (columns of a tile, halo included)
 int pair_threads_q19(int precision);
 int pair_threads_q27(int precision);

@@ -34,7 +34,10 @@ double plane_us(int nx, int ny, int q, int eb, bool cached, int w, int h)
     const bool aligned = (int64_t)nx * eb % 128 == 0 && (int64_t)w * eb % 128 == 0;
     const double row = (double)w * eb / 128;
     const double lines = H * (row + (aligned ? 2 * hx : (cached ? hx : 1 + hx))) + h * (row + (aligned || cached ? 0 : 2));
-    return 0.8 + (eb == 8 ? 2 : 1) * 0.14 * waves * q / 19 + 0.047 * lines * q / 19;
+    const double us = 0.8 + (eb == 8 ? 2 : 1) * 0.14 * waves * q / 19 + 0.047 * lines * q / 19;
+    // three wavefronts per SIMD (D3Q27, 4 bytes) issue less well than two or
+    // four: 200^3 505 us without this factor, measured 637, 96^3 50 / 61
+    return q == 27 && eb <= 4 ? 1.2 * us : us;
 }
 
 // The tile sizes worth trying: widths of whole lines and equal shares of the
