@@ -150,7 +150,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
         // keeps the reads inside the loop, and LDS reads
         int zoff = 0;
         asm volatile("" : "+s"(zoff));
-        mlp_forward_regs(*reinterpret_cast<const MlpInfer*>(reinterpret_cast<const char*>(net_lds) + zoff), xin, zout);
+        mlp_forward_regs<true>(*reinterpret_cast<const MlpInfer*>(reinterpret_cast<const char*>(net_lds) + zoff), xin, zout);
         const bool fb = mlp_fallback(zout);
         Rates<float> rt;
         rt.omega = (float)bd.omega;

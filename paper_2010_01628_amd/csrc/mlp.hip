@@ -27,7 +27,7 @@ template <class R> __device__ inline void mlp_features(const CMState<R>& st, R x
 
 // Collision with learned rates of this lane's node, populations s in place;
 // returns whether the node fell back.  All 64 lanes take part.
-template <class S>
+template <class S, bool SERIAL>
 __device__ __attribute__((always_inline)) inline bool learned_collide(const MlpInfer& net, const Phys& ph, const ForceRaw& fr, float s[19])
 {
     float Fx, Fy, Fz;
@@ -36,7 +36,7 @@ __device__ __attribute__((always_inline)) inline bool learned_collide(const MlpI
     CMState<float> st;
     pre_collide<float, true>(s, (float)ph.rho0, Fx, Fy, Fz, st);
     mlp_features(st, xin);
-    mlp_forward_regs(net, xin, zout);
+    mlp_forward_regs<SERIAL>(net, xin, zout);
     const bool fb = mlp_fallback(zout);
     const Rates<float> rt = rates_of<float>(ph);
     RawMoments<float> p;
@@ -120,7 +120,8 @@ __device__ inline void step_mlp_body(const S* src, S* dst, const Geom& g, const 
         gather<LatD3Q19, S, P, WALLS, NT, O32>(src, g.stride, d, s);
         net_copy_finish(netcopy, &net->infer, MLP_INFER_WORDS, net_lds);
     }
-    const bool fb = learned_collide<S>(*snet, ph, fr, s);
+    // SERIAL (mlp_block_regs): the AA steps and streamed 2-byte A-B
+    const bool fb = learned_collide<S, P != AB || (NT && sizeof(S) == 2)>(*snet, ph, fr, s);
     if (valid) scatter<LatD3Q19, S, P, WALLS, NT, O32>(dst, g.stride, d, s);
     // fallback count: one atomic add per wavefront that has fallen-back
     // nodes (none in normal operation), so a wavefront neither waits for the
@@ -132,8 +133,8 @@ __device__ inline void step_mlp_body(const S* src, S* dst, const Geom& g, const 
     }
 }
 
-// Five waves per SIMD for A-B and the AA even step (88 VGPRs), four for the
-// AA odd step (125); no spills.
+// Four waves per SIMD or more without spills, three for the AA odd step with
+// walls.
 template <class S, bool WALLS, bool NT, bool O32, bool ROWS = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_step_mlp_ab(
     const S* src, S* dst, Geom g, Phys ph, const MlpPacked* __restrict__ net, uint32_t* __restrict__ fb_partials)
@@ -142,7 +143,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
 }
 
 template <class S, Pattern P, bool WALLS, bool NT>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_step_mlp(const S* src, S* dst, Geom g, Phys ph,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((P == AA_ODD && WALLS ? 3 : 4)))) void k_step_mlp(const S* src, S* dst, Geom g, Phys ph,
                                                   const MlpPacked* __restrict__ net, uint32_t* __restrict__ fb_partials)
 {
     step_mlp_body<S, P, WALLS, NT>(src, dst, g, ph, net, fb_partials);

@@ -321,27 +321,31 @@ __device__ inline bf16x8_t w_op(const MlpInfer& W, int p)
 // rows q (q < 5) of the output layer.
 //
 // What bounds the learned steps: the issue of about 690 VALU instructions and
-// ten products per wavefront beside the step's own traffic.  The scheduling
-// barriers (here between the layers, in mlp_forward_regs between the blocks)
-// keep the biases and operands of one product at a time in registers: 88
-// VGPRs and five waves per SIMD in place of 125 and four for A-B, 125 and four
-// in place of 200 and two for the AA odd step.  With them and the operands in
-// lane order, us per step: FP16 192^3 A-B 156 -> 148, AA 204 -> 161, 128^3 A-B
-// 47 -> 40, AA 60 -> 43; FP32 192^3 A-B 198 -> 195, AA 233 -> 216.  (Without
-// the barriers A-B takes 152; loading the next 64 nodes' populations ahead of
-// the network, four waves per SIMD, 148 at 192^3 and 45 at 128^3.)
+// ten products per wavefront beside the step's own traffic.  SERIAL:
+// scheduling barriers (here between the layers, in mlp_forward_regs between
+// the blocks) keep the biases and operands of one product at a time in
+// registers: 88 VGPRs and five waves per SIMD in place of 125 and four for
+// A-B, 125 and four in place of 200 and two for the AA odd step.  They pay
+// where the populations come from memory two bytes at a time, or where the
+// registers allow two waves: us per step without / with them, FP16 A-B 192^3
+// 148 / 145, 256^3 328 / 324, in the last-level cache 128^3 39.2 / 40.4,
+// 114x110x79 with walls 24.8 / 25.8; FP32 A-B 256^3 434 / 437; FP16 AA 192^3
+// 201 / 161.  (With the weights read by rows of the matrices FP16 A-B 192^3
+// took 152, 128^3 46.6, AA 204; loading the next 64 nodes' populations ahead
+// of the network, four waves per SIMD, 148 and 45.)
+template <bool SERIAL>
 __device__ inline void mlp_block_regs(const MlpInfer& W, const bf16x8_t in, float o[5])
 {
     f32x16_t acc = bias_acc(W.b1);
     acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w_op(W, 0), in, acc, 0, 0, 0);
     bf16x8_t h[2];
     act_to_operands(acc, h);
-    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (SERIAL) __builtin_amdgcn_sched_barrier(0);
     acc = bias_acc(W.b2);
 #pragma unroll
     for (int m = 0; m < 2; ++m) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w_op(W, 1 + m), h[m], acc, 0, 0, 0);
     act_to_operands(acc, h);
-    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (SERIAL) __builtin_amdgcn_sched_barrier(0);
     acc = bias_acc(W.b3);
 #pragma unroll
     for (int m = 0; m < 2; ++m) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w_op(W, 3 + m), h[m], acc, 0, 0, 0);
@@ -352,6 +356,7 @@ __device__ inline void mlp_block_regs(const MlpInfer& W, const bf16x8_t in, floa
 // Forward pass for the 64 nodes of this wavefront (node = lane), network W in
 // global or LDS memory.  x: this lane's 11 raw features; z: its 9 outputs.
 // Must be called by all 64 lanes.
+template <bool SERIAL>
 __device__ inline void mlp_forward_regs(const MlpInfer& W, const float x[MLP_NIN], float z[MLP_NOUT])
 {
     // input operands: features scaled and rounded, lo = features 0..7 and
@@ -377,9 +382,9 @@ __device__ inline void mlp_forward_regs(const MlpInfer& W, const float x[MLP_NIN
     // o_b[q]: output q (lanes < 32) or 4 + q (lanes >= 32) of node 32 b + l % 32;
     // o_b[4]: output 8 (lanes < 32)
     float o0[5], o1[5];
-    mlp_block_regs(W, __builtin_bit_cast(bf16x8_t, lo), o0);
-    __builtin_amdgcn_sched_barrier(0);
-    mlp_block_regs(W, __builtin_bit_cast(bf16x8_t, hi), o1);
+    mlp_block_regs<SERIAL>(W, __builtin_bit_cast(bf16x8_t, lo), o0);
+    if constexpr (SERIAL) __builtin_amdgcn_sched_barrier(0);
+    mlp_block_regs<SERIAL>(W, __builtin_bit_cast(bf16x8_t, hi), o1);
 #pragma unroll
     for (int q = 0; q < 5; ++q) swap_halves(o0[q], o1[q]);
 #pragma unroll
