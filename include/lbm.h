@@ -192,7 +192,8 @@ typedef struct {
                                  for staged steps and for A-B with 4- and 8-byte storage,
                                  cached otherwise; cached too where all buffers together
                                  hold 48 MB to 256 MiB, or 48 MB and more in x rows that
-                                 are not whole 128-byte lines), 1 = non-temporal
+                                 are not whole 128-byte lines, and for single steps that
+                                 take the planes in turn upwards and downwards), 1 = non-temporal
                                  (streaming) hints, 2 = ordinary cached accesses */
     int32_t coupled;          /* lbm_coupling */
     lbm_phase_params phase;   /* LBM_COUPLED_PHASE: q = 19, FP64 or FP32, A-B, periodic, no

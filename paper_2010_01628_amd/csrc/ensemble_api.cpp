@@ -292,7 +292,7 @@ int lbm_ensemble_create(const lbm_box* boxes, int32_t nboxes, int32_t q, int32_t
         hipMalloc((void**)&e->fb, sizeof(uint32_t) * (size_t)(e->fb_len = std::max<int64_t>((int64_t)ncu * 64, tiles))) !=
             hipSuccess)
         return cleanup(efail(LBM_ENOMEM, "ensemble tables"));
-    e->nt = !lbm::ordinary_accesses((int64_t)2 * e->q * e->nodes * e->eb, 128);
+    e->nt = !lbm::ordinary_accesses((int64_t)2 * e->q * e->nodes * e->eb, 2, 128);
     const std::vector<lbm::EnsPairItem> list = pair_list(e, ncu);
     if (!list.empty() && hipMalloc((void**)&e->pair_dev, sizeof(list[0]) * list.size()) != hipSuccess)
         return cleanup(efail(LBM_ENOMEM, "ensemble tables"));

@@ -40,6 +40,7 @@ struct lbm_handle {
     lbm::PairShape pair{};             // tiles of the two-steps-per-pass launch
     bool pair_ok = false;              // lbm_step takes two steps per pass where it can
     bool cached = false;               // population accesses without the streaming hint (ordinary_accesses)
+    bool alternate = false;            // single steps take the planes upwards and downwards in turn
     bool walls = false, general = false, nt = true;
     int64_t bytes = 0;
     int nblocks = 0;

@@ -142,6 +142,9 @@ __device__ inline bool thread_node(const Geom& g, int& x, int& y, int& z)
     return x < g.nx && y < g.ny;
 }
 
+// Plane of this work-group of a single step (Geom::rev).
+__device__ inline int plane_z(const Geom& g) { return g.rev ? g.nz - 1 - blockIdx.z : blockIdx.z; }
+
 // index of node x + (dx, dy, dz), dx etc. in {-1, 0, 1}
 __device__ inline int nb(const NodeIdx& d, int dx, int dy, int dz) { return d.ox[1 + dx] + d.oy[1 + dy] + d.oz[1 + dz]; }
 
@@ -400,11 +403,11 @@ __device__ inline void block_coords(const Geom& g, int chunk, int& bxi, int& byi
         bxi = L % gx;
         const int t = L / gx;
         byi = t % gy;
-        bz = t / gy;
+        bz = g.rev ? g.nz - 1 - t / gy : t / gy;
     } else {
         bxi = blockIdx.x;
         byi = blockIdx.y;
-        bz = blockIdx.z;
+        bz = plane_z(g);
     }
 }
 

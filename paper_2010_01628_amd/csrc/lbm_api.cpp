@@ -211,7 +211,7 @@ int64_t pad_stride(int64_t N, int eb)
 // traffic at 6.1 TB/s, 1.04 times that on rows of whole 128-byte lines; on
 // others, whose stores share lines between rows, 1.5 times with streaming
 // accesses, 1.2 to 1.55 times by the storage with ordinary ones (`cached`),
-// 1.1 to 1.25 times where the last-level cache holds both buffers (`fits`);
+// 1.1 to 1.15 times where the last-level cache holds both buffers (`fits`);
 // at least 4 us.  Two steps measured against a pair, us: 256^3 FP32 834 / 612,
 // with walls 856 / 620, FP64 1805 / 1367, FP16 430 / 436 (single); 64^3 FP32
 // 15 / 22 (single); D3Q27 128^3 FP32 160 / 127.  Rows sharing lines: 200^3
@@ -233,7 +233,7 @@ void set_pair(lbm_handle* h, bool cached, bool fits)
     const int eb = elem_bytes(h->p.precision);
     const double traffic_us = 2e-6 * h->p.q * eb * (double)h->g.N / 6.1;
     const bool aligned = (int64_t)h->g.nx * eb % 128 == 0;
-    const double single_us = std::max(4.0, traffic_us * (aligned ? 1.04 : !cached ? 1.5 : fits ? (eb == 2 ? 1.25 : 1.1) : (eb == 2 ? 1.55 : eb == 4 ? 1.3 : 1.2)));
+    const double single_us = std::max(4.0, traffic_us * (aligned ? 1.04 : !cached ? 1.5 : fits ? (eb == 2 ? 1.15 : 1.1) : (eb == 2 ? 1.55 : eb == 4 ? 1.3 : 1.2)));
     const bool forced = env && env[0] == '1';
     int cus = 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, h->device) != hipSuccess || cus <= 0) return;
@@ -391,12 +391,17 @@ int lbm_create(const lbm_params* p, void* stream, lbm_handle** out)
         if (p->cache_policy == 0 && h->g.row_stage) h->nt = true;
     }
     {
+        // (two-colour steps write two lattices: rows sharing lines gain nothing
+        // beyond the cache, 80x320x80 183 us streaming, 194 ordinary)
         // values per node of every buffer (two of each lattice with A-B)
         const int coupled = p->coupled == LBM_COUPLED_PHASE ? 7 : p->coupled == LBM_COUPLED_MAGNETIC ? 21
                             : p->coupled == LBM_COUPLED_COLOUR ? 19 : 0;
-        const int64_t bytes = (int64_t)(p->streaming == LBM_AB ? 2 : 1) * (p->q + coupled) * h->g.N * eb;
-        h->cached = p->cache_policy == 2 || (p->cache_policy == 0 && lbm::ordinary_accesses(bytes, (int64_t)p->nx * eb));
-        if (h->cached) h->nt = false;
+        const int nbuf = p->streaming == LBM_AB ? 2 : 1;
+        const int64_t bytes = (int64_t)nbuf * (p->q + coupled) * h->g.N * eb;
+        h->cached = p->cache_policy == 2 || (p->cache_policy == 0 && lbm::ordinary_accesses(bytes, nbuf, p->coupled == LBM_COUPLED_COLOUR ? 0 : (int64_t)p->nx * eb));
+        h->alternate = p->cache_policy != 1 && lbm::alternate_planes(bytes, nbuf) &&
+                       (p->coupled == LBM_COUPLED_NONE || p->coupled == LBM_COUPLED_MAGNETIC);
+        if (h->cached || (h->alternate && p->cache_policy == 0)) h->nt = false;
         set_pair(h, h->cached, bytes <= ((int64_t)256 << 20));
     }
 
@@ -493,6 +498,7 @@ int lbm_step(lbm_handle* h, int64_t nsteps)
     if (!h) return fail(LBM_EINVAL, "NULL handle");
     if (nsteps < 0) return fail(LBM_EINVAL, "nsteps < 0");
     for (int64_t s = 0; s < nsteps; ++s) {
+        h->g.rev = h->alternate ? (int)(h->steps & 1) : 0;
         const int pat = pattern_of(h);
         const int src = h->cur;
         const int dst = h->p.streaming == LBM_AB ? 1 - h->cur : h->cur;

@@ -14,6 +14,7 @@ enum { FORCE_NONE = 0, FORCE_UNIFORM = 1, FORCE_FIELD = 2, FORCE_ROW_TABLE = 3 }
 struct Geom {
     int nx, ny, nz, nxy;
     int N;          // nodes
+    int rev = 0;    // single steps: planes last to first; the results do not depend on it
     int64_t stride; // elements between consecutive population arrays (>= N)
     int xcd_chunk = 1; // 1-D step grids: rows per XCD run (1 = launch order)
     int row_stage = 0; // periodic A-B / AA odd step with whole-row work-groups: x-moving populations via LDS
@@ -119,10 +120,23 @@ struct PairShape {
 // Larger ones with such rows: 200^3 FP32 320 / 265 (a pair of steps), FP16 255
 // / 164, FP32 AA 340 / 257; 330x150x200 FP32 282 / 219 (two steps per pass),
 // FP64 516 / 389; 208x200x200 FP16 248 / 183; with whole lines, 256x256x200
-// FP32 242 / 254, AA 333 / 361.
-inline bool ordinary_accesses(int64_t bytes, int64_t row_bytes)
+// FP32 242 / 254, AA 333 / 361.  One buffer of 24 MB is the lower end: AA FP16
+// 96^3 (34 MB) 14.6 / 12.1, A-B FP32 64^3 (2 x 20 MB) 7.5 / 8.1.
+inline bool ordinary_accesses(int64_t bytes, int buffers, int64_t row_bytes)
 {
-    return bytes >= 48000000 && (bytes <= ((int64_t)256 << 20) || row_bytes % 128 != 0);
+    return bytes >= (int64_t)24000000 * buffers && (bytes <= ((int64_t)256 << 20) || row_bytes % 128 != 0);
+}
+// Whether single steps go through the planes upwards and downwards in turn,
+// with ordinary accesses: each starts with the planes that the step before
+// took last, which the last-level cache still holds.  That pays up to about
+// three times its size in place (AA) and twice with two buffers.  Always
+// upwards, streaming / in turn, us per step: AA FP32 160^3 (311 MB) 115 / 89,
+// 192^3 196 / 160, FP16 256^3 (637 MB) 204 / 191, FP32 256^3 (1.3 GB) 419 / 433;
+// A-B FP32 144^3 (454 MB) 101 / 89, FP16 192^3 (538 MB) 96 / 97, FP64 96^3 (269
+// MB) 53 / 37; magnetic 96x128x96 (377 MB) 90 / 72, 128x160x128 (839 MB) 156 / 158.
+inline bool alternate_planes(int64_t bytes, int buffers)
+{
+    return bytes >= (int64_t)24000000 * buffers && bytes <= (buffers == 1 ? 800000000 : 480000000);
 }
 // threads of the pair kernel's work-groups (columns of a tile, halo included)
 int pair_threads_q19(int precision);

@@ -122,7 +122,7 @@ __global__ __launch_bounds__(256) void k_mhd_step(const S* __restrict__ fsrc, S*
     using R = typename Codec<S>::R;
     const int x = blockIdx.x * blockDim.x + threadIdx.x;
     const int y = blockIdx.y * blockDim.y + threadIdx.y;
-    const int z = blockIdx.z;
+    const int z = plane_z(gm);
     if (x >= gm.nx || y >= gm.ny) return;
     NodeIdx d;
     node_idx(gm, x, y, z, d);

@@ -78,7 +78,7 @@ __device__ inline void step_mlp_body(const S* src, S* dst, const Geom& g, const 
     const bool valid = xr < g.nx && yr < g.ny;
     const int x = xr < g.nx ? xr : g.nx - 1;
     const int y = yr < g.ny ? yr : g.ny - 1;
-    const int z = blockIdx.z;
+    const int z = plane_z(g);
     NodeIdx d;
     node_idx(g, x, y, z, d);
     // the force's loads next, then the populations' (ahead of them for every
