@@ -943,7 +943,7 @@ int lbm_mlp_accumulate_grad(lbm_mlp* m, lbm_handle* h, const float* target, cons
     int rc = training_checks(m, h, sigma, 1, isig);
     if (rc) return rc;
     const lbm::Geom& g = h->g;
-    const int nwb = lbm::train_waves(g), nlp = lbm::train_loss_parts(g);
+    const int nwb = lbm::train_rows(g), nlp = lbm::train_loss_parts(g);
     rc = grow((void**)&m->gbuf, m->gbuf_elems, (int64_t)2 * 19 * g.N, sizeof(float));
     if (!rc) rc = grow((void**)&m->grad_parts, m->grad_parts_n, (int64_t)nwb * LBM_MLP_NPARAM, sizeof(float));
     if (!rc) rc = grow((void**)&m->loss_parts, m->loss_parts_n, nlp, sizeof(double));
@@ -957,8 +957,8 @@ int lbm_mlp_accumulate_grad(lbm_mlp* m, lbm_handle* h, const float* target, cons
                          h->stream);
     lbm::launch_train_loss((const float*)post, g, (float)h->p.rho0, target, m->inv_sigma, m->gbuf, m->loss_parts, nullptr,
                            0.0f, h->stream);
-    lbm::launch_train_backward((const float*)state, m->gbuf, g, h->ph, m->packed, m->grad_parts, nullptr, false, nullptr,
-                               nullptr, nullptr, nullptr, 0.0f, h->stream);
+    lbm::launch_train_backward((const float*)state, m->gbuf, g, h->ph, m->packed, m->grad_parts, nullptr, nullptr, false,
+                               nullptr, nullptr, nullptr, nullptr, 0.0f, h->stream);
     lbm::launch_reduce_grad(m->grad_parts, nwb, m->grad, m->red_tmp, h->stream);
     lbm::launch_sum_partials(m->loss_parts, 1, nlp, nlp, nlp, m->loss_dev, h->stream);
     HIP_TRY(hipGetLastError());
@@ -992,11 +992,12 @@ int lbm_mlp_accumulate_rollout_grad(lbm_mlp* m, lbm_handle* h, const float* targ
     }
     const lbm::Geom& g = h->g;
     const int64_t state_elems = (int64_t)19 * g.stride;
-    const int nwb = lbm::train_waves(g), nlp = lbm::train_loss_parts(g); // nwb >= nlp
-    rc = grow((void**)&m->gbuf, m->gbuf_elems, (int64_t)2 * 19 * g.N, sizeof(float));
+    const int nwb = lbm::train_rows(g), nlp = lbm::train_loss_parts(g), ngr = lbm::train_groups(g);
+    const int npr = std::max(ngr, nlp); // loss partials per step
+    rc = grow((void**)&m->gbuf, m->gbuf_elems, (int64_t)2 * 19 * g.N + lbm::train_feat_elems(g), sizeof(float));
     if (!rc) rc = grow((void**)&m->traj, m->traj_elems, (int64_t)steps * state_elems, sizeof(float));
     if (!rc) rc = grow((void**)&m->grad_parts, m->grad_parts_n, (int64_t)nwb * LBM_MLP_NPARAM, sizeof(float));
-    if (!rc) rc = grow((void**)&m->loss_parts, m->loss_parts_n, (int64_t)steps * nwb, sizeof(double));
+    if (!rc) rc = grow((void**)&m->loss_parts, m->loss_parts_n, (int64_t)steps * npr, sizeof(double));
     if (!rc) rc = grow((void**)&m->isig_steps, m->isig_steps_n, (int64_t)steps * 10, sizeof(float));
     const bool energy = m->energy_weight > 0.0;
     if (!rc && energy) rc = grow((void**)&m->energies, m->energies_n, (int64_t)2 * steps, sizeof(double));
@@ -1035,21 +1036,22 @@ int lbm_mlp_accumulate_rollout_grad(lbm_mlp* m, lbm_handle* h, const float* targ
     // the loss after k steps
     float* A = m->gbuf;
     float* B = m->gbuf + (int64_t)19 * g.N;
+    float* feat = m->gbuf + (int64_t)2 * 19 * g.N;
     auto target_of = [&](int k) { return targets + (int64_t)(k - 1) * 10 * g.N; }; // k = 1..steps
     auto isig_of = [&](int k) { return m->isig_steps + (int64_t)(k - 1) * 10; };
-    auto parts_of = [&](int k) { return m->loss_parts + (int64_t)(k - 1) * nwb; };
+    auto parts_of = [&](int k) { return m->loss_parts + (int64_t)(k - 1) * npr; };
     auto energy_of = [&](int k) { return energy ? m->energies + 2 * (k - 1) : nullptr; };
     lbm::launch_train_loss(P(steps), g, (float)h->p.rho0, target_of(steps), isig_of(steps), A, parts_of(steps),
                            energy_of(steps), ew, h->stream);
     for (int k = steps - 1; k >= 0; --k) {
         // the partials of all steps add up in place; one reduction at the end
-        lbm::launch_train_backward(P(k), A, g, h->ph, m->packed, m->grad_parts, k > 0 ? B : dstate, k < steps - 1,
+        lbm::launch_train_backward(P(k), A, g, h->ph, m->packed, m->grad_parts, feat, k > 0 ? B : dstate, k < steps - 1,
                                    k > 0 ? target_of(k) : nullptr, k > 0 ? isig_of(k) : nullptr,
                                    k > 0 ? parts_of(k) : nullptr, k > 0 ? energy_of(k) : nullptr, ew, h->stream);
         std::swap(A, B);
     }
     lbm::launch_reduce_grad(m->grad_parts, nwb, m->grad, m->red_tmp, h->stream);
-    lbm::launch_sum_partials(m->loss_parts, steps, nwb, nwb, nlp, m->loss_steps, h->stream);
+    lbm::launch_sum_partials(m->loss_parts, steps, npr, ngr, nlp, m->loss_steps, h->stream);
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipMemcpyAsync(m->loss_steps_host, m->loss_steps, sizeof(double) * steps, hipMemcpyDeviceToHost, h->stream));
     std::vector<double> en(energy ? 2 * (size_t)steps : 0);

@@ -181,10 +181,12 @@ void launch_reduce(const double* partials, int nblocks, double* out, hipStream_t
 constexpr int MLP_PARAMS = 1737;
 void launch_step_mlp(int precision, int pattern, bool walls, bool nt, const void* src, void* dst, const Geom& g,
                      const Phys& ph, const void* net, uint32_t* fb_partials, dim3 grid, dim3 block, hipStream_t st);
-// FP64 loss partials of launch_train_loss; wavefronts (gradient and loss
-// partials) of launch_train_backward
+// FP64 loss partials of launch_train_loss; gradient and loss partials of
+// launch_train_backward
 int train_loss_parts(const Geom& g);
-int train_waves(const Geom& g);
+int train_rows(const Geom& g);
+int train_groups(const Geom& g);
+int64_t train_feat_elems(const Geom& g); // floats of launch_train_backward's feat
 // energy (device, [E, E_target]) or nullptr: adds the energy term ew ((E - E_t) / E_t)^2
 void launch_train_loss(const float* post, const Geom& g, float rho0, const float* target, const float* inv_sigma,
                        float* gbuf, double* loss_partials, const double* energy, float ew, hipStream_t st);
@@ -197,8 +199,8 @@ void launch_train_energy(const float* posts, int64_t step_stride, int steps, con
 // loss on f(t) against `target` (or nullptr) added to it; accumulate: add to
 // grad_partials instead of overwriting them
 void launch_train_backward(const float* state, const float* gbuf, const Geom& g, const Phys& ph, const void* net,
-                           float* grad_partials, float* gout, bool accumulate, const float* target, const float* inv_sigma,
-                           double* loss_partials, const double* energy, float ew, hipStream_t st);
+                           float* grad_partials, float* feat, float* gout, bool accumulate, const float* target,
+                           const float* inv_sigma, double* loss_partials, const double* energy, float ew, hipStream_t st);
 // tmp: reduce_grad_tmp_bytes() of device scratch
 size_t reduce_grad_tmp_bytes();
 void launch_reduce_grad(const float* partials, int nparts, double* grad, double* tmp, hipStream_t st);

@@ -1,6 +1,6 @@
 // Learned-rate D3Q19 step, its training kernels, and the D3Q27 -> D3Q19
 // projection that produces training data.
-#include "cm_adjoint.hpp"
+#include "dual.hpp"
 #include "lattice_kernels.hpp"
 #include "mlp_device.hpp"
 
@@ -160,10 +160,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((P == AA_OD
 // (c_i . u - |u|^2 / 2).  The term's value is formed by the host.
 // ---------------------------------------------------------------------------
 // Loss of one node with populations s (deviations): its sum of squares, and
-// dL/df_i in add_to[i] += ... (or = ..., not `accumulate`).
-__device__ inline double train_loss_node(const float s[19], int n, int N, float rho0, const float* __restrict__ target,
+// dL/df_i to put(i, value) for every i that want(i).
+template <class W, class P>
+__device__ __attribute__((always_inline)) inline double train_loss_node(const float s[19], int n, int N, float rho0, const float* __restrict__ target,
                                          const float* __restrict__ inv_sigma, const double* __restrict__ energy, float ew,
-                                         bool accumulate, float gi_out[19])
+                                         W want, P put)
 {
     // moments of f = w rho0 + s: rest part (1, 0,0,0, 1/3 x3, 0 x3) rho0
     float m[10] = {rho0, 0, 0, 0, rho0 / 3.0f, rho0 / 3.0f, rho0 / 3.0f, 0, 0, 0};
@@ -201,11 +202,12 @@ __device__ inline double train_loss_node(const float s[19], int n, int N, float 
     }
 #pragma unroll
     for (int i = 0; i < 19; ++i) {
+        if (!want(i)) continue;
         const float cx = LatD3Q19::cx(i), cy = LatD3Q19::cy(i), cz = LatD3Q19::cz(i);
         float gi = dm[0] + cx * dm[1] + cy * dm[2] + cz * dm[3] + cx * cx * dm[4] + cy * cy * dm[5] + cz * cz * dm[6] +
                    cx * cy * dm[7] + cx * cz * dm[8] + cy * cz * dm[9];
         if (energy) gi += ce * (cx * ux + cy * uy + cz * uz - u2);
-        gi_out[i] = accumulate ? gi_out[i] + gi : gi;
+        put(i, gi);
     }
     return l2;
 }
@@ -232,11 +234,10 @@ __global__ __launch_bounds__(256) void k_train_loss(const float* __restrict__ po
     if (n < g.N) {
         NodeIdx d;
         node_of(g, n, d);
-        float s[19], gi[19];
+        float s[19];
         gather<LatD3Q19, float, AB, false>(post, g.stride, d, s);
-        v = train_loss_node(s, n, g.N, rho0, target, inv_sigma, energy, ew, false, gi);
-#pragma unroll
-        for (int i = 0; i < 19; ++i) gbuf[(int64_t)i * g.N + n] = gi[i];
+        v = train_loss_node(s, n, g.N, rho0, target, inv_sigma, energy, ew, [](int) { return true; },
+                            [&](int i, float gi) { gbuf[(int64_t)i * g.N + n] = gi; });
     }
     v = wave_sum(v);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
@@ -287,28 +288,21 @@ __global__ __launch_bounds__(256) void k_train_energy(const float* __restrict__ 
     }
 }
 
-// Backward pass, one wavefront per block (64 consecutive nodes): recompute the
-// forward state from f(t), pull dL/df*_i(x) = dL/df_i(x + c_i, t+1), form
-// dL/domega_j = kbar_{10+j} (-(k_{10+j} - k_eq) - R_{10+j}/2) with
+// Backward pass, a wavefront per x row (per 64 nodes of a longer one):
+// recompute the forward state from f(t), pull dL/df*_i(x) = dL/df_i(x + c_i,
+// t+1), form dL/domega_j = kbar_{10+j} (-(k_{10+j} - k_eq) - R_{10+j}/2) with
 // kbar = S(+u)^T M^-T gbar, then back-propagate through the network.  Writes
-// this wavefront's 1737 gradient entries to grad_partials[wave].
+// the row's 1737 gradient entries to grad_partials[row].
 //
-// PROP (rollouts): also dL/df_j(x, t), written to gout[j N + x]: the
-// collision's adjoint (cm_adjoint.hpp), at fixed rates and through the
-// features, whose dL/dx the network's backward pass gives (ReLU masks, W1^T,
-// the input scales).  Nodes that fall back use rates 1 that do not depend on
-// the state.  With `target` (every step but the first) the loss on f(t)
-// itself, whose populations the wavefront has gathered, is added to gout, and
-// its sum of squares goes to loss_partials[wave].
+// PROP (rollouts): also the rates (1 of nodes that fall back) and dL/dx of the
+// features (ReLU masks, W1^T, the input scales), feat[j N + x] for
+// k_train_dstate.
 //
-// What bounds it: latency; a 32^3 step is 512 wavefronts, two per compute
-// unit, each a chain of loads, products through LDS and two collisions'
-// arithmetic.  32^3, us per step: 47 with one directional derivative of the
-// collision per population and a wavefront per row of 32 nodes; 18 with the
-// collision's adjoint and 64 consecutive nodes; 14.6 with all loads (the
-// network, the old gradient partials) issued first; 12.8 with dL/dx as a
-// product.  The loss on f(t) and the energies were three more launches per
-// step (15 us).
+// What bounds both: latency and, in k_train_dstate, issue; a 32^3 step is 1024
+// rows.  32^3, us per step, both together: 47 with all derivatives in the row's
+// own wavefront, 44 with one wavefront per derivative of 64 nodes.  The loss on
+// f(t) and the energies were three more
+// launches per step (15 us).
 struct TrainLoss {
     const float* target;    // NULL: no loss on f(t)
     const float* inv_sigma;
@@ -316,22 +310,22 @@ struct TrainLoss {
     float ew;
     double* partials;
 };
+constexpr int TRAIN_FEAT = MLP_NOUT + MLP_NIN;
 template <bool PROP>
 __global__ __launch_bounds__(64) void k_train_backward(const float* __restrict__ state, const float* __restrict__ gbuf,
                                                        Geom g, Phys ph, const MlpPacked* __restrict__ net,
-                                                       float* __restrict__ grad_partials, float* __restrict__ gout,
-                                                       int accumulate, TrainLoss tl)
+                                                       float* __restrict__ grad_partials, float* __restrict__ feat,
+                                                       int accumulate)
 {
     const float rho0 = (float)ph.rho0;
     __shared__ MlpTrain snet;
     __shared__ uint16_t tx[MLP_TILE], th1[MLP_TILE], th2[MLP_TILE], tdz[MLP_TILE], tdh[MLP_TILE];
-    __shared__ float tz[64 * MLP_NIN];
+    __shared__ float tz[64 * MLP_NOUT];
     const int l = threadIdx.x;
-    const int nr = blockIdx.x * 64 + l;
-    const bool valid = nr < g.N;
-    const int n0 = valid ? nr : g.N - 1;
+    const int xr = blockIdx.x * 64 + l;
+    const bool valid = xr < g.nx;
     NodeIdx d;
-    node_of(g, n0, d);
+    node_idx(g, valid ? xr : g.nx - 1, blockIdx.y, blockIdx.z, d);
     float s[19], gbar[19];
     gather<LatD3Q19, float, AB, false>(state, g.stride, d, s);
     // adjoint of the streaming
@@ -344,7 +338,7 @@ __global__ __launch_bounds__(64) void k_train_backward(const float* __restrict__
     uint4 nc[(NCHUNK + 63) / 64];
 #pragma unroll
     for (int c = 0; c < (NCHUNK + 63) / 64; ++c) nc[c] = reinterpret_cast<const uint4*>(&net->train)[min(c * 64 + l, NCHUNK - 1)];
-    float* gp = grad_partials + (int64_t)blockIdx.x * MLP_NPARAM;
+    float* gp = grad_partials + (int64_t)(blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z)) * MLP_NPARAM;
     const int col = l & 31, row4 = 4 * (l >> 5); // accumulator register r: row 8 (r / 4) + row4 + r % 4, column col
     float g1[16], g2[16], g3[5], gb[3];
     {
@@ -370,9 +364,8 @@ __global__ __launch_bounds__(64) void k_train_backward(const float* __restrict__
     mlp_features(st, xin);
     mlp_forward_wave(snet, tx, th1, th2, tz, xin, zout);
     const bool fb = mlp_rates(zout, rates);
-    RawMoments<float> qb, kb;
-    pops_from_raw_T(gbar, qb);
-    kb = qb;
+    RawMoments<float> kb;
+    pops_from_raw_T(gbar, kb);
     shift_all_T(kb, st.ux, st.uy, st.uz);
     const RawMoments<float>& n = st.n;
     // no force in training: R = 0 on rows 10..18
@@ -447,31 +440,79 @@ __global__ __launch_bounds__(64) void k_train_backward(const float* __restrict__
         if (l < 32) gp[MLP_OFF_B1 + l] = gb[0] + sb;
     }
     if constexpr (PROP) {
-        // xbar = (dh1 W1) * inv_scale, back to the node's lane through LDS
+        if (!valid) return;
+        const int n0 = nb(d, 0, 0, 0);
+        // xbar = (W1^T dh1) * inv_scale: dh1 of this lane's node is row l of tdz
         float xbar[MLP_NIN];
 #pragma unroll
-        for (int rb = 0; rb < 2; ++rb) {
-            const f32x16_t acc = mfma_xwT<32>(tdz, rb, snet.w1t, 32);
-            if (col < MLP_NIN)
+        for (int i = 0; i < MLP_NIN; ++i) xbar[i] = 0.0f;
+#pragma unroll 8
+        for (int o = 0; o < 32; ++o) {
+            const float dh = bf16_to_f32(tdz[l * MLP_LDS_STRIDE + o]);
+            const uint4 *wr = reinterpret_cast<const uint4*>(snet.w1 + o * 16), w0 = wr[0], w1 = wr[1];
+            const uint32_t ww[6] = {w0.x, w0.y, w0.z, w0.w, w1.x, w1.y};
 #pragma unroll
-                for (int r = 0; r < 16; ++r) tz[acc_row(rb, r) * MLP_NIN + col] = acc[r];
+            for (int i = 0; i < MLP_NIN; ++i) xbar[i] += dh * bf16_to_f32((uint16_t)(ww[i / 2] >> (16 * (i & 1))));
         }
-        __syncthreads();
 #pragma unroll
-        for (int i = 0; i < MLP_NIN; ++i) xbar[i] = tz[l * MLP_NIN + i] * snet.inv_scale[i];
-        Rates<float> rt = rates_of<float>(ph);
+        for (int j = 0; j < MLP_NOUT; ++j) feat[(int64_t)j * g.N + n0] = rates[j];
 #pragma unroll
-        for (int j = 0; j < MLP_NOUT; ++j) rt.omega_hi[j] = rates[j];
-        collide_adjoint(st, rho0, rt, qb, kb, xbar, gbar);
-        if (tl.target) {
-            double l2 = train_loss_node(s, n0, g.N, rho0, tl.target, tl.inv_sigma, tl.energy, tl.ew, true, gbar);
-            l2 = wave_sum(valid ? l2 : 0.0);
-            if (l == 0) tl.partials[blockIdx.x] = l2 / (double)g.N;
-        }
-        if (valid)
-#pragma unroll
-            for (int j = 0; j < 19; ++j) gout[(int64_t)j * g.N + n0] = gbar[j];
+        for (int i = 0; i < MLP_NIN; ++i) feat[(int64_t)(MLP_NOUT + i) * g.N + n0] = xbar[i] * snet.inv_scale[i];
     }
+}
+
+// dL/df_j(x, t), written to gout[j N + x]: one forward derivative of the
+// collision along population j = blockIdx.y (dual.hpp), at fixed rates and
+// through the features, with the rates and dL/dfeatures of k_train_backward.
+// With `target` (every step but the first) the loss on f(t) itself is added,
+// and its sum of squares goes to loss_partials[64-node block].
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_train_dstate(
+    const float* __restrict__ state, const float* __restrict__ gbuf, Geom g, Phys ph, const float* __restrict__ feat,
+    float* __restrict__ gout, TrainLoss tl)
+{
+    const float rho0 = (float)ph.rho0;
+    const int nr = blockIdx.x * 64 + threadIdx.x, j = blockIdx.y;
+    const bool valid = nr < g.N;
+    const int n0 = valid ? nr : g.N - 1;
+    NodeIdx d;
+    node_of(g, n0, d);
+    float s[19], gbar[19];
+    gather<LatD3Q19, float, AB, false>(state, g.stride, d, s);
+#pragma unroll
+    for (int i = 0; i < 19; ++i)
+        gbar[i] = gbuf[(int64_t)i * g.N + nb(d, LatD3Q19::cx(i), LatD3Q19::cy(i), LatD3Q19::cz(i))];
+    Rates<Dual> rt = rates_of<Dual>(ph);
+    float xbar[MLP_NIN];
+#pragma unroll
+    for (int k = 0; k < MLP_NOUT; ++k) rt.omega_hi[k] = Dual(feat[(int64_t)k * g.N + n0], 0.0f);
+#pragma unroll
+    for (int k = 0; k < MLP_NIN; ++k) xbar[k] = feat[(int64_t)(MLP_NOUT + k) * g.N + n0];
+    float loss = 0.0f;
+    if (tl.target) {
+        double l2 = train_loss_node(s, n0, g.N, rho0, tl.target, tl.inv_sigma, tl.energy, tl.ew,
+                                    [&](int i) { return i == j; }, [&](int, float gi) { loss = gi; });
+        if (j == 0) {
+            l2 = wave_sum(valid ? l2 : 0.0);
+            if (threadIdx.x == 0) tl.partials[blockIdx.x] = l2 / (double)g.N;
+        }
+    }
+    Dual sd[19];
+#pragma unroll
+    for (int i = 0; i < 19; ++i) sd[i] = Dual(s[i], i == j ? 1.0f : 0.0f);
+    CMState<Dual> sdt;
+    pre_collide<Dual, true>(sd, Dual(rho0, 0.0f), Dual(0.0), Dual(0.0), Dual(0.0), sdt);
+    Dual xd[MLP_NIN];
+    mlp_features(sdt, xd);
+    RawMoments<Dual> pd;
+    relax<Dual, true>(sdt, rt, pd);
+    post_collide_increment(sdt, pd, sd);
+    float acc = 0.0f;
+#pragma unroll
+    for (int i = 0; i < 19; ++i) acc += gbar[i] * sd[i].d;
+#pragma unroll
+    for (int k = 0; k < MLP_NIN; ++k) acc += xbar[k] * xd[k].d;
+    if (tl.target) acc = acc + loss;
+    if (valid) gout[(int64_t)j * g.N + n0] = acc;
 }
 
 // grad[p] += sum over the per-wavefront partials, in FP64 and a fixed order
@@ -749,7 +790,10 @@ void launch_step_mlp(int precision, int pattern, bool walls, bool nt, const void
 }
 
 int train_loss_parts(const Geom& g) { return (g.N + 255) / 256; }
-int train_waves(const Geom& g) { return (g.N + 63) / 64; }
+// gradient partials (wavefronts of k_train_backward), loss partials (64-node blocks of k_train_dstate)
+int train_rows(const Geom& g) { return (g.nx + 63) / 64 * g.ny * g.nz; }
+int train_groups(const Geom& g) { return (g.N + 63) / 64; }
+int64_t train_feat_elems(const Geom& g) { return (int64_t)TRAIN_FEAT * g.N; }
 
 void launch_train_loss(const float* post, const Geom& g, float rho0, const float* target, const float* inv_sigma,
                        float* gbuf, double* loss_partials, const double* energy, float ew, hipStream_t st)
@@ -766,17 +810,19 @@ void launch_train_energy(const float* posts, int64_t step_stride, int steps, con
 }
 
 void launch_train_backward(const float* state, const float* gbuf, const Geom& g, const Phys& ph, const void* net,
-                           float* grad_partials, float* gout, bool accumulate, const float* target, const float* inv_sigma,
-                           double* loss_partials, const double* energy, float ew, hipStream_t st)
+                           float* grad_partials, float* feat, float* gout, bool accumulate, const float* target,
+                           const float* inv_sigma, double* loss_partials, const double* energy, float ew, hipStream_t st)
 {
-    const TrainLoss tl{target, inv_sigma, energy, ew, loss_partials};
-    const dim3 grid(train_waves(g));
-    if (gout)
-        hipLaunchKernelGGL(k_train_backward<true>, grid, dim3(64), 0, st, state, gbuf, g, ph, (const MlpPacked*)net,
-                           grad_partials, gout, (int)accumulate, tl);
-    else
+    const dim3 grid((g.nx + 63) / 64, g.ny, g.nz);
+    if (!gout) {
         hipLaunchKernelGGL(k_train_backward<false>, grid, dim3(64), 0, st, state, gbuf, g, ph, (const MlpPacked*)net,
-                           grad_partials, gout, (int)accumulate, tl);
+                           grad_partials, nullptr, (int)accumulate);
+        return;
+    }
+    hipLaunchKernelGGL(k_train_backward<true>, grid, dim3(64), 0, st, state, gbuf, g, ph, (const MlpPacked*)net,
+                       grad_partials, feat, (int)accumulate);
+    hipLaunchKernelGGL(k_train_dstate, dim3(train_groups(g), 19), dim3(64), 0, st, state, gbuf, g, ph, feat, gout,
+                       TrainLoss{target, inv_sigma, energy, ew, loss_partials});
 }
 
 size_t reduce_grad_tmp_bytes() { return sizeof(double) * MLP_RED_SLICES * MLP_NPARAM; }
