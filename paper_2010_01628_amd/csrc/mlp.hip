@@ -300,9 +300,9 @@ __global__ __launch_bounds__(256) void k_train_energy(const float* __restrict__ 
 //
 // What bounds both: latency and, in k_train_dstate, issue; a 32^3 step is 1024
 // rows.  32^3, us per step, both together: 47 with all derivatives in the row's
-// own wavefront, 44 with one wavefront per derivative of 64 nodes.  The loss on
-// f(t) and the energies were three more
-// launches per step (15 us).
+// own wavefront, 44 with one wavefront per derivative of 64 nodes, 35 with
+// three derivatives to a wavefront.  The loss on f(t) and the energies were
+// three more launches per step (15 us).
 struct TrainLoss {
     const float* target;    // NULL: no loss on f(t)
     const float* inv_sigma;
@@ -461,17 +461,22 @@ __global__ __launch_bounds__(64) void k_train_backward(const float* __restrict__
     }
 }
 
-// dL/df_j(x, t), written to gout[j N + x]: one forward derivative of the
-// collision along population j = blockIdx.y (dual.hpp), at fixed rates and
+// dL/df_j(x, t), written to gout[j N + x]: forward derivatives of the collision
+// along TRAIN_K populations j from TRAIN_K blockIdx.y (dual.hpp), at fixed rates and
 // through the features, with the rates and dL/dfeatures of k_train_backward.
 // With `target` (every step but the first) the loss on f(t) itself is added,
 // and its sum of squares goes to loss_partials[64-node block].
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_train_dstate(
+// Three populations to a wavefront share the collision's values (3085 VALU
+// instructions, 1832 for one); 32^3, 32 steps of a rollout, us: one 1748, two
+// 1527, three 1447, four 1630 (spills).
+constexpr int TRAIN_K = 3;
+__global__ __launch_bounds__(64) void k_train_dstate(
     const float* __restrict__ state, const float* __restrict__ gbuf, Geom g, Phys ph, const float* __restrict__ feat,
     float* __restrict__ gout, TrainLoss tl)
 {
     const float rho0 = (float)ph.rho0;
-    const int nr = blockIdx.x * 64 + threadIdx.x, j = blockIdx.y;
+    const int nr = blockIdx.x * 64 + threadIdx.x, j0 = TRAIN_K * blockIdx.y;
+    typedef Dual<TRAIN_K> D;
     const bool valid = nr < g.N;
     const int n0 = valid ? nr : g.N - 1;
     NodeIdx d;
@@ -481,38 +486,55 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_
 #pragma unroll
     for (int i = 0; i < 19; ++i)
         gbar[i] = gbuf[(int64_t)i * g.N + nb(d, LatD3Q19::cx(i), LatD3Q19::cy(i), LatD3Q19::cz(i))];
-    Rates<Dual> rt = rates_of<Dual>(ph);
+    auto constant = [](float c) {
+        D r(0.0);
+        r.v = c;
+        return r;
+    };
+    Rates<D> rt = rates_of<D>(ph);
     float xbar[MLP_NIN];
 #pragma unroll
-    for (int k = 0; k < MLP_NOUT; ++k) rt.omega_hi[k] = Dual(feat[(int64_t)k * g.N + n0], 0.0f);
+    for (int k = 0; k < MLP_NOUT; ++k) rt.omega_hi[k] = constant(feat[(int64_t)k * g.N + n0]);
 #pragma unroll
     for (int k = 0; k < MLP_NIN; ++k) xbar[k] = feat[(int64_t)(MLP_NOUT + k) * g.N + n0];
-    float loss = 0.0f;
+    float loss[TRAIN_K] = {};
     if (tl.target) {
         double l2 = train_loss_node(s, n0, g.N, rho0, tl.target, tl.inv_sigma, tl.energy, tl.ew,
-                                    [&](int i) { return i == j; }, [&](int, float gi) { loss = gi; });
-        if (j == 0) {
+                                    [&](int i) { return i >= j0 && i < j0 + TRAIN_K; }, [&](int i, float gi) {
+#pragma unroll
+                                        for (int k = 0; k < TRAIN_K; ++k)
+                                            if (i == j0 + k) loss[k] = gi;
+                                    });
+        if (j0 == 0) {
             l2 = wave_sum(valid ? l2 : 0.0);
             if (threadIdx.x == 0) tl.partials[blockIdx.x] = l2 / (double)g.N;
         }
     }
-    Dual sd[19];
+    D sd[19];
 #pragma unroll
-    for (int i = 0; i < 19; ++i) sd[i] = Dual(s[i], i == j ? 1.0f : 0.0f);
-    CMState<Dual> sdt;
-    pre_collide<Dual, true>(sd, Dual(rho0, 0.0f), Dual(0.0), Dual(0.0), Dual(0.0), sdt);
-    Dual xd[MLP_NIN];
+    for (int i = 0; i < 19; ++i) {
+        sd[i].v = s[i];
+#pragma unroll
+        for (int k = 0; k < TRAIN_K; ++k) sd[i].d[k] = i == j0 + k ? 1.0f : 0.0f;
+    }
+    CMState<D> sdt;
+    pre_collide<D, true>(sd, constant(rho0), D(0.0), D(0.0), D(0.0), sdt);
+    D xd[MLP_NIN];
     mlp_features(sdt, xd);
-    RawMoments<Dual> pd;
-    relax<Dual, true>(sdt, rt, pd);
+    RawMoments<D> pd;
+    relax<D, true>(sdt, rt, pd);
     post_collide_increment(sdt, pd, sd);
-    float acc = 0.0f;
 #pragma unroll
-    for (int i = 0; i < 19; ++i) acc += gbar[i] * sd[i].d;
+    for (int k = 0; k < TRAIN_K; ++k) {
+        if (j0 + k >= 19) break;
+        float acc = 0.0f;
 #pragma unroll
-    for (int k = 0; k < MLP_NIN; ++k) acc += xbar[k] * xd[k].d;
-    if (tl.target) acc = acc + loss;
-    if (valid) gout[(int64_t)j * g.N + n0] = acc;
+        for (int i = 0; i < 19; ++i) acc += gbar[i] * sd[i].d[k];
+#pragma unroll
+        for (int i = 0; i < MLP_NIN; ++i) acc += xbar[i] * xd[i].d[k];
+        if (tl.target) acc = acc + loss[k];
+        if (valid) gout[(int64_t)(j0 + k) * g.N + n0] = acc;
+    }
 }
 
 // grad[p] += sum over the per-wavefront partials, in FP64 and a fixed order
@@ -821,7 +843,7 @@ void launch_train_backward(const float* state, const float* gbuf, const Geom& g,
     }
     hipLaunchKernelGGL(k_train_backward<true>, grid, dim3(64), 0, st, state, gbuf, g, ph, (const MlpPacked*)net,
                        grad_partials, feat, (int)accumulate);
-    hipLaunchKernelGGL(k_train_dstate, dim3(train_groups(g), 19), dim3(64), 0, st, state, gbuf, g, ph, feat, gout,
+    hipLaunchKernelGGL(k_train_dstate, dim3(train_groups(g), (19 + TRAIN_K - 1) / TRAIN_K), dim3(64), 0, st, state, gbuf, g, ph, feat, gout,
                        TrainLoss{target, inv_sigma, energy, ew, loss_partials});
 }
 
