@@ -399,7 +399,7 @@ int lbm_create(const lbm_params* p, void* stream, lbm_handle** out)
         const int nbuf = p->streaming == LBM_AB ? 2 : 1;
         const int64_t bytes = (int64_t)nbuf * (p->q + coupled) * h->g.N * eb;
         h->cached = p->cache_policy == 2 || (p->cache_policy == 0 && lbm::ordinary_accesses(bytes, nbuf, p->coupled == LBM_COUPLED_COLOUR ? 0 : (int64_t)p->nx * eb));
-        h->alternate = p->cache_policy != 1 && lbm::alternate_planes(bytes, nbuf) &&
+        h->alternate = p->cache_policy != 1 && lbm::alternate_planes(bytes, nbuf, eb) &&
                        (p->coupled == LBM_COUPLED_NONE || p->coupled == LBM_COUPLED_MAGNETIC);
         if (h->cached || (h->alternate && p->cache_policy == 0)) h->nt = false;
         set_pair(h, h->cached, bytes <= ((int64_t)256 << 20));
