@@ -224,6 +224,7 @@ typedef struct lbm_handle lbm_handle;
  * needed in normal use):
  *   LBM_OFF32=0         64-bit population addresses even where every array is
  *                       below 4 GiB (the path of larger lattices);
+ *   LBM_TWO_STEP=0/1    single steps only / two steps per pass wherever possible;
  *   LBM_ROW_STAGING=0/1 no staging of the x-moving populations / staging
  *                       wherever it is possible, overriding the default and
  *                       lbm_tune;
@@ -257,7 +258,9 @@ int lbm_create(const lbm_params *p, void *stream, lbm_handle **out);
  * device).  Resets the step counter to 0. */
 int lbm_init(lbm_handle *h, const double *rho, const double *u, int on_device);
 
-/* Advance nsteps >= 0 time steps.  Returns LBM_EUNSTABLE at the first failed
+/* Advance nsteps >= 0 time steps.  A-B lattices without coupling or network
+ * may take two steps per pass over memory (nsteps >= 2; the same bits as
+ * single steps).  Returns LBM_EUNSTABLE at the first failed
  * stability check (state left readable, step counter at the failed check). */
 int lbm_step(lbm_handle *h, int64_t nsteps);
 
