@@ -260,7 +260,9 @@ int lbm_init(lbm_handle *h, const double *rho, const double *u, int on_device);
 
 /* Advance nsteps >= 0 time steps.  A-B lattices without coupling or network
  * may take two steps per pass over memory (nsteps >= 2; the same bits as
- * single steps).  Returns LBM_EUNSTABLE at the first failed
+ * single steps).  Recorded into a HIP graph, a call of an even number of steps
+ * can be replayed: the populations are back in the buffer they started from.
+ * Returns LBM_EUNSTABLE at the first failed
  * stability check (state left readable, step counter at the failed check). */
 int lbm_step(lbm_handle *h, int64_t nsteps);
 

@@ -419,11 +419,13 @@ int lbm_ensemble_step(lbm_ensemble* e, int64_t nsteps)
     const int per = pairs(e) ? 2 : 1; // steps per launch
     chunk = chunk / (2 * per) * (2 * per);
     int64_t left = nsteps;
+    int64_t npairs = per == 2 ? lbm::pairs_in(nsteps, e->stream) : 0; // passes of two steps left
     auto advance = [&]() {
-        if (per == 2 && left >= 2) {
+        if (npairs > 0 && left >= 2) {
             launch_pair(e);
             e->steps += 2;
             left -= 2;
+            npairs--;
         } else {
             launch_one(e);
             e->steps++;
@@ -441,6 +443,7 @@ int lbm_ensemble_step(lbm_ensemble* e, int64_t nsteps)
             EHIP(hipGraphLaunch(e->exec, e->stream));
             e->steps += chunk;
             left -= chunk;
+            npairs -= chunk / 2;
         }
     }
     while (left > 0) advance();

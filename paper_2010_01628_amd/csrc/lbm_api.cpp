@@ -497,6 +497,7 @@ int lbm_step(lbm_handle* h, int64_t nsteps)
 {
     if (!h) return fail(LBM_EINVAL, "NULL handle");
     if (nsteps < 0) return fail(LBM_EINVAL, "nsteps < 0");
+    int64_t pairs = h->pair_ok ? lbm::pairs_in(nsteps, h->stream) : 0; // passes of two steps left
     for (int64_t s = 0; s < nsteps; ++s) {
         h->g.rev = h->alternate ? (int)(h->steps & 1) : 0;
         const int pat = pattern_of(h);
@@ -520,7 +521,7 @@ int lbm_step(lbm_handle* h, int64_t nsteps)
         if (h->mlp)
             lbm::launch_step_mlp(h->p.precision, pat, h->walls, h->nt, h->buf[src], h->buf[dst], h->g, h->ph,
                                  h->mlp->packed, h->fb_partials, h->grid, h->block, h->stream);
-        else if (h->pair_ok && s + 1 < nsteps && !(h->p.check_every > 0 && (h->steps + 1) % h->p.check_every == 0)) {
+        else if (pairs > 0 && s + 1 < nsteps && !(h->p.check_every > 0 && (h->steps + 1) % h->p.check_every == 0)) {
             // two steps in one pass, unless a stability check falls between them
             uint32_t key2 = 0;
             if (h->kprec == lbm::PREC_BF16SR) {
@@ -533,6 +534,7 @@ int lbm_step(lbm_handle* h, int64_t nsteps)
                              h->buf[dst], h->g, h->ph, sh, key2, h->stream);
             h->steps++;
             s++;
+            pairs--;
         } else {
             if (h->kprec == lbm::PREC_BF16SR) h->ph.sr_key = step_key(h->p.seed, h->steps);
             lbm::launch_step(h->p.q, h->p.moments == LBM_RAW_MOMENTS, h->kprec, pat, h->walls, h->general, h->nt,

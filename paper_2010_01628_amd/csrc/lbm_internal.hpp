@@ -141,6 +141,18 @@ inline bool alternate_planes(int64_t bytes, int buffers, int elem_bytes)
     if (buffers == 1) return bytes >= 24000000 && bytes <= 800000000;
     return elem_bytes >= 4 && bytes > ((int64_t)256 << 20) && bytes <= 480000000;
 }
+// Passes of two steps that `nsteps` steps may take on this stream.  A pass
+// changes buffers once for its two steps, so a call that is recorded into a
+// graph takes an even number of them: it then leaves the populations in the
+// buffer that single steps leave them in, and a graph of an even number of
+// steps can be replayed.
+inline int64_t pairs_in(int64_t nsteps, hipStream_t st)
+{
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    // (the null stream cannot be recorded)
+    if (nsteps >= 2 && st && hipStreamIsCapturing(st, &status) != hipSuccess) (void)hipGetLastError();
+    return status == hipStreamCaptureStatusActive ? nsteps / 4 * 2 : nsteps / 2;
+}
 // threads of the pair kernel's work-groups (columns of a tile, halo included)
 int pair_threads_q19(int precision);
 int pair_threads_q27(int precision);

@@ -1,0 +1,107 @@
+"""Which kernels the entry points launch, on which buffers and with how much
+device memory, on the CPU: a child process loads the library over a HIP
+runtime that records launches instead of running them (hip_recorder.cpp)."""
+import json
+import os
+import subprocess
+import sys
+import textwrap
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HERE = os.path.dirname(os.path.abspath(__file__))
+STREAM = 0x1000  # any non-null stream
+
+PREAMBLE = """
+import ctypes, json, sys, types
+import numpy as np
+rec = ctypes.CDLL({shim!r}, mode=ctypes.RTLD_GLOBAL)
+rec.rec_name.restype = ctypes.c_char_p
+rec.rec_arg.restype = ctypes.c_void_p
+rec.rec_threads.restype = rec.rec_live_bytes.restype = rec.rec_peak_bytes.restype = ctypes.c_int64
+sys.modules["torch"] = types.ModuleType("torch")  # its HIP runtime must not be the one that is bound
+from paper_2010_01628_amd import lbm as L
+L.lib()
+STREAM = {stream}
+
+
+def lattice(nx, ny, nz, **kw):
+    return L.lbm_create(L.make_params(nx, ny, nz, **kw), STREAM)
+
+
+def launched():
+    # (kernel, its first two arguments) since the last call
+    out = [(rec.rec_name(i).decode(), rec.rec_arg(i, 0), rec.rec_arg(i, 1)) for i in range(rec.rec_count())]
+    rec.rec_clear()
+    return out
+
+
+def kinds():
+    # what each launch since the last call is
+    return ["block" if "k_step_pair_block" in n else "sweep" if "k_step_pair" in n or "k_ens_pair" in n
+            else "single" if "k_step" in n or "k_ens_step" in n else "other" for n, _, _ in launched()]
+"""
+
+
+@pytest.fixture(scope="module")
+def recorder(tmp_path_factory):
+    so = tmp_path_factory.mktemp("recorder") / "librecorder.so"
+    subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-w", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                    "-o", str(so), os.path.join(HERE, "hip_recorder.cpp")], check=True)
+
+    def run(code, **env):
+        full = {k: v for k, v in os.environ.items() if not k.startswith("LBM_")}
+        full.update(env)
+        body = PREAMBLE.format(shim=str(so), stream=STREAM) + textwrap.dedent(code)
+        r = subprocess.run([sys.executable, "-c", body], cwd=ROOT, env=full, capture_output=True, text=True, timeout=120)
+        assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-3000:]
+        return json.loads(r.stdout.splitlines()[-1])
+
+    return run
+
+
+def test_recorder_sees_the_default_paths(recorder):
+    """Small A-B lattices take blocks, large ones sweeps, two steps to a
+    launch; an odd step, AA and LBM_TWO_STEP=0 single steps."""
+    code = """
+    out = []
+    for size, kw, n in (((64, 20, 9), {}, 6), ((64, 20, 9), {}, 7), ((200, 101, 75), {}, 5), ((64, 20, 9), dict(streaming="aa"), 3)):
+        h = lattice(*size, **kw)
+        launched()
+        L.lbm_step(h, n)
+        out.append(kinds())
+        L.lbm_destroy(h)
+    print(json.dumps(out))
+    """
+    assert recorder(code) == [["block"] * 3, ["block"] * 3 + ["single"], ["sweep"] * 2 + ["single"], ["single"] * 3]
+    assert recorder(code, LBM_TWO_STEP="0") == [["single"] * n for n in (6, 7, 5, 3)]
+
+
+@pytest.mark.parametrize("steps", [1, 2, 3, 4, 6, 7, 10, 13])
+def test_captured_steps_keep_the_buffer_parity(recorder, steps):
+    """Recorded into a graph, lbm_step(n) and lbm_ensemble_step(n) leave the
+    populations in the buffer that n single steps leave them in: a graph of an
+    even number of steps can be replayed.  (A pass of two steps changes
+    buffers once.)"""
+    got = recorder(f"""
+    n = {steps}
+    out = []
+    h = lattice(64, 20, 9)
+    e = L.lbm_ensemble_create([(32, 1.5)] * 64, 19, L.LBM_FP64, STREAM)
+    for step, obj in ((L.lbm_step, h), (L.lib().lbm_ensemble_step, e)):
+        rec.rec_set_capturing(1)
+        launched()
+        step(obj, n)
+        ls = launched()
+        assert all(a == b for (_, _, a), (_, b, _) in zip(ls, ls[1:]))  # each launch reads what the one before wrote
+        out.append([ls[0][1] == ls[-1][2], len(ls)])
+        rec.rec_set_capturing(0)
+        step(obj, 4)
+        out[-1].append(kinds())
+    print(json.dumps(out))
+    """)
+    for back, launches, eager in got:
+        assert back == (steps % 2 == 0)
+        assert launches < steps or steps < 4  # pairs are still taken
+        assert eager in (["block"] * 2, ["sweep"] * 2)
