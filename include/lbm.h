@@ -224,7 +224,11 @@ typedef struct lbm_handle lbm_handle;
  * needed in normal use):
  *   LBM_OFF32=0         64-bit population addresses even where every array is
  *                       below 4 GiB (the path of larger lattices);
- *   LBM_TWO_STEP=0/1    single steps only / two steps per pass wherever possible;
+ *   LBM_TWO_STEP=0/1    single steps only / two steps per pass wherever possible
+ *                       (default: where they are estimated faster, and single
+ *                       steps where LBM_OFF32=0, LBM_ROW_STAGING,
+ *                       LBM_XCD_CHUNK or LBM_WAVES_PER_SIMD, which choose
+ *                       among launches of the single step, is set);
  *   LBM_ROW_STAGING=0/1 no staging of the x-moving populations / staging
  *                       wherever it is possible, overriding the default and
  *                       lbm_tune;

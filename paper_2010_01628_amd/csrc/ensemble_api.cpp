@@ -106,11 +106,11 @@ void launch_pair(lbm_ensemble* e)
 // 5.55 TB/s, are estimated faster.  Measured, us per step, single / pair: 64
 // boxes of 48, 64 and 96 (31 M nodes) D3Q19 FP32 864 / 608, FP64 1824 / 1203,
 // D3Q27 FP32 1279 / 828; four boxes of 32 to 96 D3Q19 FP32 38.9 / 43.3
-// (single), FP64 78.7 / 65.2.  LBM_TWO_STEP=0 and =1 as for the lattice.
+// (single), FP64 78.7 / 65.2.  LBM_TWO_STEP as for the lattice.
 std::vector<lbm::EnsPairItem> pair_list(const lbm_ensemble* e, int cus)
 {
-    const char* env = std::getenv("LBM_TWO_STEP");
-    if (env && env[0] == '0') return {};
+    const int choice = lbm::two_step_choice();
+    if (choice == 0) return {};
     const int prec = e->precision == LBM_FP64 ? lbm::PREC_FP64 : lbm::PREC_FP32;
     const int threads = e->q == 27 ? lbm::pair_threads_q27(prec) : lbm::pair_threads_q19(prec);
     std::vector<lbm::PairShape> tile(e->nboxes);
@@ -138,7 +138,7 @@ std::vector<lbm::EnsPairItem> pair_list(const lbm_ensemble* e, int cus)
         }
     }
     const double single_us = std::max(4.0, 2e-6 * e->q * e->eb * (double)e->nodes / (e->nt ? 5.55 : 6.1));
-    if (!(env && env[0] == '1') && best_us > 0.95 * 2 * single_us) return {};
+    if (choice != 1 && best_us > 0.95 * 2 * single_us) return {};
     struct Run {
         int box, z0, len;
         double cost;

@@ -220,21 +220,20 @@ int64_t pad_stride(int64_t N, int eb)
 // 79 / 63, with walls 78 / 70, FP16 49 / 61 (single); FP32 100^3 56 / 44,
 // 128x128x96 73 / 58, 72^3 26 / 24 (single); FP64 80^3 51 / 42, 91^3 78 / 59;
 // D3Q27 96^3 FP32 62 / 61, 64^3 22 / 30 (single).
-// LBM_TWO_STEP=0 keeps single steps, =1 takes sweeps wherever they are
-// possible.  Lattices small enough for one work-group per compute unit take
-// blocks instead.
+// LBM_TWO_STEP=1 takes sweeps wherever they are possible.  Lattices small
+// enough for one work-group per compute unit take blocks instead.
 void set_pair(lbm_handle* h, bool cached, bool fits)
 {
     h->pair_ok = false;
     if (h->p.streaming != LBM_AB || h->p.coupled != LBM_COUPLED_NONE) return;
     if ((int64_t)h->g.nxy * 8 >= ((int64_t)1 << 31)) return; // 32-bit offsets within a plane
-    const char* env = std::getenv("LBM_TWO_STEP");
-    if (env && env[0] == '0') return;
+    const int choice = lbm::two_step_choice();
+    if (choice == 0) return;
     const int eb = elem_bytes(h->p.precision);
     const double traffic_us = 2e-6 * h->p.q * eb * (double)h->g.N / 6.1;
     const bool aligned = (int64_t)h->g.nx * eb % 128 == 0;
     const double single_us = std::max(4.0, traffic_us * (aligned ? 1.04 : !cached ? 1.5 : fits ? (eb == 2 ? 1.15 : 1.1) : (eb == 2 ? 1.55 : eb == 4 ? 1.3 : 1.2)));
-    const bool forced = env && env[0] == '1';
+    const bool forced = choice == 1;
     int cus = 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, h->device) != hipSuccess || cus <= 0) return;
     if (!forced) {

@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <cstdlib>
+
 namespace lbm {
 
 // kernel storage types; PREC_BF16SR: BF16 with stochastic rounding (plain
@@ -140,6 +142,17 @@ inline bool alternate_planes(int64_t bytes, int buffers, int elem_bytes)
 {
     if (buffers == 1) return bytes >= 24000000 && bytes <= 800000000;
     return elem_bytes >= 4 && bytes > ((int64_t)256 << 20) && bytes <= 480000000;
+}
+// LBM_TWO_STEP: 0 keeps single steps, 1 takes passes of two wherever they are
+// possible; -1: by the estimates.  Without it, a variable that picks a launch
+// or an addressing of the single step keeps single steps, which it is about.
+inline int two_step_choice()
+{
+    if (const char* env = std::getenv("LBM_TWO_STEP")) return env[0] == '0' ? 0 : (env[0] == '1' ? 1 : -1);
+    const char* off32 = std::getenv("LBM_OFF32");
+    const bool single = (off32 && off32[0] == '0') || std::getenv("LBM_ROW_STAGING") || std::getenv("LBM_XCD_CHUNK") ||
+                        std::getenv("LBM_WAVES_PER_SIMD");
+    return single ? 0 : -1;
 }
 // Passes of two steps that `nsteps` steps may take on this stream.  A pass
 // changes buffers once for its two steps, so a call that is recorded into a

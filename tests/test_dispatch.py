@@ -105,3 +105,26 @@ def test_captured_steps_keep_the_buffer_parity(recorder, steps):
         assert back == (steps % 2 == 0)
         assert launches < steps or steps < 4  # pairs are still taken
         assert eager in (["block"] * 2, ["sweep"] * 2)
+
+
+@pytest.mark.parametrize("var,value,single", [
+    ("LBM_OFF32", "0", True), ("LBM_OFF32", "1", False), ("LBM_ROW_STAGING", "0", True), ("LBM_ROW_STAGING", "1", True),
+    ("LBM_XCD_CHUNK", "4", True), ("LBM_WAVES_PER_SIMD", "0", True), ("LBM_WAVES_PER_SIMD", "2", True)])
+def test_single_step_variables_reach_single_steps(recorder, var, value, single):
+    """A variable that picks a launch or an addressing of the single step
+    takes single steps, so that it has the effect it is documented with;
+    LBM_TWO_STEP=1 beside it takes passes of two steps all the same."""
+    code = """
+    out = []
+    e = L.lbm_ensemble_create([(32, 1.5)] * 64, 19, L.LBM_FP64, STREAM)
+    for h in (lattice(64, 20, 9), lattice(200, 101, 75)):
+        launched()
+        L.lbm_step(h, 6)
+        out.append(kinds())
+    L.lib().lbm_ensemble_step(e, 6)
+    out.append(kinds())
+    print(json.dumps(out))
+    """
+    singles = [["single"] * 6] * 3
+    assert recorder(code, **{var: value}) == (singles if single else [["block"] * 3, ["sweep"] * 3, ["sweep"] * 3])
+    assert recorder(code, LBM_TWO_STEP="1", **{var: value}) == [["sweep"] * 3] * 3
