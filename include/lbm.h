@@ -353,9 +353,9 @@ int lbm_set_coupled_populations(lbm_handle *h, const double *in, int on_device);
  * non-temporal, 2 = cached, row_stage 1 = staged; each may be NULL).  The
  * state advances by the steps taken and the step counter counts them.  The
  * choice is cached for the process per (GPU architecture, lattice size, q,
- * precision, streaming, walls, general rates): a later call with the same key
- * applies it without running steps.  Not for coupled lattices or attached
- * networks (LBM_EUNSUPPORTED). */
+ * precision, streaming, walls, general rates, order of the planes): a later
+ * call with the same key applies it without running steps.  Not for coupled
+ * lattices or attached networks (LBM_EUNSUPPORTED). */
 int lbm_tune(lbm_handle *h, int32_t trial_steps, int32_t *block_x, int32_t *block_y, int32_t *cache_policy,
              int32_t *row_stage);
 

@@ -641,6 +641,7 @@ namespace {
 struct TuneEntry {
     std::string arch;
     int nx, ny, nz, q, moments, precision, streaming, walls, general;
+    bool alternate; // plane order of the steps that were timed
     int bx, by, nt, rs;
 };
 std::mutex g_tune_mu;
@@ -666,12 +667,12 @@ int lbm_tune(lbm_handle* h, int32_t trial_steps, int32_t* block_x, int32_t* bloc
     hipDeviceProp_t prop;
     HIP_TRY(hipGetDeviceProperties(&prop, h->device));
     TuneEntry key{prop.gcnArchName, h->g.nx, h->g.ny, h->g.nz, h->p.q, h->p.moments, h->kprec,
-                  h->p.streaming, h->walls ? 1 : 0, h->general ? 1 : 0, 0, 0, 0, 0};
+                  h->p.streaming, h->walls ? 1 : 0, h->general ? 1 : 0, h->alternate, 0, 0, 0, 0};
     auto same = [&](const TuneEntry& e) {
         return e.arch == key.arch && e.nx == key.nx && e.ny == key.ny && e.nz == key.nz && e.q == key.q &&
                e.moments == key.moments &&
                e.precision == key.precision && e.streaming == key.streaming && e.walls == key.walls &&
-               e.general == key.general;
+               e.general == key.general && e.alternate == key.alternate;
     };
     bool cached = false;
     {

@@ -128,3 +128,20 @@ def test_single_step_variables_reach_single_steps(recorder, var, value, single):
     singles = [["single"] * 6] * 3
     assert recorder(code, **{var: value}) == (singles if single else [["block"] * 3, ["sweep"] * 3, ["sweep"] * 3])
     assert recorder(code, LBM_TWO_STEP="1", **{var: value}) == [["sweep"] * 3] * 3
+
+
+def test_tuned_launch_is_kept_per_plane_order(recorder):
+    """lbm_tune's choice is kept for lattices whose single steps take the
+    planes in the same order as the ones it was timed on: streaming accesses
+    (cache_policy 1) always upwards, the default upwards and downwards in turn
+    on this size in place."""
+    got = recorder("""
+    out = []
+    for policy in (1, 0, 1, 0):
+        h = lattice(96, 90, 80, streaming="aa", cache_policy=policy)
+        L._check(L.lib().lbm_tune(h, 2, None, None, None, None))
+        out.append(L.lbm_step_count(h) > 0)  # candidates were timed on steps
+        L.lbm_destroy(h)
+    print(json.dumps(out))
+    """)
+    assert got == [True, True, False, False]
