@@ -959,7 +959,7 @@ int lbm_mlp_accumulate_grad(lbm_mlp* m, lbm_handle* h, const float* target, cons
                          h->stream);
     lbm::launch_train_loss((const float*)post, g, (float)h->p.rho0, target, m->inv_sigma, m->gbuf, m->loss_parts, nullptr,
                            0.0f, h->stream);
-    lbm::launch_train_backward((const float*)state, m->gbuf, g, h->ph, m->packed, m->grad_parts, nullptr, nullptr, false,
+    lbm::launch_train_backward((const float*)state, m->gbuf, g, h->ph, m->packed, m->grad_parts, nullptr, nullptr, nullptr, false,
                                nullptr, nullptr, nullptr, nullptr, 0.0f, h->stream);
     lbm::launch_reduce_grad(m->grad_parts, nwb, m->grad, m->red_tmp, h->stream);
     lbm::launch_sum_partials(m->loss_parts, 1, nlp, nlp, nlp, m->loss_dev, h->stream);
@@ -996,7 +996,7 @@ int lbm_mlp_accumulate_rollout_grad(lbm_mlp* m, lbm_handle* h, const float* targ
     const int64_t state_elems = (int64_t)19 * g.stride;
     const int nwb = lbm::train_rows(g), nlp = lbm::train_loss_parts(g), ngr = lbm::train_groups(g);
     const int npr = std::max(ngr, nlp); // loss partials per step
-    rc = grow((void**)&m->gbuf, m->gbuf_elems, (int64_t)2 * 19 * g.N + lbm::train_feat_elems(g), sizeof(float));
+    rc = grow((void**)&m->gbuf, m->gbuf_elems, (int64_t)2 * 19 * g.N, sizeof(float));
     if (!rc) rc = grow((void**)&m->traj, m->traj_elems, (int64_t)steps * state_elems, sizeof(float));
     if (!rc) rc = grow((void**)&m->grad_parts, m->grad_parts_n, (int64_t)nwb * LBM_MLP_NPARAM, sizeof(float));
     if (!rc) rc = grow((void**)&m->loss_parts, m->loss_parts_n, (int64_t)steps * npr, sizeof(double));
@@ -1038,7 +1038,10 @@ int lbm_mlp_accumulate_rollout_grad(lbm_mlp* m, lbm_handle* h, const float* targ
     // the loss after k steps
     float* A = m->gbuf;
     float* B = m->gbuf + (int64_t)19 * g.N;
-    float* feat = m->gbuf + (int64_t)2 * 19 * g.N;
+    // rates and dL/dfeatures of a step pass between its two launches in memory
+    // that is free then: the state after the step, whose loss and step are done
+    // (P(k + 1), of at least 19 N floats), and the lattice's other buffer
+    float* xbar = (float*)h->buf[1 - h->cur];
     auto target_of = [&](int k) { return targets + (int64_t)(k - 1) * 10 * g.N; }; // k = 1..steps
     auto isig_of = [&](int k) { return m->isig_steps + (int64_t)(k - 1) * 10; };
     auto parts_of = [&](int k) { return m->loss_parts + (int64_t)(k - 1) * npr; };
@@ -1047,8 +1050,8 @@ int lbm_mlp_accumulate_rollout_grad(lbm_mlp* m, lbm_handle* h, const float* targ
                            energy_of(steps), ew, h->stream);
     for (int k = steps - 1; k >= 0; --k) {
         // the partials of all steps add up in place; one reduction at the end
-        lbm::launch_train_backward(P(k), A, g, h->ph, m->packed, m->grad_parts, feat, k > 0 ? B : dstate, k < steps - 1,
-                                   k > 0 ? target_of(k) : nullptr, k > 0 ? isig_of(k) : nullptr,
+        lbm::launch_train_backward(P(k), A, g, h->ph, m->packed, m->grad_parts, P(k + 1), xbar, k > 0 ? B : dstate,
+                                   k < steps - 1, k > 0 ? target_of(k) : nullptr, k > 0 ? isig_of(k) : nullptr,
                                    k > 0 ? parts_of(k) : nullptr, k > 0 ? energy_of(k) : nullptr, ew, h->stream);
         std::swap(A, B);
     }

@@ -214,7 +214,6 @@ void launch_step_mlp(int precision, int pattern, bool walls, bool nt, const void
 int train_loss_parts(const Geom& g);
 int train_rows(const Geom& g);
 int train_groups(const Geom& g);
-int64_t train_feat_elems(const Geom& g); // floats of launch_train_backward's feat
 // energy (device, [E, E_target]) or nullptr: adds the energy term ew ((E - E_t) / E_t)^2
 void launch_train_loss(const float* post, const Geom& g, float rho0, const float* target, const float* inv_sigma,
                        float* gbuf, double* loss_partials, const double* energy, float ew, hipStream_t st);
@@ -224,10 +223,11 @@ void launch_train_loss(const float* post, const Geom& g, float rho0, const float
 void launch_train_energy(const float* posts, int64_t step_stride, int steps, const Geom& g, float rho0, const float* targets,
                          double* partials, hipStream_t st);
 // gout != nullptr: also write dL/df(t) (rollout back-propagation), with the
-// loss on f(t) against `target` (or nullptr) added to it; accumulate: add to
+// loss on f(t) against `target` (or nullptr) added to it, by way of `rates`
+// (9 N floats) and `xbar` (11 N, dL/dfeatures), both scratch; accumulate: add to
 // grad_partials instead of overwriting them
 void launch_train_backward(const float* state, const float* gbuf, const Geom& g, const Phys& ph, const void* net,
-                           float* grad_partials, float* feat, float* gout, bool accumulate, const float* target,
+                           float* grad_partials, float* rates, float* xbar, float* gout, bool accumulate, const float* target,
                            const float* inv_sigma, double* loss_partials, const double* energy, float ew, hipStream_t st);
 // tmp: reduce_grad_tmp_bytes() of device scratch
 size_t reduce_grad_tmp_bytes();

@@ -294,9 +294,9 @@ __global__ __launch_bounds__(256) void k_train_energy(const float* __restrict__ 
 // kbar = S(+u)^T M^-T gbar, then back-propagate through the network.  Writes
 // the row's 1737 gradient entries to grad_partials[row].
 //
-// PROP (rollouts): also the rates (1 of nodes that fall back) and dL/dx of the
-// features (ReLU masks, W1^T, the input scales), feat[j N + x] for
-// k_train_dstate.
+// PROP (rollouts): also the rates (1 of nodes that fall back), rates_out[j N +
+// x], and dL/dx of the features (ReLU masks, W1^T, the input scales),
+// xbar_out[i N + x], for k_train_dstate.
 //
 // What bounds both: latency and, in k_train_dstate, issue; a 32^3 step is 1024
 // rows.  32^3, us per step, both together: 47 with all derivatives in the row's
@@ -310,12 +310,11 @@ struct TrainLoss {
     float ew;
     double* partials;
 };
-constexpr int TRAIN_FEAT = MLP_NOUT + MLP_NIN;
 template <bool PROP>
 __global__ __launch_bounds__(64) void k_train_backward(const float* __restrict__ state, const float* __restrict__ gbuf,
                                                        Geom g, Phys ph, const MlpPacked* __restrict__ net,
-                                                       float* __restrict__ grad_partials, float* __restrict__ feat,
-                                                       int accumulate)
+                                                       float* __restrict__ grad_partials, float* __restrict__ rates_out,
+                                                       float* __restrict__ xbar_out, int accumulate)
 {
     const float rho0 = (float)ph.rho0;
     __shared__ MlpTrain snet;
@@ -455,9 +454,9 @@ __global__ __launch_bounds__(64) void k_train_backward(const float* __restrict__
             for (int i = 0; i < MLP_NIN; ++i) xbar[i] += dh * bf16_to_f32((uint16_t)(ww[i / 2] >> (16 * (i & 1))));
         }
 #pragma unroll
-        for (int j = 0; j < MLP_NOUT; ++j) feat[(int64_t)j * g.N + n0] = rates[j];
+        for (int j = 0; j < MLP_NOUT; ++j) rates_out[(int64_t)j * g.N + n0] = rates[j];
 #pragma unroll
-        for (int i = 0; i < MLP_NIN; ++i) feat[(int64_t)(MLP_NOUT + i) * g.N + n0] = xbar[i] * snet.inv_scale[i];
+        for (int i = 0; i < MLP_NIN; ++i) xbar_out[(int64_t)i * g.N + n0] = xbar[i] * snet.inv_scale[i];
     }
 }
 
@@ -471,8 +470,8 @@ __global__ __launch_bounds__(64) void k_train_backward(const float* __restrict__
 // 1527, three 1447, four 1630 (spills).
 constexpr int TRAIN_K = 3;
 __global__ __launch_bounds__(64) void k_train_dstate(
-    const float* __restrict__ state, const float* __restrict__ gbuf, Geom g, Phys ph, const float* __restrict__ feat,
-    float* __restrict__ gout, TrainLoss tl)
+    const float* __restrict__ state, const float* __restrict__ gbuf, Geom g, Phys ph, const float* __restrict__ rates,
+    const float* __restrict__ xbar_in, float* __restrict__ gout, TrainLoss tl)
 {
     const float rho0 = (float)ph.rho0;
     const int nr = blockIdx.x * 64 + threadIdx.x, j0 = TRAIN_K * blockIdx.y;
@@ -494,9 +493,9 @@ __global__ __launch_bounds__(64) void k_train_dstate(
     Rates<D> rt = rates_of<D>(ph);
     float xbar[MLP_NIN];
 #pragma unroll
-    for (int k = 0; k < MLP_NOUT; ++k) rt.omega_hi[k] = constant(feat[(int64_t)k * g.N + n0]);
+    for (int k = 0; k < MLP_NOUT; ++k) rt.omega_hi[k] = constant(rates[(int64_t)k * g.N + n0]);
 #pragma unroll
-    for (int k = 0; k < MLP_NIN; ++k) xbar[k] = feat[(int64_t)(MLP_NOUT + k) * g.N + n0];
+    for (int k = 0; k < MLP_NIN; ++k) xbar[k] = xbar_in[(int64_t)k * g.N + n0];
     float loss[TRAIN_K] = {};
     if (tl.target) {
         double l2 = train_loss_node(s, n0, g.N, rho0, tl.target, tl.inv_sigma, tl.energy, tl.ew,
@@ -815,7 +814,6 @@ int train_loss_parts(const Geom& g) { return (g.N + 255) / 256; }
 // gradient partials (wavefronts of k_train_backward), loss partials (64-node blocks of k_train_dstate)
 int train_rows(const Geom& g) { return (g.nx + 63) / 64 * g.ny * g.nz; }
 int train_groups(const Geom& g) { return (g.N + 63) / 64; }
-int64_t train_feat_elems(const Geom& g) { return (int64_t)TRAIN_FEAT * g.N; }
 
 void launch_train_loss(const float* post, const Geom& g, float rho0, const float* target, const float* inv_sigma,
                        float* gbuf, double* loss_partials, const double* energy, float ew, hipStream_t st)
@@ -832,18 +830,18 @@ void launch_train_energy(const float* posts, int64_t step_stride, int steps, con
 }
 
 void launch_train_backward(const float* state, const float* gbuf, const Geom& g, const Phys& ph, const void* net,
-                           float* grad_partials, float* feat, float* gout, bool accumulate, const float* target,
+                           float* grad_partials, float* rates, float* xbar, float* gout, bool accumulate, const float* target,
                            const float* inv_sigma, double* loss_partials, const double* energy, float ew, hipStream_t st)
 {
     const dim3 grid((g.nx + 63) / 64, g.ny, g.nz);
     if (!gout) {
         hipLaunchKernelGGL(k_train_backward<false>, grid, dim3(64), 0, st, state, gbuf, g, ph, (const MlpPacked*)net,
-                           grad_partials, nullptr, (int)accumulate);
+                           grad_partials, nullptr, nullptr, (int)accumulate);
         return;
     }
     hipLaunchKernelGGL(k_train_backward<true>, grid, dim3(64), 0, st, state, gbuf, g, ph, (const MlpPacked*)net,
-                       grad_partials, feat, (int)accumulate);
-    hipLaunchKernelGGL(k_train_dstate, dim3(train_groups(g), (19 + TRAIN_K - 1) / TRAIN_K), dim3(64), 0, st, state, gbuf, g, ph, feat, gout,
+                       grad_partials, rates, xbar, (int)accumulate);
+    hipLaunchKernelGGL(k_train_dstate, dim3(train_groups(g), (19 + TRAIN_K - 1) / TRAIN_K), dim3(64), 0, st, state, gbuf, g, ph, rates, xbar, gout,
                        TrainLoss{target, inv_sigma, energy, ew, loss_partials});
 }
 

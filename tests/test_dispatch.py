@@ -145,3 +145,28 @@ def test_tuned_launch_is_kept_per_plane_order(recorder):
     print(json.dumps(out))
     """)
     assert got == [True, True, False, False]
+
+
+@pytest.mark.parametrize("steps", [1, 3])
+@pytest.mark.parametrize("dstate", [False, True])
+def test_rollout_scratch(recorder, steps, dstate):
+    """A rollout's gradient keeps its states, two adjoint states, a gradient
+    per row of nodes and the losses' partial sums, and nothing else of the
+    lattice's size."""
+    got = recorder(f"""
+    n, steps = 32, {steps}
+    N = n ** 3
+    h = lattice(n, n, n)
+    m = L.lbm_mlp_create(None, np.ones(11, dtype=np.float32), STREAM)
+    L.lbm_set_mlp(h, m)
+    before = rec.rec_live_bytes()
+    targets = np.ones((steps, 10, N), dtype=np.float32)
+    out = np.zeros((19, N), dtype=np.float32)
+    L.lbm_mlp_accumulate_rollout_grad(m, h, targets.ctypes.data, steps, np.ones(10), None,
+                                      out.ctypes.data if {dstate} else None)
+    print(json.dumps([rec.rec_live_bytes() - before, N, L.lbm_device_bytes(h)]))
+    """)
+    used, N, lattice_bytes = got
+    state = lattice_bytes // 2  # (two buffers and small tables)
+    allowed = 2 * 19 * 4 * N + steps * state + 4 * 1737 * N // 32 + steps * 8 * N // 64 + 65536
+    assert used <= allowed, (used, allowed)
