@@ -626,7 +626,6 @@ __global__ __launch_bounds__(256) void k_mlp_pack(const float* __restrict__ thet
         const uint16_t v3 = o < MLP_NOUT ? f32_to_bf16(theta[MLP_OFF_W3 + o * 32 + k]) : 0;
         tr.w3[i] = v3;
         tr.w3t[k * 32 + o] = v3;
-        tr.w1t[k * 32 + o] = k < MLP_NIN ? f32_to_bf16(theta[MLP_OFF_W1 + o * MLP_NIN + k]) : 0;
     }
     if (t < 32) {
         in.b1[t] = tr.b1[t] = theta[MLP_OFF_B1 + t];

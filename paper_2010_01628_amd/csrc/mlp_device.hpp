@@ -60,7 +60,6 @@ struct alignas(16) MlpTrain {
     float inv_scale[16];
     uint16_t w2t[32 * 32]; // [in][out]
     uint16_t w3t[32 * 32]; // [in][out (9 used)]
-    uint16_t w1t[32 * 32]; // [in (11 used)][out]
 };
 static_assert(sizeof(MlpTrain) % 16 == 0, "16-byte network copies");
 
