@@ -137,3 +137,51 @@ def test_ensemble(q, precision, steps, chunk, monkeypatch):
     assert np.array_equal(ka, kb)
     for a, b in zip(fa, fb):
         assert np.isfinite(a).all() and np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("boxes,q,precision", [
+    ([(32, 1.9), (32, 1.5), (7, 1.2)], 19, "fp32"),  # 10 MB
+    ([(32, 1.9), (32, 1.5), (7, 1.2)], 27, "fp32"),
+    ([(32, 1.9), (32, 1.5)], 19, "fp64"),
+    ([(96, 1.9), (96, 1.6), (64, 1.2)], 19, "fp32"),  # 309 MB
+])
+def test_ensemble_with_streaming_stores(boxes, q, precision, monkeypatch):
+    """Ensembles that take streaming stores (below 48 MB or above 256 MiB) in
+    boxes whose rows are whole 128-byte lines: bit for bit the single-step
+    ensemble's."""
+    def run(two):
+        monkeypatch.setenv("LBM_TWO_STEP", two)
+        ens = L.Ensemble(boxes, q=q, precision=precision)
+        for b, (n, _) in enumerate(boxes):
+            rho, u, _ = inputs.random_lattice_fields(n, n, n, seed=b + 1, umax=0.03)
+            ens.init(b, rho, u)
+        ens.step(7)
+        f = [ens.get_populations(b) for b in range(len(boxes))]
+        ens.close()
+        return f
+
+    for a, b in zip(run("0"), run("1")):
+        assert np.isfinite(a).all() and np.array_equal(a, b)
+
+
+def test_arrays_beyond_4_gib(monkeypatch):
+    """Population arrays that start beyond 4 GiB from the first (384x400x384
+    FP32, 4.5 GB a buffer): passes of two steps equal single steps, bit for
+    bit."""
+    import torch
+
+    size = (384, 400, 384)
+    shape = size[::-1]
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    rho = 1.0 + 0.01 * torch.rand(shape, generator=gen, dtype=torch.float64, device="cuda")
+    u = 0.05 * (torch.rand((3,) + shape, generator=gen, dtype=torch.float64, device="cuda") - 0.5)
+    runs = []
+    for two in ("0", "1"):
+        monkeypatch.setenv("LBM_TWO_STEP", two)
+        lat = L.Lattice(L.make_params(*size, precision="fp32", omega=1.7))
+        lat.init(rho, u)
+        lat.step(5)
+        runs.append(lat.get_populations())
+        lat.close()
+    assert torch.isfinite(runs[0]).all()
+    assert torch.equal(runs[0], runs[1])
