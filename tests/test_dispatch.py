@@ -170,3 +170,21 @@ def test_rollout_scratch(recorder, steps, dstate):
     state = lattice_bytes // 2  # (two buffers and small tables)
     allowed = 2 * 19 * 4 * N + steps * state + 4 * 1737 * N // 32 + steps * 8 * N // 64 + 65536
     assert used <= allowed, (used, allowed)
+
+
+def test_benchmark_ensemble_takes_passes_of_two_steps(recorder):
+    """The 64-box workload's plain ensembles take two steps to a pass (bench.py
+    counts their bytes by that)."""
+    got = recorder("""
+    from paper_2010_01628_amd import inputs
+    boxes = [(n, inputs.omega_from_nu(nu)) for n, nu, _ in inputs.ensemble_boxes()]
+    out = []
+    for q in (19, 27):
+        e = L.lbm_ensemble_create(boxes, q, L.LBM_FP32, STREAM)
+        launched()
+        L.lib().lbm_ensemble_step(e, 4)
+        out.append(kinds())
+        L.lib().lbm_ensemble_destroy(e)
+    print(json.dumps(out))
+    """)
+    assert got == [["sweep"] * 2] * 2
