@@ -181,8 +181,9 @@ typedef struct {
                                  y = ny - 1 (halfway bounce-back) */
     int32_t check_every;      /* > 0: every that many steps lbm_step checks that the density
                                  is finite and positive everywhere (FP64 reduction) */
-    int32_t block_x, block_y; /* work-group shape of the step kernels (product a multiple of 64,
-                                 at most 256); 0 = library default: whole x rows of up to 256
+    int32_t block_x, block_y; /* work-group shape of the kernels of single steps and fields
+                                 (product a multiple of 64, at most 256; passes of two steps
+                                 have tiles of their own); 0 = library default: whole x rows of up to 256
                                  nodes per work-group, one work-group of nx threads per row
                                  of 257..1024 nodes (where the staging rows fit in 64 KB of
                                  LDS; not for A-B with 16-bit storage, which keeps 256-wide
@@ -190,11 +191,17 @@ typedef struct {
                                  through LDS on periodic lattices */
     int32_t cache_policy;     /* population loads/stores: 0 = library default (non-temporal
                                  for staged steps and for A-B with 4- and 8-byte storage,
-                                 cached otherwise; cached too where all buffers together
-                                 hold 48 MB to 256 MiB, or 48 MB and more in x rows that
-                                 are not whole 128-byte lines, and for single steps that
-                                 take the planes in turn upwards and downwards), 1 = non-temporal
-                                 (streaming) hints, 2 = ordinary cached accesses */
+                                 cached otherwise; cached too where the buffers hold 24 MB
+                                 each (of all lattices) or more, and at most 256 MiB
+                                 together or, but for colour-gradient lattices, x rows that
+                                 are not whole 128-byte lines; and for single steps of plain,
+                                 learned and magnetic lattices that take the planes upwards
+                                 and downwards in turn: one buffer of 24 to 800 MB, or two
+                                 with 4- or 8-byte storage of 256 MiB to 480 MB together),
+                                 1 = non-temporal (streaming) hints, planes always upwards,
+                                 2 = ordinary cached accesses.  Passes of two steps read
+                                 with ordinary accesses; large lattices' passes store by
+                                 this policy */
     int32_t coupled;          /* lbm_coupling */
     lbm_phase_params phase;   /* LBM_COUPLED_PHASE: q = 19, FP64 or FP32, A-B, periodic, no
                                  external force, the paper's bulk and higher-order rates,
@@ -342,14 +349,16 @@ int lbm_colour_fields(lbm_handle *h, double *rho_red, double *rho_blue, int on_d
 int lbm_get_coupled_populations(lbm_handle *h, double *out, int on_device);
 int lbm_set_coupled_populations(lbm_handle *h, const double *in, int on_device);
 
-/* Autotuner of the plain step kernel: runs 2 + trial_steps (rounded up to
+/* Autotuner of the plain single step: runs 2 + trial_steps (rounded up to
  * even) real steps, three times in interleaved rounds, for each work-group
  * shape 256x1, 128x2, 64x4, 128x1, 64x2, 64x1 (those that fit the lattice;
  * for rows of 257..1024 nodes also nx x 1, staged only)
  * with and without non-temporal hints and, where a work-group spans whole x
  * rows (periodic; A-B, or the odd step of AA), with and without staging the
- * x-moving populations through LDS; keeps the fastest (by each candidate's best round) for later
- * lbm_step calls and reports it (block_x, block_y, cache_policy 1 =
+ * x-moving populations through LDS; keeps the fastest (by each candidate's
+ * best round) for later single steps (lbm_step of one step, odd last ones, and
+ * every step of a lattice that takes no passes of two, whose tiles and hints
+ * are not tuned) and reports it (block_x, block_y, cache_policy 1 =
  * non-temporal, 2 = cached, row_stage 1 = staged; each may be NULL).  The
  * state advances by the steps taken and the step counter counts them.  The
  * choice is cached for the process per (GPU architecture, lattice size, q,
@@ -362,10 +371,10 @@ int lbm_tune(lbm_handle *h, int32_t trial_steps, int32_t *block_x, int32_t *bloc
 /* Number of steps taken since lbm_init. */
 int64_t lbm_step_count(const lbm_handle *h);
 
-/* Which plain step kernel lbm_step launches (not the learned or coupled
- * ones): 0 = one node per thread, 1 = x-moving populations staged through LDS
- * along whole rows (the default wherever possible; lbm_tune may choose
- * either); -1 for a NULL handle. */
+/* Which plain kernel lbm_step launches for a single step (not the learned or
+ * coupled ones, nor passes of two steps): 0 = one node per thread, 1 =
+ * x-moving populations staged through LDS along whole rows (the default
+ * wherever possible; lbm_tune may choose either); -1 for a NULL handle. */
 int32_t lbm_step_variant(const lbm_handle *h);
 
 /* Device bytes held by the handle (population buffers and tables). */
@@ -490,11 +499,13 @@ int lbm_stream_copy(const void *src, void *dst, int64_t n, int32_t q, int32_t el
 
 /* ---------------------------------------------------------------------------
  * Ensembles: many independent periodic cubic boxes (different sides and
- * viscosities, no force) advanced together, one launch per step over a
- * (box, 256-node tile) work list, walked by a fixed number of work-groups
- * (one per tile by default; lbm_ensemble_tune tries persistent grids of
- * 2..64 work-groups per compute unit); the step loop is captured in a HIP
- * graph and replayed.  Same collision as a single lattice (Sec. II.B for q =
+ * viscosities, no force) advanced together.  Plain boxes take two steps per
+ * launch where that is estimated faster, over a list of (box, tile, run of
+ * planes); otherwise, and with a network, one launch per step over a (box,
+ * 256-node tile) work list, walked by a fixed number of work-groups (one per
+ * tile by default; lbm_ensemble_tune tries persistent grids of 2..64
+ * work-groups per compute unit).  The step loop is captured in a HIP graph
+ * and replayed.  Same collision as a single lattice (Sec. II.B for q =
  * 19, App. D for q = 27); A-B streaming; FP32 or FP64 storage.
  * ------------------------------------------------------------------------- */
 typedef struct lbm_ensemble lbm_ensemble;
@@ -520,10 +531,11 @@ int lbm_ensemble_get_populations(lbm_ensemble *e, int32_t box, double *f, int on
 int64_t lbm_ensemble_nodes(const lbm_ensemble *e);
 int64_t lbm_ensemble_step_count(const lbm_ensemble *e);
 int64_t lbm_ensemble_fallback_count(lbm_ensemble *e);
-/* Autotuner: times `trial_steps` steps (rounded up to even) for each
- * candidate launch -- 2, 4, 8, 16, 32 or 64 persistent work-groups per
+/* Autotuner of the launch of one step: times `trial_steps` steps (rounded up
+ * to even) for each candidate -- 2, 4, 8, 16, 32 or 64 persistent work-groups per
  * compute unit, or one work-group per tile -- and keeps the fastest
- * (*grid_out, may be NULL).  It advances the state by those steps; call it
+ * (*grid_out, may be NULL) for learned and odd steps and the energies (passes
+ * of two steps have one work-group per item of their list).  It advances the state by those steps; call it
  * before lbm_ensemble_init (the rest state is a fixed point) to leave the
  * state untouched. */
 int lbm_ensemble_tune(lbm_ensemble *e, int32_t trial_steps, int32_t *grid_out);

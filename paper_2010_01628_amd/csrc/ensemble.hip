@@ -1,12 +1,13 @@
 // Ensemble of independent periodic cubic boxes of different sizes, advanced
-// by one persistent launch per step.
+// by one launch per step, or per two plain steps (k_ens_pair).
 //
 // All boxes live in one allocation: box b's populations start at element
-// offset off_b and are SoA with its own stride (N_b padded).  The work list is
-// every box cut into tiles of 256 consecutive nodes (x fastest); tile t
-// belongs to box tile_box[t].  A launch has a fixed number of workgroups that
-// walk the tile list with stride gridDim.x, so uneven boxes need no separate
-// launches and the whole step is one kernel node in a captured graph.
+// offset off_b and are SoA with its own stride (N_b padded).  A single step's
+// work list is every box cut into tiles of 256 consecutive nodes (x fastest);
+// tile t belongs to box tile_box[t].  A launch has a fixed number of
+// workgroups that walk the tile list with stride gridDim.x, so uneven boxes
+// need no separate launches and the whole step is one kernel node in a
+// captured graph.
 #include "lattice_kernels.hpp"
 #include "mlp_device.hpp"
 #include "two_step.hpp"

@@ -658,12 +658,14 @@ class Lattice:
 
     @property
     def step_variant(self):
-        """0: one node per thread, 1: x-moving populations staged through LDS."""
+        """Kernel of a single step: 0: one node per thread, 1: x-moving
+        populations staged through LDS."""
         return lbm_step_variant(self.h)
 
     def tune(self, trial_steps=10):
-        """Pick the step kernel's work-group shape, cache policy and row
-        staging by timing real steps (the state advances); returns
+        """Pick the single step's work-group shape, cache policy and row
+        staging by timing real steps (the state advances; passes of two steps
+        are not tuned); returns
         (block_x, block_y, policy, row_stage)."""
         bx, by, nt, rs = ctypes.c_int32(), ctypes.c_int32(), ctypes.c_int32(), ctypes.c_int32()
         _check(lib().lbm_tune(self.h, int(trial_steps), ctypes.byref(bx), ctypes.byref(by), ctypes.byref(nt),
