@@ -465,8 +465,8 @@ __global__ __launch_bounds__(64) void k_train_backward(const float* __restrict__
 // through the features, with the rates and dL/dfeatures of k_train_backward.
 // With `target` (every step but the first) the loss on f(t) itself is added,
 // and its sum of squares goes to loss_partials[64-node block].
-// Three populations to a wavefront share the collision's values (3085 VALU
-// instructions, 1832 for one); 32^3, 32 steps of a rollout, us: one 1748, two
+// Three populations to a wavefront share the collision's values (2783 VALU
+// instructions per wavefront); 32^3, 32 steps of a rollout, us: one 1748, two
 // 1527, three 1447, four 1630 (spills).
 constexpr int TRAIN_K = 3;
 __global__ __launch_bounds__(64) void k_train_dstate(

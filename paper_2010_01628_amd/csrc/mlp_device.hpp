@@ -39,8 +39,8 @@ static_assert(MLP_OFF_B3 + MLP_NOUT == MLP_NPARAM, "parameter layout");
 // of a product holding the eight bf16 at op[product][8 l], so that a
 // wavefront's read of one is 1 KiB in a row.  (Rows of the 32 x 32 matrices
 // lie 64 bytes apart, and 32 lanes reading one row each met 8 to 16 in a bank:
-// 456 of the 656 LDS cycles per wavefront, the LDS 87 % busy through the
-// learned 192^3 FP16 step.)
+// 228 of the 344 LDS cycles per wavefront of the learned 192^3 FP16 step were
+// conflicts, now none of 168.)
 struct alignas(16) MlpInfer {
     uint16_t op[5][64 * 8];
     float b1[32], b2[32], b3[32];
@@ -319,8 +319,9 @@ __device__ inline bf16x8_t w_op(const MlpInfer& W, int p)
 // One 32-node column block through the three layers; o[q] = accumulator
 // rows q (q < 5) of the output layer.
 //
-// What bounds the learned steps: the issue of about 690 VALU instructions and
-// ten products per wavefront beside the step's own traffic.  SERIAL:
+// What bounds the learned steps: the issue of 631 VALU instructions (2-byte
+// storage; 604 with FP32) and ten products per wavefront beside the step's own
+// traffic.  SERIAL:
 // scheduling barriers (here between the layers, in mlp_forward_regs between
 // the blocks) keep the biases and operands of one product at a time in
 // registers: 88 VGPRs and five waves per SIMD in place of 125 and four for

@@ -16,7 +16,7 @@
 //
 // What bounds it: a single step moves 2 Q values per node and runs at the rate
 // of a copy of its own traffic; a pair moves Q in (the halo columns again: HBM
-// reads 1.14 times the lattice with 32x13 tiles) and Q out.  256^3 FP32, 64x13
+// reads 1.11 times the lattice with 64x13 tiles) and Q out.  256^3 FP32, 64x13
 // tiles in three runs of planes: 834 us for two single steps, 620 for a pair;
 // its loads and stores alone take 540, its collisions alone 360.
 //
