@@ -656,7 +656,8 @@ __global__ __launch_bounds__(256) void k_init(S* __restrict__ buf, Geom g, doubl
 }
 
 // Populations f = w rho0 + s from double[Q N] (device) into the state.
-template <class L, class S, Pattern P, bool WALLS>
+// STREAM (stream_set): streaming hint on f.
+template <class L, class S, Pattern P, bool WALLS, bool STREAM>
 __global__ __launch_bounds__(256) void k_set_pops(S* __restrict__ buf, Geom g, double rho0, const double* __restrict__ f)
 {
     using R = typename Codec<S>::R;
@@ -668,20 +669,21 @@ __global__ __launch_bounds__(256) void k_set_pops(S* __restrict__ buf, Geom g, d
     node_idx(g, x, y, z, d);
     const int n = nb(d, 0, 0, 0);
     R s[L::Q];
-    // streaming reads where f does not fit the last-level cache (192^3 FP16
-    // 260 -> 241 us, FP32 302 -> 268; 200x101x75, 230 MB, 60 -> 65; FP64 no gain)
-    if (sizeof(S) < 8 && (int64_t)g.N * L::Q * 8 > ((int64_t)256 << 20)) {
-        asm volatile("" : "+s"(f)); // (the branches' loads would be merged into ordinary ones)
 #pragma unroll
-        for (int i = 0; i < L::Q; ++i) s[i] = (R)(ld<double, true>(f + (int64_t)i * g.N + n) - L::w(i) * rho0);
-    } else {
-#pragma unroll
-        for (int i = 0; i < L::Q; ++i) s[i] = (R)(f[(int64_t)i * g.N + n] - L::w(i) * rho0);
-    }
+    for (int i = 0; i < L::Q; ++i) s[i] = (R)(ld<double, STREAM>(f + (int64_t)i * g.N + n) - L::w(i) * rho0);
     place_state<L, S, P, WALLS>(buf, g.stride, d, s);
 }
+// 2-byte storage, where f does not fit the last-level cache: 192^3 FP16 A-B 265
+// -> 240 us, 160^3 BF16 AA 160 -> 142, 201x199x150 FP16 250 -> 234; FP32 gains on
+// some sizes and loses on others (128^3 98 -> 88, 256x256x192 511 -> 529,
+// 201x199x150 287 -> 339)
+template <class S> inline bool stream_set(const Geom& g, int q)
+{
+    return sizeof(S) == 2 && (int64_t)g.N * q * 8 > ((int64_t)256 << 20);
+}
 
-template <class L, class S, Pattern P, bool WALLS>
+// The state's populations to f.  STREAM (stream_get): streaming hint on f.
+template <class L, class S, Pattern P, bool WALLS, bool STREAM>
 __global__ __launch_bounds__(256) void k_get_pops(const S* __restrict__ buf, Geom g, double rho0, double* __restrict__ f)
 {
     using R = typename Codec<S>::R;
@@ -694,11 +696,14 @@ __global__ __launch_bounds__(256) void k_get_pops(const S* __restrict__ buf, Geo
     const int n = nb(d, 0, 0, 0);
     R s[L::Q];
     gather<L, S, P, WALLS>(buf, g.stride, d, s);
-    // streaming stores with 4 and 8 bytes, after steps: 200x101x75 FP32 67 ->
-    // 59 us, 192^3 320 -> 311, D3Q27 128^3 FP64 197 -> 192; FP16 AA 249 -> 267
 #pragma unroll
-    for (int i = 0; i < L::Q; ++i) st<double, (sizeof(S) >= 4)>(f + (int64_t)i * g.N + n, L::w(i) * rho0 + (double)s[i]);
+    for (int i = 0; i < L::Q; ++i) st<double, STREAM>(f + (int64_t)i * g.N + n, L::w(i) * rho0 + (double)s[i]);
 }
+// 4- and 8-byte storage, where f's rows are whole halves of 128-byte lines:
+// 200x101x75 FP32 70 -> 56 us, 128^3 93 -> 70, D3Q27 FP64 96^3 74 -> 55; rows that
+// share them lose (201x199x150 FP32 304 -> 340, D3Q27 434 -> 518, 100^3 37 -> 42),
+// and so does 2-byte storage (192^3 FP16 AA 249 -> 267)
+template <class S> inline bool stream_get(const Geom& g) { return sizeof(S) >= 4 && g.nx % 8 == 0; }
 
 // ---------------------------------------------------------------------------
 // Macroscopic fields and FP64 diagnostics.  Each block reduces its nodes with
@@ -912,20 +917,24 @@ template <class L, class S> struct Launch {
 #undef LBM_STEP_O
     }
 
-#define LBM_DISPATCH_PW(KERNEL, ...)                                                                     \
-    switch (pattern) {                                                                                   \
-    case AB:                                                                                             \
-        if (walls) hipLaunchKernelGGL((KERNEL<L, S, AB, true>), grid, block, 0, st, __VA_ARGS__);          \
-        else hipLaunchKernelGGL((KERNEL<L, S, AB, false>), grid, block, 0, st, __VA_ARGS__);               \
-        break;                                                                                           \
-    case AA_EVEN:                                                                                        \
-        if (walls) hipLaunchKernelGGL((KERNEL<L, S, AA_EVEN, true>), grid, block, 0, st, __VA_ARGS__);     \
-        else hipLaunchKernelGGL((KERNEL<L, S, AA_EVEN, false>), grid, block, 0, st, __VA_ARGS__);          \
-        break;                                                                                           \
-    default:                                                                                             \
-        if (walls) hipLaunchKernelGGL((KERNEL<L, S, AA_ODD, true>), grid, block, 0, st, __VA_ARGS__);      \
-        else hipLaunchKernelGGL((KERNEL<L, S, AA_ODD, false>), grid, block, 0, st, __VA_ARGS__);           \
+// TAIL: the kernel's template arguments after WALLS
+#define LBM_DISPATCH_PWX(KERNEL, TAIL, ...)                                                                     \
+    switch (pattern) {                                                                                          \
+    case AB:                                                                                                    \
+        if (walls) hipLaunchKernelGGL((KERNEL<L, S, AB, true TAIL>), grid, block, 0, st, __VA_ARGS__);          \
+        else hipLaunchKernelGGL((KERNEL<L, S, AB, false TAIL>), grid, block, 0, st, __VA_ARGS__);               \
+        break;                                                                                                  \
+    case AA_EVEN:                                                                                               \
+        if (walls) hipLaunchKernelGGL((KERNEL<L, S, AA_EVEN, true TAIL>), grid, block, 0, st, __VA_ARGS__);     \
+        else hipLaunchKernelGGL((KERNEL<L, S, AA_EVEN, false TAIL>), grid, block, 0, st, __VA_ARGS__);          \
+        break;                                                                                                  \
+    default:                                                                                                    \
+        if (walls) hipLaunchKernelGGL((KERNEL<L, S, AA_ODD, true TAIL>), grid, block, 0, st, __VA_ARGS__);      \
+        else hipLaunchKernelGGL((KERNEL<L, S, AA_ODD, false TAIL>), grid, block, 0, st, __VA_ARGS__);           \
     }
+#define LBM_DISPATCH_PW(KERNEL, ...) LBM_DISPATCH_PWX(KERNEL, , __VA_ARGS__)
+#define LBM_STREAMING , true
+#define LBM_ORDINARY , false
 
     static void init(int pattern, bool walls, void* buf, const Geom& g, double rho0, const double* rho, const double* u,
                      dim3 grid, dim3 block, hipStream_t st)
@@ -935,12 +944,24 @@ template <class L, class S> struct Launch {
     static void set_pops(int pattern, bool walls, void* buf, const Geom& g, double rho0, const double* f, dim3 grid,
                          dim3 block, hipStream_t st)
     {
-        LBM_DISPATCH_PW(k_set_pops, (S*)buf, g, rho0, f);
+        if constexpr (sizeof(S) == 2) {
+            if (stream_set<S>(g, L::Q)) {
+                LBM_DISPATCH_PWX(k_set_pops, LBM_STREAMING, (S*)buf, g, rho0, f);
+                return;
+            }
+        }
+        LBM_DISPATCH_PWX(k_set_pops, LBM_ORDINARY, (S*)buf, g, rho0, f);
     }
     static void get_pops(int pattern, bool walls, const void* buf, const Geom& g, double rho0, double* f, dim3 grid,
                          dim3 block, hipStream_t st)
     {
-        LBM_DISPATCH_PW(k_get_pops, (const S*)buf, g, rho0, f);
+        if constexpr (sizeof(S) >= 4) {
+            if (stream_get<S>(g)) {
+                LBM_DISPATCH_PWX(k_get_pops, LBM_STREAMING, (const S*)buf, g, rho0, f);
+                return;
+            }
+        }
+        LBM_DISPATCH_PWX(k_get_pops, LBM_ORDINARY, (const S*)buf, g, rho0, f);
     }
     static void moments(int pattern, bool walls, const void* buf, const Geom& g, const Phys& ph, double* rho, double* u,
                         double* partials, dim3 grid, dim3 block, hipStream_t st)
@@ -948,6 +969,9 @@ template <class L, class S> struct Launch {
         LBM_DISPATCH_PW(k_moments, (const S*)buf, g, ph, rho, u, partials);
     }
 #undef LBM_DISPATCH_PW
+#undef LBM_DISPATCH_PWX
+#undef LBM_STREAMING
+#undef LBM_ORDINARY
 };
 
 } // namespace lbm

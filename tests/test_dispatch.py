@@ -188,3 +188,36 @@ def test_benchmark_ensemble_takes_passes_of_two_steps(recorder):
     print(json.dumps(out))
     """)
     assert got == [["sweep"] * 2] * 2
+
+
+@pytest.mark.parametrize("size,precision,streams", [
+    ((96, 64, 40), "fp32", True), ((200, 64, 40), "fp64", True),    # get: rows of whole halves of lines
+    ((100, 64, 40), "fp32", False), ((201, 64, 40), "fp64", False), # ... rows that share them
+    ((96, 64, 40), "fp16", False)])
+def test_checkpoint_stores(recorder, size, precision, streams):
+    """lbm_get_populations stores with the streaming hint only where rows do
+    not share half-lines, and not from 2-byte storage."""
+    name = recorder(f"""
+    h = lattice(*{size}, precision={precision!r})
+    f = np.zeros(19 * {size[0] * size[1] * size[2]})
+    launched()
+    L.lbm_get_populations(h, f.ctypes.data, True)
+    print(json.dumps(launched()[0][0]))
+    """)
+    assert "k_get_pops" in name and ("Lb1EEEv" in name) == streams, name
+
+
+@pytest.mark.parametrize("size,precision,streams", [
+    ((96, 96, 90), "fp16", False), ((128, 128, 110), "bf16", True), ((201, 97, 93), "fp16", True),
+    ((128, 128, 110), "fp32", False), ((201, 97, 93), "fp32", False), ((96, 96, 90), "fp32", False)])
+def test_restore_loads(recorder, size, precision, streams):
+    """lbm_set_populations reads with the streaming hint only into 2-byte
+    storage, from arrays larger than the last-level cache."""
+    name = recorder(f"""
+    h = lattice(*{size}, precision={precision!r})
+    f = np.zeros(19 * {size[0] * size[1] * size[2]})
+    launched()
+    L.lbm_set_populations(h, f.ctypes.data, True)
+    print(json.dumps(launched()[0][0]))
+    """)
+    assert "k_set_pops" in name and ("Lb1EEEv" in name) == streams, name
