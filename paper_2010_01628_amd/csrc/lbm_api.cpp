@@ -390,17 +390,19 @@ int lbm_create(const lbm_params* p, void* stream, lbm_handle** out)
         if (p->cache_policy == 0 && h->g.row_stage) h->nt = true;
     }
     {
-        // (two-colour steps write two lattices: rows sharing lines gain nothing
-        // beyond the cache, 80x320x80 183 us streaming, 194 ordinary)
         // values per node of every buffer (two of each lattice with A-B)
         const int coupled = p->coupled == LBM_COUPLED_PHASE ? 7 : p->coupled == LBM_COUPLED_MAGNETIC ? 21
                             : p->coupled == LBM_COUPLED_COLOUR ? 19 : 0;
         const int nbuf = p->streaming == LBM_AB ? 2 : 1;
         const int64_t bytes = (int64_t)nbuf * (p->q + coupled) * h->g.N * eb;
-        h->cached = p->cache_policy == 2 || (p->cache_policy == 0 && lbm::ordinary_accesses(bytes, nbuf, p->coupled == LBM_COUPLED_COLOUR ? 0 : (int64_t)p->nx * eb));
+        const bool whole_rows = (int64_t)p->nx * eb % 128 == 0;
+        const lbm::StepState single{bytes, nbuf, eb, p->q, p->coupled,
+                                    whole_rows || (p->coupled == LBM_COUPLED_NONE && h->g.row_stage)};
+        const bool ordinary = p->cache_policy == 2 || (p->cache_policy == 0 && lbm::single_ordinary(single));
+        h->cached = p->cache_policy == 2 || (p->cache_policy == 0 && lbm::ordinary_accesses(bytes, nbuf, (int64_t)p->nx * eb));
         h->alternate = p->cache_policy != 1 && lbm::alternate_planes(bytes, nbuf, eb) &&
                        (p->coupled == LBM_COUPLED_NONE || p->coupled == LBM_COUPLED_MAGNETIC);
-        if (h->cached || (h->alternate && p->cache_policy == 0)) h->nt = false;
+        if (ordinary || (h->alternate && p->cache_policy == 0)) h->nt = false;
         set_pair(h, h->cached, bytes <= ((int64_t)256 << 20));
     }
 

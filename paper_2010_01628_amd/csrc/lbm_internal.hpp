@@ -110,20 +110,12 @@ struct PairShape {
     int block;
     int nt = 1; // streaming hint on the sweeps' stores
 };
-// Whether the steps take ordinary loads and stores instead of streaming ones,
-// for a state of this many bytes (all buffers of all lattices) in x rows of
-// row_bytes: states larger than the L2s hold that either stay in the 256 MiB
-// last-level cache from one step to the next or have rows that are not whole
-// 128-byte lines, whose shared lines it merges.  In the cache, streaming / ordinary, us per step: FP32
-// 96^3 26.6 / 19.4, 100^3 41 / 23.6, FP16 128^3 29.4 / 21.9, FP32 AA 128^3
-// 54.8 / 40.5, Shan-Chen 100^3 50.4 / 42.6, two-phase 96^3 43.9 / 32.7,
-// magnetic 64^3 17.6 / 12.9; below the range (40 MB) FP32 64^3 7.5 / 8.1,
-// above it (320 MB) Shan-Chen 128^3 85 / 88, two-phase 128^3 (436 MB) 85 / 94.
-// Larger ones with such rows: 200^3 FP32 320 / 265 (a pair of steps), FP16 255
-// / 164, FP32 AA 340 / 257; 330x150x200 FP32 282 / 219 (two steps per pass),
-// FP64 516 / 389; 208x200x200 FP16 248 / 183; with whole lines, 256x256x200
-// FP32 242 / 254, AA 333 / 361.  One buffer of 24 MB is the lower end: AA FP16
-// 96^3 (34 MB) 14.6 / 12.1, A-B FP32 64^3 (2 x 20 MB) 7.5 / 8.1.
+// Whether passes of two steps, and ensembles, take ordinary accesses instead of
+// streaming ones, for a state of this many bytes (all buffers) in x rows of
+// row_bytes: where the 256 MiB last-level cache keeps it from one launch to the
+// next, or rows that are not whole 128-byte lines share lines, which it merges
+// (two steps, streaming / ordinary, us: 200^3 FP32 320 / 265, 330x150x200 FP32 282 /
+// 219, FP64 516 / 389).
 inline bool ordinary_accesses(int64_t bytes, int buffers, int64_t row_bytes)
 {
     return bytes >= (int64_t)24000000 * buffers && (bytes <= ((int64_t)256 << 20) || row_bytes % 128 != 0);

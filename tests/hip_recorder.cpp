@@ -16,6 +16,7 @@ struct Launch {
     std::string name;
     dim3 grid, block;
     const void* arg[2]; // the first two parameters
+    int rev;            // step kernels: Geom::rev
 };
 std::map<const void*, std::string>& names()
 {
@@ -54,6 +55,7 @@ int64_t rec_threads(int i)
     const Launch& l = launches[i];
     return (int64_t)l.grid.x * l.grid.y * l.grid.z * l.block.x * l.block.y * l.block.z;
 }
+int rec_rev(int i) { return launches[i].rev; }
 void rec_clear() { launches.clear(); }
 int64_t rec_live_bytes() { return live; }
 int64_t rec_peak_bytes() { return peak; }
@@ -89,8 +91,11 @@ hipError_t __hipPopCallConfiguration(dim3* g, dim3* b, size_t* lds, hipStream_t*
 }
 hipError_t hipLaunchKernel(const void* f, dim3 g, dim3 b, void** args, size_t, hipStream_t)
 {
-    Launch l{names()[f], g, b, {nullptr, nullptr}};
+    Launch l{names()[f], g, b, {nullptr, nullptr}, 0};
     for (int k = 0; k < 2; ++k) std::memcpy(&l.arg[k], args[k], sizeof(void*));
+    const auto is = [&](const char* part) { return l.name.find(part) != std::string::npos; };
+    const int geom = is("k_mhd_step") ? 4 : is("k_step_aa") ? 1 : is("k_step_ab") || is("k_step_mlp") ? 2 : -1;
+    if (geom >= 0) l.rev = static_cast<const int*>(args[geom])[5]; // nx, ny, nz, nxy, N, rev
     launches.push_back(l);
     return hipSuccess;
 }

@@ -41,6 +41,21 @@ def kinds():
     # what each launch since the last call is
     return ["block" if "k_step_pair_block" in n else "sweep" if "k_step_pair" in n or "k_ens_pair" in n
             else "single" if "k_step" in n or "k_ens_step" in n else "other" for n, _, _ in launched()]
+
+
+def accesses(h):
+    # two single steps: whether each streams, and whether it takes the planes downwards
+    import re
+    out = []
+    for _ in range(2):
+        launched()
+        L.lbm_step(h, 1)
+        i, name = [(i, rec.rec_name(i).decode()) for i in range(rec.rec_count())][-1]
+        flags = [f == "1" for f in re.findall("Lb([01])E", name)]
+        at = 1 if re.search("k_step_ab_rows|k_step_aa_odd_rows|k_step_mlp|k_mhd_step|k_sc_step|k_cg_step", name) else \
+            0 if "k_phase_step" in name else 2
+        out.append([flags[at], bool(rec.rec_rev(i))])
+    return out
 """
 
 
@@ -221,3 +236,30 @@ def test_restore_loads(recorder, size, precision, streams):
     print(json.dumps(launched()[0][0]))
     """)
     assert "k_set_pops" in name and ("Lb1EEEv" in name) == streams, name
+
+
+MHD = dict(magnetic=dict(eta=0.1))
+SC = dict(shan_chen=dict(G=-5.0))
+CG = dict(colour=dict(alpha_red=7 / 9), walls_y=True)
+PHASE = dict(phase=dict(rho_light=1.0, rho_heavy=10.0, sigma=1e-3, width=4.0, mobility=0.1))
+
+
+@pytest.mark.parametrize("size,kw,streams", [
+    ((64, 64, 64), dict(), True), ((64, 64, 80), dict(), False),                  # 20, 25 MB a buffer
+    ((64, 64, 64), dict(q=27), True), ((64, 64, 80), dict(q=27), False),          # 28, 35 MB
+    ((64, 64, 64), dict(precision="fp64"), False),
+    ((160, 160, 128), dict(), True), ((161, 160, 128), dict(), False),            # 498 MB: whole lines, shared ones
+    ((48, 300, 230), dict(), True), ((48, 300, 230), dict(walls_y=True), False),  # 503 MB: staged rows fill lines
+    ((64, 64, 48), MHD, False),
+    ((64, 64, 80), PHASE, False), ((170, 150, 141), PHASE, False), ((100, 100, 100), dict(precision="fp64", **PHASE), True),
+    ((64, 80, 80), SC, True), ((96, 96, 96), SC, False), ((64, 64, 80), dict(precision="fp64", **SC), True),
+    ((72, 72, 64), SC, True), ((75, 75, 75), SC, False), ((150, 140, 130), SC, False), ((201, 199, 150), SC, True),
+    ((64, 64, 80), CG, True), ((128, 80, 64), CG, False), ((67, 66, 65), CG, False), ((150, 130, 110), CG, True)])
+def test_single_steps_stream_where_it_pays(recorder, size, kw, streams):
+    """Both sides of each bound of the rule for ordinary accesses, upwards
+    (a lattice that alternates has ordinary ones anyway)."""
+    got = recorder(f"""
+    h = lattice(*{size}, **{kw})
+    print(json.dumps(accesses(h)))
+    """, LBM_TWO_STEP="0")
+    assert got == [[streams, False]] * 2
