@@ -12,6 +12,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <functional>
 #include <vector>
 
 #include "lbm_internal.hpp"
@@ -102,11 +103,17 @@ void launch_pair(lbm_ensemble* e)
 // of one length chosen for all boxes (short runs repeat more planes, long ones
 // leave compute units without work at the end).  The tiles of a run share
 // their halos, so a run stays on one XCD; runs go to the least loaded XCD,
-// the largest first.  Empty where two single steps, at their traffic at
-// 5.55 TB/s, are estimated faster.  Measured, us per step, single / pair: 64
-// boxes of 48, 64 and 96 (31 M nodes) D3Q19 FP32 864 / 608, FP64 1824 / 1203,
-// D3Q27 FP32 1279 / 828; four boxes of 32 to 96 D3Q19 FP32 38.9 / 43.3
-// (single), FP64 78.7 / 65.2.  LBM_TWO_STEP as for the lattice.
+// the largest first.  A pass is estimated as these blocks in this order, each
+// on the XCD's first free compute unit (a block fills one): the boxes' total
+// over all units misses whole rounds of blocks and uneven XCDs.  Empty where
+// two single steps, at their traffic at 5.55 TB/s, and at 7.6 TB/s where the
+// cache holds it, are estimated faster.  Measured over 45 sets of boxes in
+// both lattices and precisions: passes from 0.65 to 1.03 of the single steps'
+// time, the run length within 2 % of the best on average; by the total it was
+// 8 %, and one box of 144^3 D3Q27 FP64 took passes of 1.36.  Us per step,
+// single / pair: 64 boxes of 48, 64 and 96 (31 M nodes) D3Q19 FP32 864 / 608,
+// FP64 1824 / 1203, D3Q27 FP32 1279 / 828; one of 200^3 D3Q27 FP32 345 / 372
+// (single).  LBM_TWO_STEP as for the lattice.
 std::vector<lbm::EnsPairItem> pair_list(const lbm_ensemble* e, int cus)
 {
     const int choice = lbm::two_step_choice();
@@ -120,51 +127,60 @@ std::vector<lbm::EnsPairItem> pair_list(const lbm_ensemble* e, int cus)
         while (e->L[a] != e->L[b]) ++a;
         tile[b] = a < b ? tile[a] : lbm::pair_tile(e->L[b], e->L[b], e->q, e->eb, !e->nt || e->L[b] * e->eb % 128 != 0, threads, &us[b]);
         if (a < b) us[b] = us[a];
+        else if (e->q == 27 && e->eb == 8 && e->L[b] % 8) us[b] *= 1.17; // rows that share half-lines: 1.13 to 1.24
         if (tile[b].w == 0) return {};
     }
-    int best_len = 0;
+    struct Run {
+        int box, z0, len, xcd;
+        double cost; // of all tiles
+    };
+    const int xcd_cus = std::max(1, cus / 8);
+    // runs of at most `len` planes, given to the XCDs, and the estimated time
+    auto plan = [&](int len, std::vector<Run>& runs) {
+        runs.clear();
+        for (int b = 0; b < e->nboxes; ++b) {
+            const int n = (e->L[b] + len - 1) / len, planes = (e->L[b] + n - 1) / n;
+            for (int z = 0; z < e->L[b]; z += planes) {
+                const int l = std::min(planes, e->L[b] - z);
+                runs.push_back({b, z, l, 0, (double)tile[b].tx * tile[b].ty * (l + 2) * us[b]});
+            }
+        }
+        std::stable_sort(runs.begin(), runs.end(), [](const Run& a, const Run& b) { return a.cost > b.cost; });
+        double load[8] = {}, end = 0.0;
+        std::vector<double> busy[8]; // heaps of the units' times, the first free on top
+        for (auto& v : busy) v.assign(xcd_cus, 0.0);
+        for (Run& r : runs) {
+            r.xcd = (int)(std::min_element(load, load + 8) - load);
+            load[r.xcd] += r.cost;
+            std::vector<double>& v = busy[r.xcd];
+            for (int k = tile[r.box].tx * tile[r.box].ty; k > 0; --k) {
+                std::pop_heap(v.begin(), v.end(), std::greater<>());
+                v.back() += (r.len + 2) * us[r.box];
+                end = std::max(end, v.back());
+                std::push_heap(v.begin(), v.end(), std::greater<>());
+            }
+        }
+        return 2.0 + end;
+    };
+    std::vector<Run> runs, best;
     double best_us = 1e300;
     for (int len : {6, 8, 12, 16, 24, 32, 48, 64, 96, 128}) {
-        double total = 0.0, longest = 0.0;
-        for (int b = 0; b < e->nboxes; ++b) {
-            const int runs = (e->L[b] + len - 1) / len, planes = (e->L[b] + runs - 1) / runs;
-            total += (double)tile[b].tx * tile[b].ty * runs * (planes + 2) * us[b];
-            longest = std::max(longest, (planes + 2) * us[b]);
-        }
-        const double t = 2.0 + std::max(total / cus + 0.5 * longest, longest);
-        if (t < best_us) {
-            best_us = t;
-            best_len = len;
+        const double t = plan(len, runs);
+        if (t < 1.005 * best_us) { // of equal ones the longer: it repeats fewer planes
+            best_us = std::min(t, best_us);
+            best.swap(runs);
         }
     }
-    const double single_us = std::max(4.0, 2e-6 * e->q * e->eb * (double)e->nodes / (e->nt ? 5.55 : 6.1));
+    const double single_us = std::max(4.0, 2e-6 * e->q * e->eb * (double)e->nodes / (e->nt ? 5.55 : 7.6));
     if (choice != 1 && best_us > 0.95 * 2 * single_us) return {};
-    struct Run {
-        int box, z0, len;
-        double cost;
-    };
-    std::vector<Run> runs;
-    for (int b = 0; b < e->nboxes; ++b) {
-        const int n = (e->L[b] + best_len - 1) / best_len, len = (e->L[b] + n - 1) / n;
-        for (int z = 0; z < e->L[b]; z += len) {
-            const int l = std::min(len, e->L[b] - z);
-            runs.push_back({b, z, l, (double)tile[b].tx * tile[b].ty * (l + 2) * us[b]});
-        }
-    }
-    std::stable_sort(runs.begin(), runs.end(), [](const Run& a, const Run& b) { return a.cost > b.cost; });
     std::vector<lbm::EnsPairItem> of_xcd[8];
-    double load[8] = {};
-    for (const Run& r : runs) {
-        int x = 0;
-        for (int k = 1; k < 8; ++k)
-            if (load[k] < load[x]) x = k;
-        load[x] += r.cost;
+    for (const Run& r : best) {
         const lbm::PairShape& t = tile[r.box];
         const int L = e->L[r.box], W = t.w + (t.w < L ? 2 : 0);
         for (int iy = 0; iy < t.ty; ++iy)
             for (int ix = 0; ix < t.tx; ++ix)
-                of_xcd[x].push_back({r.box, ix * t.w, iy * t.h, r.z0, std::min(t.w, L - ix * t.w),
-                                     std::min(t.h, L - iy * t.h), r.len, W});
+                of_xcd[r.xcd].push_back({r.box, ix * t.w, iy * t.h, r.z0, std::min(t.w, L - ix * t.w),
+                                         std::min(t.h, L - iy * t.h), r.len, W});
     }
     size_t most = 0;
     for (const auto& v : of_xcd) most = std::max(most, v.size());

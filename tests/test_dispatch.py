@@ -331,3 +331,20 @@ def test_moments_stores(recorder, size, streams):
     assert len(names) == 2
     for name in names:
         assert "k_moments" in name and ("Lb1EEEv" in name) == streams, name
+
+
+@pytest.mark.parametrize("boxes,q,precision,want", [
+    ([200], 27, "LBM_FP32", "single"), ([144], 27, "LBM_FP64", "single"), ([160], 19, "LBM_FP64", "single"),
+    ([80] * 4, 27, "LBM_FP64", "single"), ([100] * 3, 27, "LBM_FP64", "single"), ([32] * 32, 27, "LBM_FP32", "single"), ([64], 19, "LBM_FP32", "single"),
+    ([200], 19, "LBM_FP32", "sweep"), ([48] * 16, 19, "LBM_FP64", "sweep"), ([128] * 2, 27, "LBM_FP32", "sweep"),
+    ([48, 64, 96, 33] * 4, 27, "LBM_FP32", "sweep")])
+def test_ensemble_passes_where_they_are_faster(recorder, boxes, q, precision, want):
+    """The ensemble's estimate counts rounds of whole blocks on each XCD's
+    units: passes of two steps only where they are measured faster."""
+    got = recorder(f"""
+    e = L.lbm_ensemble_create([(n, 1.5) for n in {boxes}], {q}, L.{precision}, STREAM)
+    launched()
+    L.lib().lbm_ensemble_step(e, 4)
+    print(json.dumps(kinds()))
+    """)
+    assert got == [want] * (4 if want == "single" else 2)
