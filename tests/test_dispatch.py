@@ -335,7 +335,8 @@ def test_moments_stores(recorder, size, streams):
 
 @pytest.mark.parametrize("boxes,q,precision,want", [
     ([200], 27, "LBM_FP32", "single"), ([144], 27, "LBM_FP64", "single"), ([160], 19, "LBM_FP64", "single"),
-    ([80] * 4, 27, "LBM_FP64", "single"), ([100] * 3, 27, "LBM_FP64", "single"), ([32] * 32, 27, "LBM_FP32", "single"), ([64], 19, "LBM_FP32", "single"),
+    ([80] * 4, 27, "LBM_FP64", "single"), ([100] * 3, 27, "LBM_FP64", "single"),
+    ([32] * 32, 27, "LBM_FP32", "single"), ([64], 19, "LBM_FP32", "single"),
     ([200], 19, "LBM_FP32", "sweep"), ([48] * 16, 19, "LBM_FP64", "sweep"), ([128] * 2, 27, "LBM_FP32", "sweep"),
     ([48, 64, 96, 33] * 4, 27, "LBM_FP32", "sweep")])
 def test_ensemble_passes_where_they_are_faster(recorder, boxes, q, precision, want):
