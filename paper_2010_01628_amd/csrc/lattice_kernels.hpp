@@ -765,18 +765,12 @@ __device__ inline void block_reduce_store(double v[NDIAG], double* __restrict__ 
     }
 }
 
-// Streaming stores where the fields' rows are whole halves of 128-byte lines:
-// 64^3 FP32 11.3 -> 10.1 us, 128x128x112 FP64 64 -> 55; on rows that share them
-// 201x199x150 FP32 131 -> 138, FP64 208 -> 218.
-inline bool stream_moments(const Geom& g) { return g.nx % 8 == 0; }
-
 // One work-group per (x-block, y-block) covers the planes z = blockIdx.z,
 // blockIdx.z + gridDim.z, ...  A work-group's reduction (96 exchanges between
 // lanes) costs as much as reading a plane's nodes, so callers launch about
 // 4096 work-groups however many planes there are: 384^3 FP16 AA 1085 -> 790
 // us, the sum over the partials (one work-group) 270 -> 5 us.
-// STREAM (stream_moments): streaming hint on rho_out and u_out.
-template <class L, class S, Pattern P, bool WALLS, bool STREAM>
+template <class L, class S, Pattern P, bool WALLS>
 __global__ __launch_bounds__(256) void k_moments(const S* __restrict__ buf, Geom g, Phys ph, double* __restrict__ rho_out,
                                                 double* __restrict__ u_out, double* __restrict__ partials)
 {
@@ -807,11 +801,11 @@ __global__ __launch_bounds__(256) void k_moments(const S* __restrict__ buf, Geom
         const double ux = (jx + 0.5 * (double)Fx) / rho;
         const double uy = (jy + 0.5 * (double)Fy) / rho;
         const double uz = (jz + 0.5 * (double)Fz) / rho;
-        if (rho_out) st<double, STREAM>(rho_out + n, rho);
+        if (rho_out) __builtin_nontemporal_store(rho, rho_out + n);
         if (u_out) {
-            st<double, STREAM>(u_out + n, ux);
-            st<double, STREAM>(u_out + g.N + n, uy);
-            st<double, STREAM>(u_out + 2 * (int64_t)g.N + n, uz);
+            __builtin_nontemporal_store(ux, u_out + n);
+            __builtin_nontemporal_store(uy, u_out + g.N + n);
+            __builtin_nontemporal_store(uz, u_out + 2 * (int64_t)g.N + n);
         }
         const double u2 = ux * ux + uy * uy + uz * uz;
         double w[NDIAG];
@@ -972,11 +966,7 @@ template <class L, class S> struct Launch {
     static void moments(int pattern, bool walls, const void* buf, const Geom& g, const Phys& ph, double* rho, double* u,
                         double* partials, dim3 grid, dim3 block, hipStream_t st)
     {
-        if (stream_moments(g)) {
-            LBM_DISPATCH_PWX(k_moments, LBM_STREAMING, (const S*)buf, g, ph, rho, u, partials);
-        } else {
-            LBM_DISPATCH_PWX(k_moments, LBM_ORDINARY, (const S*)buf, g, ph, rho, u, partials);
-        }
+        LBM_DISPATCH_PW(k_moments, (const S*)buf, g, ph, rho, u, partials);
     }
 #undef LBM_DISPATCH_PW
 #undef LBM_DISPATCH_PWX

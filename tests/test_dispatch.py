@@ -316,23 +316,6 @@ def test_learned_in_place_steps_in_turn(recorder):
     assert got == [TURN, NT]
 
 
-@pytest.mark.parametrize("size,streams", [((96, 64, 40), True), ((200, 64, 40), True), ((201, 64, 40), False)])
-def test_moments_stores(recorder, size, streams):
-    """The fields of lbm_moments are stored with the streaming hint only where
-    rows do not share half-lines."""
-    names = recorder(f"""
-    h = lattice(*{size})
-    r, u = np.zeros({size[0] * size[1] * size[2]}), np.zeros({3 * size[0] * size[1] * size[2]})
-    launched()
-    L.lbm_moments(h, r.ctypes.data, u.ctypes.data, None, True)
-    L.lbm_moments_noalloc(h, r.ctypes.data, u.ctypes.data, None)
-    print(json.dumps([n for n, _, _ in launched()]))
-    """)
-    assert len(names) == 2
-    for name in names:
-        assert "k_moments" in name and ("Lb1EEEv" in name) == streams, name
-
-
 @pytest.mark.parametrize("boxes,q,precision,want", [
     ([200], 27, "LBM_FP32", "single"), ([144], 27, "LBM_FP64", "single"), ([160], 19, "LBM_FP64", "single"),
     ([80] * 4, 27, "LBM_FP64", "single"), ([100] * 3, 27, "LBM_FP64", "single"),
