@@ -191,14 +191,13 @@ typedef struct {
                                  through LDS on periodic lattices */
     int32_t cache_policy;     /* population loads/stores: 0 = library default (non-temporal
                                  for staged steps and for A-B with 4- and 8-byte storage,
-                                 cached otherwise; cached too where the last-level cache
-                                 keeps the state between steps, buffers from 24 MB (q = 19;
-                                 34 MB q = 27, 62.5 MB Shan-Chen and colour gradient) up to
-                                 256 MiB together, or where larger states' rows are not whole
-                                 128-byte lines; and for single steps of plain, learned and
-                                 magnetic lattices that take the planes upwards and downwards
-                                 in turn: one buffer up to 800 MB, two with 4- or 8-byte
-                                 storage of 250 to 300 MB, or 400 or 480 MB),
+                                 cached otherwise; cached too where the buffers hold 24 MB
+                                 each (of all lattices) or more, and at most 256 MiB
+                                 together or, but for colour-gradient lattices, x rows that
+                                 are not whole 128-byte lines; and for single steps of plain,
+                                 learned and magnetic lattices that take the planes upwards
+                                 and downwards in turn: one buffer of 24 to 800 MB, or two
+                                 with 4- or 8-byte storage of 256 MiB to 480 MB together),
                                  1 = non-temporal (streaming) hints, planes always upwards,
                                  2 = ordinary cached accesses.  Passes of two steps read
                                  with ordinary accesses; large lattices' passes store by

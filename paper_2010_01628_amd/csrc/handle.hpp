@@ -49,35 +49,6 @@ inline bool single_ordinary(const StepState& s)
     if (s.coupled == LBM_COUPLED_PHASE) return s.elem_bytes == 4;
     return s.coupled != LBM_COUPLED_SHAN_CHEN || s.bytes <= 480000000;
 }
-// Whether single steps go through the planes upwards and downwards in turn,
-// with ordinary accesses: each starts with the planes that the step before
-// took last, which the last-level cache still holds.  `streams`: whether they
-// would go upwards with streaming accesses otherwise.  us per step, otherwise
-// / in turn:
-//   two buffers, streaming: FP32 128x128x112 (279 MB) 53.1 / 45.2, 128^3 (319 MB)
-//   54.9 / 54.5 and learned 56.8 / 60.5, 160x128x128 (398 MB) 73.0 / 77.9; FP64
-//   128x96x96 (359 MB) 69.6 / 60.2, 128x128x96 (478 MB) 86.8 / 87.9; magnetic
-//   128x96x96 (377 MB) 85.2 / 69.1, 128x128x96 (503 MB) 93.4 / 93.7; 2-byte storage
-//   192^3 97.8 / 100.5
-//   two buffers, ordinary: FP32 144x144x140 (441 MB) 91.5 / 87.3, FP64 121x113x101
-//   (420 MB) 94.8 / 86.9; below 250 MB the cache holds both (FP32 128x100x120 35.9 / 36.4)
-//   one buffer: FP32 160^3 (311 MB) 118 / 107, 192^3 (538 MB) 195 / 171, 256^3 (1.3 GB)
-//   422 / 440; in the cache, whole lines, 96^3 22.6 / 21.6, shared ones D3Q27
-//   67x66x65 (31 MB) 16.0 / 16.6, FP64 60^3 11.8 / 12.5
-//   one buffer of 2 bytes, streaming: 192^3 (269 MB) 83.2 / 84.9, 256x192x160 (299
-//   MB) 93.8 / 98.4, 256x224x192 (418 MB) 136.5 / 137.2, 256x256x192 (478 MB) 153.9 /
-//   148.1, 256^3 206.5 / 202.7; learned 192^3 151.5 / 133.1, 256x192x192 195.7 / 183.3
-inline bool alternate_planes(const StepState& s, bool streams, bool learned)
-{
-    if (s.coupled != LBM_COUPLED_NONE && s.coupled != LBM_COUPLED_MAGNETIC) return false;
-    if (s.buffers == 2) {
-        const int64_t most = !streams ? 480000000 : s.elem_bytes == 8 || s.coupled ? 400000000 : 300000000;
-        return s.elem_bytes >= 4 && s.bytes > 250000000 && s.bytes <= most;
-    }
-    if (s.bytes > 800000000) return false;
-    if (streams && s.elem_bytes == 2 && !learned) return s.bytes >= 450000000;
-    return s.bytes >= (s.whole_lines ? 24000000 : 250000000);
-}
 
 } // namespace lbm
 
@@ -113,7 +84,6 @@ struct lbm_handle {
     bool pair_ok = false;              // lbm_step takes two steps per pass where it can
     bool cached = false;               // passes of two steps without the streaming hint (ordinary_accesses)
     bool alternate = false;            // single steps take the planes upwards and downwards in turn
-    bool alternate_net = false;        // the same for learned steps
     bool walls = false, general = false, nt = true;
     int64_t bytes = 0;
     int nblocks = 0;

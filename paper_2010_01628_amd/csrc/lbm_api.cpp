@@ -400,9 +400,8 @@ int lbm_create(const lbm_params* p, void* stream, lbm_handle** out)
                                     whole_rows || (p->coupled == LBM_COUPLED_NONE && h->g.row_stage)};
         const bool ordinary = p->cache_policy == 2 || (p->cache_policy == 0 && lbm::single_ordinary(single));
         h->cached = p->cache_policy == 2 || (p->cache_policy == 0 && lbm::ordinary_accesses(bytes, nbuf, (int64_t)p->nx * eb));
-        const bool streams = h->nt && !ordinary;
-        h->alternate = p->cache_policy != 1 && lbm::alternate_planes(single, streams, false);
-        h->alternate_net = p->cache_policy != 1 && lbm::alternate_planes(single, streams, true);
+        h->alternate = p->cache_policy != 1 && lbm::alternate_planes(bytes, nbuf, eb) &&
+                       (p->coupled == LBM_COUPLED_NONE || p->coupled == LBM_COUPLED_MAGNETIC);
         if (ordinary || (h->alternate && p->cache_policy == 0)) h->nt = false;
         set_pair(h, h->cached, bytes <= ((int64_t)256 << 20));
     }
@@ -501,7 +500,7 @@ int lbm_step(lbm_handle* h, int64_t nsteps)
     if (nsteps < 0) return fail(LBM_EINVAL, "nsteps < 0");
     int64_t pairs = h->pair_ok ? lbm::pairs_in(nsteps, h->stream) : 0; // passes of two steps left
     for (int64_t s = 0; s < nsteps; ++s) {
-        h->g.rev = (h->mlp ? h->alternate_net : h->alternate) ? (int)(h->steps & 1) : 0;
+        h->g.rev = h->alternate ? (int)(h->steps & 1) : 0;
         const int pat = pattern_of(h);
         const int src = h->cur;
         const int dst = h->p.streaming == LBM_AB ? 1 - h->cur : h->cur;
@@ -521,8 +520,8 @@ int lbm_step(lbm_handle* h, int64_t nsteps)
             continue;
         }
         if (h->mlp)
-            lbm::launch_step_mlp(h->p.precision, pat, h->walls, h->nt && h->alternate_net == h->alternate, h->buf[src],
-                                 h->buf[dst], h->g, h->ph, h->mlp->packed, h->fb_partials, h->grid, h->block, h->stream);
+            lbm::launch_step_mlp(h->p.precision, pat, h->walls, h->nt, h->buf[src], h->buf[dst], h->g, h->ph,
+                                 h->mlp->packed, h->fb_partials, h->grid, h->block, h->stream);
         else if (pairs > 0 && s + 1 < nsteps && !(h->p.check_every > 0 && (h->steps + 1) % h->p.check_every == 0)) {
             // two steps in one pass, unless a stability check falls between them
             uint32_t key2 = 0;

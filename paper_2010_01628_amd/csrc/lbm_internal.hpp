@@ -120,6 +120,21 @@ inline bool ordinary_accesses(int64_t bytes, int buffers, int64_t row_bytes)
 {
     return bytes >= (int64_t)24000000 * buffers && (bytes <= ((int64_t)256 << 20) || row_bytes % 128 != 0);
 }
+// Whether single steps go through the planes upwards and downwards in turn,
+// with ordinary accesses: each starts with the planes that the step before
+// took last, which the last-level cache still holds.  That pays up to about
+// three times its size in place (AA) and twice with two buffers.  Always
+// upwards, streaming / in turn, us per step: AA FP32 160^3 (311 MB) 115 / 89,
+// 192^3 196 / 160, FP16 256^3 (637 MB) 204 / 191, FP32 256^3 (1.3 GB) 419 / 433;
+// A-B FP32 144^3 (454 MB) 101 / 89, FP16 192^3 (538 MB) 96 / 97, FP64 96^3 (269
+// MB) 53 / 37; magnetic 96x128x96 (377 MB) 90 / 72, 128x160x128 (839 MB) 156 /
+// 158.  Two buffers that fit the cache gain nothing (FP16 144^3 35.7 / 36.1),
+// nor do they with 2-byte storage (160^3, 311 MB, 75 / 76).
+inline bool alternate_planes(int64_t bytes, int buffers, int elem_bytes)
+{
+    if (buffers == 1) return bytes >= 24000000 && bytes <= 800000000;
+    return elem_bytes >= 4 && bytes > ((int64_t)256 << 20) && bytes <= 480000000;
+}
 // LBM_TWO_STEP: 0 keeps single steps, 1 takes passes of two wherever they are
 // possible; -1: by the estimates.  Without it, a variable that picks a launch
 // or an addressing of the single step keeps single steps, which it is about.

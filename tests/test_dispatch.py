@@ -265,57 +265,6 @@ def test_single_steps_stream_where_it_pays(recorder, size, kw, streams):
     assert got == [[streams, False]] * 2
 
 
-UP, TURN, NT = [[False, False]] * 2, [[False, False], [False, True]], [[True, False]] * 2
-
-
-@pytest.mark.parametrize("size,kw,want", [
-    # two buffers, whole lines
-    ((128, 128, 100), dict(), UP), ((128, 128, 104), dict(), TURN), ((128, 128, 112), dict(), TURN),  # 249, 259, 279 MB
-    ((128, 128, 128), dict(), NT), ((160, 128, 128), dict(), NT),                            # 319, 398 MB
-    ((128, 96, 96), dict(precision="fp64"), TURN), ((128, 128, 96), dict(precision="fp64"), NT),  # 359, 478 MB
-    ((128, 96, 96), MHD, TURN), ((128, 128, 96), MHD, NT),                                        # 377, 503 MB
-    ((128, 128, 96), dict(q=27), NT),                                                             # 340 MB
-    ((192, 192, 160), dict(precision="fp16"), NT),                                                # 448 MB
-    # two buffers, rows that share lines
-    ((144, 144, 140), dict(), TURN), ((161, 144, 140), dict(), UP),                                   # 441, 493 MB
-    ((144, 144, 140), dict(cache_policy=1), NT), ((128, 128, 128), dict(cache_policy=2), TURN),
-    # one buffer
-    ((96, 96, 80), dict(streaming="aa"), TURN), ((75, 75, 75), dict(streaming="aa"), UP),             # 56, 32 MB
-    ((170, 150, 141), dict(streaming="aa"), TURN),                                                    # 273 MB
-    ((192, 192, 192), dict(streaming="aa"), TURN), ((224, 224, 224), dict(streaming="aa"), UP),       # 538, 854 MB
-    ((256, 256, 192), dict(streaming="aa"), NT),                                                  # 956 MB
-    ((192, 192, 160), dict(streaming="aa", precision="fp16"), TURN),                                  # 224 MB
-    ((256, 192, 160), dict(streaming="aa", precision="fp16"), NT),                                # 299 MB
-    ((256, 256, 192), dict(streaming="aa", precision="fp16"), TURN),                                  # 478 MB
-    ((224, 192, 192), dict(streaming="aa", precision="fp16"), TURN),                                  # 314 MB, not staged
-])
-def test_planes_in_turn_where_it_pays(recorder, size, kw, want):
-    """Both sides of each bound of the rule for planes upwards and downwards
-    in turn."""
-    got = recorder(f"""
-    h = lattice(*{size}, **{kw})
-    print(json.dumps(accesses(h)))
-    """, LBM_TWO_STEP="0")
-    # (the AA even step has its own loads' hint; its stores' is the rule's)
-    assert got == want
-
-
-def test_learned_in_place_steps_in_turn(recorder):
-    """The learned step of 2-byte storage in place takes the planes in turn
-    between 256 MiB and 450 MB too, where the plain one streams upwards, and
-    the plain one is as before when the network is detached."""
-    got = recorder("""
-    h = lattice(256, 192, 160, streaming="aa", precision="fp16")
-    m = L.lbm_mlp_create(None, np.ones(11, dtype=np.float32), STREAM)
-    L.lbm_set_mlp(h, m)
-    out = [accesses(h)]
-    L.lbm_set_mlp(h, None)
-    out.append(accesses(h))
-    print(json.dumps(out))
-    """)
-    assert got == [TURN, NT]
-
-
 @pytest.mark.parametrize("boxes,q,precision,want", [
     ([200], 27, "LBM_FP32", "single"), ([144], 27, "LBM_FP64", "single"), ([160], 19, "LBM_FP64", "single"),
     ([80] * 4, 27, "LBM_FP64", "single"), ([100] * 3, 27, "LBM_FP64", "single"),

@@ -78,18 +78,19 @@ def test_magnetic(size):
 
 
 @pytest.mark.parametrize("size,precision,kw", [
-    ((128, 128, 112), "fp32", {}),                    # 279 MB, staged rows of whole lines
-    ((128, 128, 112), "fp32", {"walls_y": True}),     # direct reads
+    ((128, 128, 128), "fp32", {}),                    # 319 MB, staged rows of whole lines
+    ((128, 128, 128), "fp32", {"walls_y": True}),     # direct reads
     ((144, 144, 140), "fp32", {}),                    # 441 MB, ragged rows
     ((144, 144, 140), "fp32", {"walls_y": True}),
-    ((128, 96, 96), "fp64", {}),                      # 359 MB
+    ((96, 96, 104), "fp64", {}),                      # 291 MB
     ((128, 100, 100), "fp32", {"q": 27}),             # 276 MB
     ((128, 100, 100), "fp32", {"moments": "raw", "q": 27}),
+    ((128, 160, 140), "fp32", {}),                    # 436 MB
     ((128, 160, 160), "fp32", {}),                    # 498 MB: beyond the rule, always upwards
 ])
 def test_two_buffers_in_turn(size, precision, kw, monkeypatch):
     """A-B single steps upwards and downwards in turn: two buffers that hold
-    250 MB to 300, 400 or 480 MB."""
+    256 MiB to 480 MB."""
     import torch
 
     runs = [_flow(size, (3, 2), "0", monkeypatch, precision=precision, cache_policy=c, **kw) for c in (0, 1)]
@@ -97,13 +98,10 @@ def test_two_buffers_in_turn(size, precision, kw, monkeypatch):
     assert torch.equal(runs[0], runs[1])
 
 
-@pytest.mark.parametrize("size,precision,streaming,walls", [
-    ((128, 128, 112), "fp32", "ab", False), ((128, 128, 112), "fp32", "ab", True), ((144, 144, 140), "fp32", "ab", False),
-    ((256, 192, 160), "fp16", "aa", False)])  # 299 MB in place: in turn with the network only
-def test_two_buffers_in_turn_learned(size, precision, streaming, walls, monkeypatch):
+@pytest.mark.parametrize("size,walls", [((128, 128, 128), False), ((128, 128, 128), True), ((144, 144, 140), False)])
+def test_two_buffers_in_turn_learned(size, walls, monkeypatch):
     import torch
 
-    runs = [_flow(size, (3, 2), "0", monkeypatch, learned=True, precision=precision, streaming=streaming, cache_policy=c,
-                  walls_y=walls) for c in (0, 1)]
+    runs = [_flow(size, (3, 2), "0", monkeypatch, learned=True, precision="fp32", cache_policy=c, walls_y=walls) for c in (0, 1)]
     assert torch.isfinite(runs[0]).all()
     assert torch.equal(runs[0], runs[1])
