@@ -673,13 +673,17 @@ __global__ __launch_bounds__(256) void k_set_pops(S* __restrict__ buf, Geom g, d
     for (int i = 0; i < L::Q; ++i) s[i] = (R)(ld<double, STREAM>(f + (int64_t)i * g.N + n) - L::w(i) * rho0);
     place_state<L, S, P, WALLS>(buf, g.stride, d, s);
 }
-// 2-byte storage, where f does not fit the last-level cache: 192^3 FP16 A-B 265
-// -> 240 us, 160^3 BF16 AA 160 -> 142, 201x199x150 FP16 250 -> 234; FP32 gains on
-// some sizes and loses on others (128^3 98 -> 88, 256x256x192 511 -> 529,
-// 201x199x150 287 -> 339)
+// 2- and 4-byte storage, where f does not fit the last-level cache; the state
+// then stays there for the next steps.  192^3 FP16 A-B 265 -> 240 us, 160^3 BF16 AA
+// 160 -> 142, 201x199x150 FP16 250 -> 234.  FP32 where f's rows are whole 128-byte
+// lines too, or the state of half f's size fits: restore and two steps 128^3 206 ->
+// 190, 256x96x100 AA 212 -> 188, D3Q27 192x160x128 (849 MB) 591 -> 555, 150x130x110
+// (326 MB) 263 -> 244, but 201x199x150 (911 MB) 711 -> 761, D3Q27 180x180x100
+// (699 MB) 602 -> 625
 template <class S> inline bool stream_set(const Geom& g, int q)
 {
-    return sizeof(S) == 2 && (int64_t)g.N * q * 8 > ((int64_t)256 << 20);
+    const int64_t f = (int64_t)g.N * q * 8, cache = (int64_t)256 << 20;
+    return f > cache && (sizeof(S) == 2 || (sizeof(S) == 4 && (g.nx % 16 == 0 || f <= 2 * cache)));
 }
 
 // The state's populations to f.  STREAM (stream_get): streaming hint on f.
@@ -699,11 +703,19 @@ __global__ __launch_bounds__(256) void k_get_pops(const S* __restrict__ buf, Geo
 #pragma unroll
     for (int i = 0; i < L::Q; ++i) st<double, STREAM>(f + (int64_t)i * g.N + n, L::w(i) * rho0 + (double)s[i]);
 }
-// 4- and 8-byte storage, where f's rows are whole halves of 128-byte lines:
-// 200x101x75 FP32 70 -> 56 us, 128^3 93 -> 70, D3Q27 FP64 96^3 74 -> 55; rows that
-// share them lose (201x199x150 FP32 304 -> 340, D3Q27 434 -> 518, 100^3 37 -> 42),
-// and so does 2-byte storage (192^3 FP16 AA 249 -> 267)
-template <class S> inline bool stream_get(const Geom& g) { return sizeof(S) >= 4 && g.nx % 8 == 0; }
+// 4- and 8-byte storage.  Where f's rows are whole halves of 128-byte lines:
+// 200x101x75 FP32 70 -> 56 us, 128^3 93 -> 70, D3Q27 FP64 96^3 74 -> 55 (2-byte
+// storage loses, 192^3 FP16 AA 249 -> 267).  On rows that share them only where
+// ordinary stores would push a state out of the cache that is there, us for two
+// steps and f: FP32 AA 180x180x100 (state 246, f 492 MB) 357 -> 312, A-B 100^3 (304,
+// 152) 108 -> 103, FP64 100x101x75 (230, 115) 134 -> 117; but FP32 AA 100^3 (76, 152)
+// 99 -> 103, FP64 150x130x110 (652, 326) 461 -> 489, FP32 AA 161x160x159 (311, 622)
+// 473 -> 495
+template <class S> inline bool stream_get(const Geom& g, int q, int buffers)
+{
+    const int64_t f = (int64_t)g.N * q * 8, state = (int64_t)g.N * q * (int64_t)sizeof(S) * buffers, cache = (int64_t)256 << 20;
+    return sizeof(S) >= 4 && (g.nx % 8 == 0 || (state + f > cache && f <= 2 * cache && state <= 480000000));
+}
 
 // ---------------------------------------------------------------------------
 // Macroscopic fields and FP64 diagnostics.  Each block reduces its nodes with
@@ -944,7 +956,7 @@ template <class L, class S> struct Launch {
     static void set_pops(int pattern, bool walls, void* buf, const Geom& g, double rho0, const double* f, dim3 grid,
                          dim3 block, hipStream_t st)
     {
-        if constexpr (sizeof(S) == 2) {
+        if constexpr (sizeof(S) < 8) {
             if (stream_set<S>(g, L::Q)) {
                 LBM_DISPATCH_PWX(k_set_pops, LBM_STREAMING, (S*)buf, g, rho0, f);
                 return;
@@ -956,7 +968,7 @@ template <class L, class S> struct Launch {
                          dim3 block, hipStream_t st)
     {
         if constexpr (sizeof(S) >= 4) {
-            if (stream_get<S>(g)) {
+            if (stream_get<S>(g, L::Q, pattern == AB ? 2 : 1)) {
                 LBM_DISPATCH_PWX(k_get_pops, LBM_STREAMING, (const S*)buf, g, rho0, f);
                 return;
             }

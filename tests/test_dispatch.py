@@ -205,16 +205,21 @@ def test_benchmark_ensemble_takes_passes_of_two_steps(recorder):
     assert got == [["sweep"] * 2] * 2
 
 
-@pytest.mark.parametrize("size,precision,streams", [
-    ((96, 64, 40), "fp32", True), ((200, 64, 40), "fp64", True),    # get: rows of whole halves of lines
-    ((100, 64, 40), "fp32", False), ((201, 64, 40), "fp64", False), # ... rows that share them
-    ((96, 64, 40), "fp16", False)])
-def test_checkpoint_stores(recorder, size, precision, streams):
-    """lbm_get_populations stores with the streaming hint only where rows do
-    not share half-lines, and not from 2-byte storage."""
+@pytest.mark.parametrize("size,kw,streams", [
+    ((96, 64, 40), dict(), True), ((200, 64, 40), dict(precision="fp64"), True),     # rows of whole halves of lines
+    ((100, 64, 40), dict(), False), ((201, 64, 40), dict(precision="fp64"), False),  # shared ones: all in the cache
+    ((100, 100, 100), dict(), True), ((100, 100, 100), dict(streaming="aa"), False),  # state 152 and 76 MB, f 152
+    ((180, 180, 100), dict(streaming="aa"), True), ((161, 160, 159), dict(streaming="aa"), False),  # f 492, 622 MB
+    ((118, 52, 170), dict(precision="fp64"), True), ((150, 130, 110), dict(precision="fp64"), False),  # state 317, 652
+    ((150, 130, 110), dict(), True), ((150, 130, 110), dict(q=27), True), ((180, 180, 100), dict(q=27), False),
+    ((96, 64, 40), dict(precision="fp16"), False)])
+def test_checkpoint_stores(recorder, size, kw, streams):
+    """lbm_get_populations stores with the streaming hint where rows do not
+    share half-lines, or where the state would leave the last-level cache, and
+    not from 2-byte storage."""
     name = recorder(f"""
-    h = lattice(*{size}, precision={precision!r})
-    f = np.zeros(19 * {size[0] * size[1] * size[2]})
+    h = lattice(*{size}, **{kw})
+    f = np.zeros(27 * {size[0] * size[1] * size[2]})
     launched()
     L.lbm_get_populations(h, f.ctypes.data, True)
     print(json.dumps(launched()[0][0]))
@@ -224,10 +229,13 @@ def test_checkpoint_stores(recorder, size, precision, streams):
 
 @pytest.mark.parametrize("size,precision,streams", [
     ((96, 96, 90), "fp16", False), ((128, 128, 110), "bf16", True), ((201, 97, 93), "fp16", True),
-    ((128, 128, 110), "fp32", False), ((201, 97, 93), "fp32", False), ((96, 96, 90), "fp32", False)])
+    ((96, 96, 90), "fp32", False), ((128, 128, 110), "fp32", True), ((192, 160, 128), "fp32", True),  # 126, 274, 598 MB
+    ((150, 130, 110), "fp32", True), ((201, 199, 100), "fp32", False), ((200, 200, 100), "fp32", False),  # 326, 608
+    ((128, 128, 128), "fp64", False)])
 def test_restore_loads(recorder, size, precision, streams):
-    """lbm_set_populations reads with the streaming hint only into 2-byte
-    storage, from arrays larger than the last-level cache."""
+    """lbm_set_populations reads arrays larger than the last-level cache with
+    the streaming hint: into 2-byte storage, and into 4-byte storage on whole
+    lines or where the state fits the cache."""
     name = recorder(f"""
     h = lattice(*{size}, precision={precision!r})
     f = np.zeros(19 * {size[0] * size[1] * size[2]})
