@@ -192,9 +192,13 @@ typedef struct {
     int32_t cache_policy;     /* population loads/stores: 0 = library default (non-temporal
                                  for staged steps and for A-B with 4- and 8-byte storage,
                                  cached otherwise; cached too where the buffers hold 24 MB
-                                 each (of all lattices) or more, and at most 256 MiB
-                                 together or, but for colour-gradient lattices, x rows that
-                                 are not whole 128-byte lines; and for single steps of plain,
+                                 each (of all lattices; single steps with q = 27 34 MB,
+                                 Shan-Chen 45, colour gradient 62.5, or 30 on rows that are
+                                 not whole 128-byte lines) or more, and at most 256 MiB
+                                 together or, but for colour-gradient lattices and
+                                 Shan-Chen beyond 480 MB, rows that are not whole lines
+                                 (single steps: not whole together where a work-group
+                                 stages several); and for single steps of plain,
                                  learned and magnetic lattices that take the planes upwards
                                  and downwards in turn: one buffer of 24 to 800 MB, or two
                                  with 4- or 8-byte storage of 256 MiB to 480 MB together),

@@ -29,24 +29,25 @@ struct StepState {
 //   MB) 9.6 / 10.7, 64x64x80 14.9 / 13.0
 //   magnetic FP32 64^3 16.5 / 13.6, two-phase FP32 64x64x80 17.4 / 15.4
 //   Shan-Chen and two colours, which read a lattice twice: Shan-Chen FP32 64x80x80
-//   (62 MB) 16.8 / 18.6, FP64 64x64x80 (100 MB) 25.1 / 26.0, FP32 96^3 (134 MB) 42.9 /
-//   36.8; two colours FP32 64x64x80 (100 MB) 24.5 / 26.0, 128x80x64 (199 MB) 57.0 / 47.0;
+//   (62 MB) 16.8 / 18.6, FP64 64^3 (80 MB) 18.5 / 20.4, 64x64x80 (100 MB) 23.6 / 24.3,
+//   FP32 128x80x64 (100 MB) 27.5 / 25.0, FP64 80x80x64 (125 MB) 39.1 / 31.6; two colours
+//   FP32 64x64x80 (100 MB) 24.5 / 25.6, 128x80x64 (199 MB) 57.0 / 47.0;
 //   on rows that share lines Shan-Chen FP32 72x72x64 (50 MB) 15.7 / 16.4, 75^3 (64 MB)
 //   23.1 / 21.2
 // Beyond the cache only rows that share lines gain: plain FP32 201x199x150 (912
 // MB) 265 / 210, D3Q27 437 / 306, FP64 170x150x141 273 / 233, magnetic FP32
-// 170x150x141 349 / 304, two-phase FP32 201x199x150 356 / 329 but FP64 100^3 (416 MB)
-// 98.2 / 103.4; Shan-Chen FP32 150x140x130 (415 MB) 131 / 125, 201x199x150 (912 MB)
+// 170x150x141 349 / 304, two-phase FP32 201x199x150 356 / 329, FP64 97x90x80 (290 MB)
+// 87.1 / 80.2, 201x199x100 445 / 429, though 100^3 (416 MB) 97.3 / 102.7; Shan-Chen FP32 150x140x130 (415 MB) 131 / 125, 201x199x150 (912 MB)
 // 271 / 276; two colours FP32 150x130x110 (652 MB) 192 / 201.  Whole lines: FP32 A-B
 // 256x96x100 65.7 / 70.0, FP16 AA 192^3 83 / 94.
 inline bool single_ordinary(const StepState& s)
 {
     const bool twice = s.coupled == LBM_COUPLED_SHAN_CHEN || s.coupled == LBM_COUPLED_COLOUR;
-    const double least = twice ? (s.whole_lines ? 62.5e6 : 30e6) : s.coupled ? 24e6 : 24e6 * s.q / 19;
+    const double whole = s.coupled == LBM_COUPLED_COLOUR ? 62.5e6 : 45e6;
+    const double least = twice ? (s.whole_lines ? whole : 30e6) : s.coupled ? 24e6 : 24e6 * s.q / 19;
     if ((double)s.bytes < least * s.buffers) return false;
     if (s.bytes <= ((int64_t)256 << 20)) return true;
     if (s.whole_lines || s.coupled == LBM_COUPLED_COLOUR) return false;
-    if (s.coupled == LBM_COUPLED_PHASE) return s.elem_bytes == 4;
     return s.coupled != LBM_COUPLED_SHAN_CHEN || s.bytes <= 480000000;
 }
 

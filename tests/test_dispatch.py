@@ -259,8 +259,10 @@ PHASE = dict(phase=dict(rho_light=1.0, rho_heavy=10.0, sigma=1e-3, width=4.0, mo
     ((160, 160, 128), dict(), True), ((161, 160, 128), dict(), False),            # 498 MB: whole lines, shared ones
     ((48, 300, 230), dict(), True), ((48, 300, 230), dict(walls_y=True), False),  # 503 MB: staged rows fill lines
     ((64, 64, 48), MHD, False),
-    ((64, 64, 80), PHASE, False), ((170, 150, 141), PHASE, False), ((100, 100, 100), dict(precision="fp64", **PHASE), True),
-    ((64, 80, 80), SC, True), ((96, 96, 96), SC, False), ((64, 64, 80), dict(precision="fp64", **SC), True),
+    ((64, 64, 80), PHASE, False), ((170, 150, 141), PHASE, False), ((97, 90, 80), dict(precision="fp64", **PHASE), False),
+    ((128, 128, 128), PHASE, True),
+    ((64, 80, 80), SC, True), ((64, 64, 64), dict(precision="fp64", **SC), True), ((128, 80, 64), SC, False),
+    ((80, 80, 64), dict(precision="fp64", **SC), False), ((96, 96, 96), SC, False),
     ((72, 72, 64), SC, True), ((75, 75, 75), SC, False), ((150, 140, 130), SC, False), ((201, 199, 150), SC, True),
     ((64, 64, 80), CG, True), ((128, 80, 64), CG, False), ((67, 66, 65), CG, False), ((150, 130, 110), CG, True)])
 def test_single_steps_stream_where_it_pays(recorder, size, kw, streams):
