@@ -37,9 +37,10 @@ struct StepState {
 // Beyond the cache only rows that share lines gain: plain FP32 201x199x150 (912
 // MB) 265 / 210, D3Q27 437 / 306, FP64 170x150x141 273 / 233, magnetic FP32
 // 170x150x141 349 / 304, two-phase FP32 201x199x150 356 / 329, FP64 97x90x80 (290 MB)
-// 87.1 / 80.2, 201x199x100 445 / 429, though 100^3 (416 MB) 97.3 / 102.7; Shan-Chen FP32 150x140x130 (415 MB) 131 / 125, 201x199x150 (912 MB)
-// 271 / 276; two colours FP32 150x130x110 (652 MB) 192 / 201.  Whole lines: FP32 A-B
-// 256x96x100 65.7 / 70.0, FP16 AA 192^3 83 / 94.
+// 87.1 / 80.2, 201x199x100 445 / 429, though 100^3 (416 MB) 97.3 / 102.7; Shan-Chen
+// FP32 150x140x130 (415 MB) 131 / 125, 201x199x150 (912 MB) 271 / 276; two colours
+// FP32 150x130x110 (652 MB) 192 / 201.  Whole lines: FP32 A-B 256x96x100 65.7 / 70.0,
+// FP16 AA 192^3 83 / 94 (both upwards; in turn 60 and 72).
 inline bool single_ordinary(const StepState& s)
 {
     const bool twice = s.coupled == LBM_COUPLED_SHAN_CHEN || s.coupled == LBM_COUPLED_COLOUR;
